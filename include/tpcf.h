@@ -293,7 +293,8 @@ int tpcf_cancel(tpcf_ctx *ctx, int64_t job);
 
 /* Launch shape of later launches (set by the autotuner; defaults are fine).
  * Every field 0 takes the default.
- * rows_per_lane   2 or 4 rows held in registers per lane (default 4);
+ * rows_per_lane   2 or 4: a wavefront covers 64 times as many rows (default
+ *                 4; unpruned FP32 launches of fewer than 2^29 pairs: 2);
  * hist_copies     LDS histogram copies per wavefront, 4, 8, 16 or 32
  *                 (default 16); a value above what the slot count allows
  *                 (32 up to 46 slots, 16 up to 94, 8 up to 190, else 4) is
@@ -303,17 +304,11 @@ int tpcf_cancel(tpcf_ctx *ctx, int64_t job);
  * blocks_per_cu   grid size per compute unit, <= 64 (default: the blocks
  *                 that fit at once; wavefronts take work from a queue);
  * lut_bytes       largest cell table held in LDS, 4096..33792 bytes
- *                 (default 24576; for wrapped tables 32768, which then also
- *                 hold the histograms and thresholds);
- * lut_direct      1: FP32 byte tables in the wrapped layout: the kernel
- *                 starts its sum for q at a floor q0 (a power of two below
- *                 a quarter of the smallest threshold), so every key lies in
- *                 one window of cells, and reads cell (bits(q) >> shift)
- *                 mod 2^w with one bitfield extract instead of a shift, a
- *                 clamp and an add; the table's unused part holds the
- *                 histograms (see tpcf_compile_wrap32).  Falls back to the
- *                 clamped layout when nothing fits.  0 (default): the table
- *                 starts at the first edge and the key is clamped;
+ *                 (default: what the kernel's occupancy leaves, at most
+ *                 24576, which also limits larger values);
+ * lut_direct      0 or 1; accepted and reported, without effect on the
+ *                 launches (the wrapped table layout it asked for can still
+ *                 be compiled on the host, see tpcf_compile_wrap32);
  * prune           1: exact tile pruning.  Bounding caps of the column
  *                 catalog's aligned 64-point groups (built on first use,
  *                 4 doubles per group) and of each wavefront's rows bound the
@@ -376,9 +371,9 @@ typedef struct tpcf_counters {
     uint64_t two_slot_steps;  /* steps where each lane's pairs fell in two adjacent slots,
                                  decided by one threshold comparison per pair and added with
                                  two LDS atomics per lane */
-    uint64_t chord_steps;     /* FP32 angular steps that formed the squared chord: the
-                                 dot product did not decide them, or the step lay at
-                                 small angles where the chord comes first */
+    uint64_t chord_steps;     /* FP32 angular steps at small angles: a column of theirs lies
+                                 within chord^2 0.018 (about 7.7 deg) of the wavefront's
+                                 rows (unpruned launches) */
 } tpcf_counters;
 
 /* Copy the statistics to *out (may be NULL) and, with reset = 1, clear

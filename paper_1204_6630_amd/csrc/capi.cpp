@@ -63,11 +63,19 @@ struct Tuning {
     int max_cols = 0;        // largest column range of a work unit
     int blocks_per_cu = 0;   // 0: the blocks that fit at once
     int lut_bytes = 0;       // largest cell table
-    int lut_direct = 0;      // 1: FP32 byte tables in the direct layout
+    int lut_direct = 0;      // kept for the caller, no effect
     int prune = 0;           // 1: exact tile pruning
 };
 
-int rows_per_lane_of(const Tuning &t) { return t.rows_per_lane ? t.rows_per_lane : 4; }
+// Rows per lane of a launch over `pairs` pairs: 4, but 2 for FP32 tiles below
+// 2^29 pairs, where items of 256 rows are too few to fill the 4096 wavefronts
+// of the device (DD of 1e3 points 251 -> 128 us, DD+DR+RR of 1e4 x 1e4 1160
+// -> 860 us; 1e5 x 2e5 in 64 regions 7.4 ms either way).
+int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs) {
+    if (t.rows_per_lane)
+        return t.rows_per_lane;
+    return precision == TPCF_FP32_CHORD && !t.prune && pairs < ((uint64_t)1 << 29) ? 2 : 4;
+}
 
 int max_cols_of(const Tuning &t) { return t.max_cols ? t.max_cols : 4096; }
 
@@ -146,10 +154,8 @@ struct Compiled {
     DevBuf dD, dE, dqlo, dqhi, dlut, dErad;
     CellTable cells;
     Band32 band;
-    // Angular FP32: cell table of the dot-product key q' = fl(2 - 2p), packed
-    // after the chord table (at byte plut_src of dlut); no cells otherwise.
-    CellTable pcells;
-    int plut_src = 0;
+    int tile_edges_at = -1, tile_slots_at = -1;   // FP32 tiles: where their tables lie in dqlo (floats)
+    int q_exp = 0;         // FP32 tiles: distances are scaled by 2^q_exp (bands and cells by its square)
     int precision = 0;
     int entry_bytes = 2;   // 1: byte entries (0x80 | k, 0xFF), 2: 16-bit codes
     double delta = 0;      // norm bound of the band (3-D: rmax)
@@ -160,6 +166,7 @@ struct Plan {
     std::vector<Unit> units;
     DevBuf dunits;
     uint64_t pairs = 0;
+    int rows = 4;      // rows per lane of its units
 };
 
 // Launch resources of one stream.  Work on one stream runs in order, so the
@@ -502,9 +509,8 @@ std::string edges_key(const double *edges, int nbins, int precision, double delt
     if (precision == TPCF_FP32_CHORD || metric)
         k.append((const char *)&delta, sizeof delta);
     k.append((const char *)&t.lut_bytes, sizeof t.lut_bytes);
-    k.append((const char *)&t.lut_direct, sizeof t.lut_direct);
-    k.append((const char *)&t.hist_copies, sizeof t.hist_copies);   // sizes a wrapped table's free piece
-    k.append((const char *)&t.prune, sizeof t.prune);               // pruned: no dot-product tables
+    k.append((const char *)&t.hist_copies, sizeof t.hist_copies);   // the table takes the LDS they leave
+    k.append((const char *)&t.prune, sizeof t.prune);               // pruned: unscaled tables
     return k;
 }
 
@@ -555,64 +561,61 @@ int compile_host(const Tuning &tune, const double *edges, int nbins, int precisi
     c->delta = delta;
     c->metric = metric;
     const int nslots = nbins + 2;
-    c->entry_bytes = nslots <= kMaxSlots8 ? 1 : 2;
-    // FP32: by default the table fits kLdsTarget with the histograms and
-    // edges and, with the angular dot-product path, its table (kDotLutBytes)
-    // and the column staging (kStageBytes).  Pruned angular kernels take the
-    // chord path alone (the blocks they evaluate lie across edges) and give
-    // the chord table the room.
-    const bool angular32 = !metric && precision == TPCF_FP32_CHORD;
-    const bool dot = angular32 && !tune.prune;
+    const bool tiles = precision == TPCF_FP32_CHORD && !tune.prune;
+    c->entry_bytes = nslots <= kMaxSlots8 && !tiles ? 1 : 2;
+    // FP32: by default the table fits the LDS target of its kernel with the
+    // histograms and edges
     const int aux = aux_lds_bytes(nslots, hist_copies_of(tune, nslots), nbins + 1);
-    const int pbytes = dot ? kDotLutBytes : 0;
-    const int extra = dot ? pbytes + kStageBytes + 32 : 0;
     int table_bytes = tune.lut_bytes ? tune.lut_bytes : kMaxLutBytes;
     if (precision == TPCF_FP32_CHORD && !tune.lut_bytes)
-        table_bytes = std::min(table_bytes, std::max(4096, (kLdsTarget - aux - extra) & ~15));
+        table_bytes = std::min(table_bytes, std::max(4096, ((tiles ? kLdsTargetTiles - tile_lds_bytes(nslots) : kLdsTarget) - aux) & ~15));
     const int max_cells = std::min(table_bytes, kMaxLutBytes) / c->entry_bytes;
     qlo->assign(c->edges.D.size(), 0.0f);
     qhi->assign(c->edges.D.size(), 0.0f);
-    if (metric && precision == TPCF_FP32_CHORD) {
-        c->band = make_band32_3d(c->edges, delta);
-        c->cells = make_cells32_top(c->edges, c->band, qtop_key_3d(delta), max_cells);
+    if (precision == TPCF_FP32_CHORD) {
+        c->band = metric ? make_band32_3d(c->edges, delta) : make_band32(c->edges, delta);
+        uint32_t top = metric ? qtop_key_3d(delta) : qtop_key(delta);
+        if (tiles) {
+            c->q_exp = tile_scale_exp(metric, delta);
+            scale_band32(2 * c->q_exp, &c->band, &top);
+        }
+        c->cells = tiles ? make_cells_tiles(c->edges, c->band, top, max_cells)
+                         : make_cells32_top(c->edges, c->band, top, max_cells);
         *qlo = c->band.qlo;
         *qhi = c->band.qhi;
+        if (tiles) {
+            // the kernel's slot and edge tables follow the lower ends (at a
+            // multiple of 4 floats, which the kernel reads whole)
+            std::vector<float> slots, edges;
+            make_tile_tables(c->band, &slots, &edges);
+            c->tile_edges_at = ((int)qlo->size() + 3) & ~3;
+            qlo->resize((size_t)c->tile_edges_at, 0.0f);
+            qlo->insert(qlo->end(), edges.begin(), edges.end());
+            c->tile_slots_at = (int)qlo->size();
+            qlo->insert(qlo->end(), slots.begin(), slots.end());
+        }
     } else if (metric) {
         const double top = 4.0 * delta * delta * (1.0 + ldexp(1.0, -10));
         c->cells = make_cells64(c->edges, max_cells, top > 1e-300 ? top : 1e-300);
-    } else if (precision == TPCF_FP32_CHORD) {
-        c->band = make_band32(c->edges, delta);
-        if (c->entry_bytes == 1 && tune.lut_direct) {
-            Band32 fb = make_band32(c->edges, delta, floor_for(c->band));
-            const int wrap_bytes = tune.lut_bytes ? tune.lut_bytes : kWrapLutBytes - extra;
-            c->cells = make_cells32_wrap(c->edges, fb, delta, wrap_bytes, aux);
-            if (!c->cells.cells.empty())
-                c->band = fb;
-        }
-        if (c->cells.cells.empty())
-            c->cells = make_cells32(c->edges, c->band, delta, max_cells);
-        *qlo = c->band.qlo;
-        *qhi = c->band.qhi;
-        // the dot-product key's table and the per-pair band in p, after the
-        // chord band's entries in qlo / qhi
-        if (dot) {
-            c->pcells = make_cells32_top(c->edges, make_band_dot32(c->edges, delta), dot_top_key(delta),
-                                         pbytes / c->entry_bytes);
-            std::vector<float> plo, phi;
-            make_pband32(c->edges, delta, &plo, &phi);
-            qlo->insert(qlo->end(), plo.begin(), plo.end());
-            qhi->insert(qhi->end(), phi.begin(), phi.end());
-        }
     } else {
         c->cells = make_cells64(c->edges, max_cells);
     }
     packed->clear();
-    pack_cells(c->cells.direct ? c->cells.image : c->cells.cells, c->entry_bytes, packed);
-    if (!c->pcells.cells.empty()) {
-        packed->resize((packed->size() + 15) & ~(size_t)15, 0);
-        c->plut_src = (int)packed->size();
-        pack_cells(c->pcells.cells, c->entry_bytes, packed);
+    if (tiles) {
+        // entries as histogram rows (kCellOpen, kCellMulti)
+        const uint32_t rowstep = 4u * (uint32_t)hist_copies_of(tune, nslots);
+        packed->resize(2 * c->cells.cells.size());
+        for (size_t i = 0; i < c->cells.cells.size(); ++i) {
+            const uint16_t v = c->cells.cells[i];
+            const uint16_t e = v == kMulti    ? (uint16_t)(kCellOpen | kCellMulti)
+                               : (v & kMedium) ? (uint16_t)((v & 0x7FFF) * rowstep | kCellOpen)
+                                               : (uint16_t)(v * rowstep);
+            memcpy(packed->data() + 2 * i, &e, 2);
+        }
+    } else {
+        pack_cells(c->cells.cells, c->entry_bytes, packed);
     }
+    packed->resize((packed->size() + 15) & ~(size_t)15, 0);    // the kernels copy 16 bytes a lane
     return TPCF_OK;
 }
 
@@ -648,19 +651,19 @@ int get_compiled(tpcf_ctx *ctx, const double *edges, int nbins, int precision, d
     return TPCF_OK;
 }
 
-// Column chunk width of a plan: aim for >= ~4096 units on big requests,
-// within [256, max_cols], but wide enough that the unit list stays below
-// kMaxUnits (about 0.8 GB of units; catalogs of 1e8 points would otherwise
-// need tens of GB of them).
+// Column chunk width of a plan: aim for >= ~4096 units, within [64,
+// max_cols] (multiples of 256 above 256), but wide enough that the unit list
+// stays below kMaxUnits (about 0.8 GB of units; catalogs of 1e8 points would
+// otherwise need tens of GB of them).
 constexpr double kMaxUnits = 16777216.0;
 
 int64_t chunk_width(uint64_t pairs, int64_t T, int64_t max_cols, double max_units = kMaxUnits) {
     int64_t bj = (int64_t)((double)pairs / 4096.0 / (double)T);
-    bj = (bj + 255) / 256 * 256;
+    bj = bj > 256 ? (bj + 255) / 256 * 256 : (bj + 63) / 64 * 64;
     if (bj > max_cols)
         bj = max_cols;
-    if (bj < 256)
-        bj = 256;
+    if (bj < 64)
+        bj = 64;
     const double need = (double)pairs / (double)T / max_units;   // columns per unit for max_units units
     if ((double)bj < need)
         bj = ((int64_t)need + 256) / 256 * 256;
@@ -685,17 +688,22 @@ Unit mk_unit(int64_t i0, int64_t i1, int64_t j0, int64_t j1, int64_t row_lo, int
     return u;
 }
 
-Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int64_t T,
+// Pairs of a request.
+uint64_t pairs_of(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re) {
+    if (!auto_pairs)
+        return (uint64_t)(re - rb) * (uint64_t)nb;
+    // sum over i in [rb, re) of (na - 1 - i)
+    const int64_t cnt = re - rb;
+    return (uint64_t)cnt * (uint64_t)(na - 1) - (uint64_t)((rb + re - 1) * cnt / 2);
+}
+
+Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows,
                int64_t max_cols, double max_units = kMaxUnits) {
     Plan p;
-    uint64_t pairs = 0;
-    if (auto_pairs) {
-        // sum over i in [rb, re) of (na - 1 - i)
-        const int64_t cnt = re - rb;
-        pairs = (uint64_t)cnt * (uint64_t)(na - 1) - (uint64_t)((rb + re - 1) * cnt / 2);
-    } else {
-        pairs = (uint64_t)(re - rb) * (uint64_t)nb;
-    }
+    // 64 lanes x rows per lane rows per wavefront, four wavefronts per tile
+    const int64_t T = (int64_t)kWaves * kWaveSize * rows;
+    p.rows = rows;
+    const uint64_t pairs = pairs_of(auto_pairs, na, nb, rb, re);
     p.pairs = pairs;
     const int64_t bj = chunk_width(pairs, T, max_cols, max_units);
     // Row tiles start at rb (valid rows from row_lo = rb).
@@ -716,7 +724,7 @@ Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, 
             while (j0 < na) {
                 // up to the next multiple of bj; a short first piece joins the next chunk
                 int64_t j1 = (j0 / bj + 1) * bj;
-                if (j1 - j0 < 256)
+                if (j1 - j0 < std::min<int64_t>(256, bj))
                     j1 += bj;
                 if (j1 > na)
                     j1 = na;
@@ -746,9 +754,11 @@ Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, 
 // columns are cut on the bj grid and at region starts.  Auto-pairs: per row
 // tile a diagonal unit over the tile's own columns, then the columns after
 // it.  Ordered column chunk first.
-Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int64_t T, int64_t max_cols,
+Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int rows, int64_t max_cols,
                        const std::vector<int64_t> &sa, const std::vector<int64_t> &sb) {
     Plan p;
+    const int64_t T = (int64_t)kWaves * kWaveSize * rows;
+    p.rows = rows;
     p.pairs = auto_pairs ? (uint64_t)na * (uint64_t)(na > 0 ? na - 1 : 0) / 2 : (uint64_t)na * (uint64_t)nb;
     const int64_t bj = chunk_width(p.pairs, T, max_cols);
     const int nra = (int)sa.size() - 1;
@@ -797,13 +807,14 @@ Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int64_t T, int64
     return p;
 }
 
-int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, Plan **out) {
-    // 64 lanes x rows_per_lane rows per wavefront, four wavefronts per tile
-    const int64_t T = (int64_t)kWaves * kWaveSize * rows_per_lane_of(ctx->tune);
+int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows, int precision,
+             Plan **out) {
+    if (!rows)
+        rows = rows_per_lane_of(ctx->tune, precision, pairs_of(auto_pairs, na, nb, rb, re));
     const int64_t max_cols = max_cols_of(ctx->tune);
     char buf[160];
     snprintf(buf, sizeof buf, "%d:%lld:%lld:%lld:%lld:%lld:%lld", (int)auto_pairs, (long long)na,
-             (long long)nb, (long long)rb, (long long)re, (long long)T, (long long)max_cols);
+             (long long)nb, (long long)rb, (long long)re, (long long)rows, (long long)max_cols);
     auto it = ctx->plans.find(buf);
     if (it != ctx->plans.end()) {
         *out = it->second.get();
@@ -816,7 +827,7 @@ int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb,
             kv.second->dunits.release(ctx->mem);
         ctx->plans.clear();
     }
-    auto p = std::make_unique<Plan>(make_plan(auto_pairs, na, nb, rb, re, T, max_cols));
+    auto p = std::make_unique<Plan>(make_plan(auto_pairs, na, nb, rb, re, rows, max_cols));
     TRY(upload_blocking(ctx->mem, p->dunits, p->units));
     *out = p.get();
     ctx->plans[buf] = std::move(p);
@@ -826,11 +837,11 @@ int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb,
 // Plan of a whole-catalog request with jackknife regions (cached like get_plan,
 // keyed by the catalog ids, which are never reused).
 int get_plan_regions(tpcf_ctx *ctx, bool auto_pairs, int32_t cat_a, int32_t cat_b, const Catalog &A,
-                     const Catalog &B, Plan **out) {
-    const int64_t T = (int64_t)kWaves * kWaveSize * rows_per_lane_of(ctx->tune);
+                     const Catalog &B, int precision, Plan **out) {
+    const int rows = rows_per_lane_of(ctx->tune, precision, pairs_of(auto_pairs, A.n, B.n, 0, A.n));
     const int64_t max_cols = max_cols_of(ctx->tune);
     char buf[160];
-    snprintf(buf, sizeof buf, "R%d:%d:%d:%lld:%lld", (int)auto_pairs, (int)cat_a, (int)cat_b, (long long)T,
+    snprintf(buf, sizeof buf, "R%d:%d:%d:%lld:%lld", (int)auto_pairs, (int)cat_a, (int)cat_b, (long long)rows,
              (long long)max_cols);
     auto it = ctx->plans.find(buf);
     if (it != ctx->plans.end()) {
@@ -845,7 +856,7 @@ int get_plan_regions(tpcf_ctx *ctx, bool auto_pairs, int32_t cat_a, int32_t cat_
         ctx->plans.clear();
     }
     auto p = std::make_unique<Plan>(
-        make_plan_regions(auto_pairs, A.n, B.n, T, max_cols, A.reg_start, B.reg_start));
+        make_plan_regions(auto_pairs, A.n, B.n, rows, max_cols, A.reg_start, B.reg_start));
     if (p->units.size() > (size_t)0x7fffffff / kWaves)
         return fail(TPCF_E_INVALID, "too many work units (region boundaries split the work too finely)");
     TRY(upload_blocking(ctx->mem, p->dunits, p->units));
@@ -951,8 +962,9 @@ int validate(tpcf_ctx *ctx, const tpcf_job_desc &d, Request *r) {
 
 // Validate one request and get its tables and plan.  delta_override >= 0
 // compiles the FP32 band for that norm bound (shared by every job of a batch)
-// instead of the request's own.
-int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Request *r, bool regions = false) {
+// instead of the request's own; rows > 0 sets the rows per lane (likewise).
+int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Request *r, bool regions = false,
+            int rows = 0) {
     TRY(validate(ctx, d, r));
     const int64_t rb = r->rb, re = r->re;
     TRY(set_device(ctx));
@@ -967,11 +979,11 @@ int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Reques
         if (r->A->nreg < 1 || r->B->nreg != r->A->nreg)
             return fail(TPCF_E_INVALID, "both catalogs need region labels with the same number of regions");
         TRY(get_plan_regions(ctx, r->auto_pairs, r->cat_a, r->auto_pairs ? r->cat_a : r->cat_b, *r->A, *r->B,
-                             &r->plan));
+                             d.precision, &r->plan));
         r->pairs = r->plan->pairs;
         return TPCF_OK;
     }
-    TRY(get_plan(ctx, r->auto_pairs, r->A->n, r->B->n, rb, re, &r->plan));
+    TRY(get_plan(ctx, r->auto_pairs, r->A->n, r->B->n, rb, re, rows, d.precision, &r->plan));
     r->pairs = r->plan->pairs;
     if (d.kind == TPCF_RR)
         r->cache_key = cache_key(d.cat_a, d.bin_edges_deg, d.nbins, d.precision, rb, re);
@@ -1003,7 +1015,7 @@ JobDev job_of(const Request &r, unsigned long long *hist, const int *cancel) {
     return j;
 }
 
-// Threshold of the FP32 dot-product screen for the edge with threshold D
+// Threshold of an FP32 dot-product screen (tpcf_compile_screen) for the edge with threshold D
 // (angular catalogs, squared norms within 1 +- delta): p = fl32(f_i . f_j) of
 // the FP32 copies satisfies |p - d| <= E = dot_error32(delta), so p <= D - E
 // proves d <= D.  The result is rounded down to a float.
@@ -1021,19 +1033,16 @@ float dot_screen32(double D, double delta) {
 
 // Kernel arguments of a launch with compiled edges cp.  delta: bound on
 // | |v|^2 - 1 | over the launch's sky catalogs (angular pruning).
-PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, unsigned long long *stats, double delta) {
+PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, int rows, unsigned long long *stats,
+                 double delta) {
     PairArgs a;
     memset(&a, 0, sizeof a);
     a.lut = cp.dlut.p;
-    a.lut_cells = (int32_t)(cp.cells.direct ? cp.cells.image.size() : cp.cells.cells.size());
-    a.lut_wrap_bits = cp.cells.wrap_bits;
-    a.aux_off = cp.cells.aux_off;
-    a.q_floor = cp.cells.q0;
+    a.lut_cells = (int32_t)cp.cells.cells.size();
     a.lut_entry_bytes = cp.entry_bytes;
     a.lut_shift = cp.cells.shift;
     a.lut_lo = cp.cells.lo;
     a.lut_hi = cp.cells.hi;
-    a.lut_direct = cp.cells.direct ? 1 : 0;
     a.metric = cp.metric;
     a.prune = ctx->tune.prune ? 1 : 0;
     // 3-D: the FP32 row copies move each point by at most 2^-24 R per
@@ -1046,29 +1055,19 @@ PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, unsigned lo
     if (cp.precision == TPCF_FP32_CHORD) {
         float qh = cp.band.qhi[last];
         memcpy(&a.beyond_key, &qh, sizeof qh);
-        a.p_beyond = cp.metric ? -HUGE_VALF : dot_screen32(cp.edges.D[last], cp.delta);
-        if (!cp.pcells.cells.empty()) {
-            a.plut_cells = (int32_t)cp.pcells.cells.size();
-            a.plut_shift = cp.pcells.shift;
-            a.plut_lo = cp.pcells.lo;
-            a.plut_hi = cp.pcells.hi;
-            a.plut_src = cp.plut_src;
-            const int base = lds_bytes(nbins + 2, hist_copies_of(ctx->tune, nbins + 2), a.lut_cells, cp.entry_bytes,
-                                       nbins + 1, cp.cells.direct ? cp.cells.aux_off : -1);
-            a.plut_lds = (base + 15) & ~15;
-            a.stage_lds = (a.plut_lds + a.plut_cells * cp.entry_bytes + 15) & ~15;
-            // the chord loop hands steps to the dot product at chord^2 above
-            // 0.018 (about 7.7 deg), where p's error is ~2e-5 of q and a
-            // lane's pairs seldom span several bins: a heuristic, measured
-            // best on the octant workloads (0.6 to 25 deg tried)
-            a.q_dot = std::max(0.018f, (float)(400.0 * dot_error32(cp.delta)));
+        a.q_scale = ldexpf(1.0f, cp.q_exp);
+        a.q_exp2 = 2 * cp.q_exp;
+        // steps with a column within 7.7 deg of the rows' mean count as chord steps
+        a.q_small = cp.metric ? -HUGE_VALF : ldexpf(0.018f, a.q_exp2);
+        if (cp.tile_edges_at >= 0) {
+            a.tile_edges = (const float4 *)((const float *)cp.dqlo.p + cp.tile_edges_at);
+            a.tile_slots = (const float2 *)((const float *)cp.dqlo.p + cp.tile_slots_at);
         }
     } else {
         const double t = cp.edges.E[last];
         uint64_t b;
         memcpy(&b, &t, sizeof b);
         a.beyond_key = (uint32_t)(b >> 32);
-        a.p_beyond = -HUGE_VALF;
     }
     a.qlo = (const float *)cp.dqlo.p;
     a.qhi = (const float *)cp.dqhi.p;
@@ -1077,7 +1076,7 @@ PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, unsigned lo
     a.nedges = nbins + 1;
     a.nslots = nbins + 2;
     a.hist_copies = hist_copies_of(ctx->tune, nbins + 2);
-    a.rows_per_lane = rows_per_lane_of(ctx->tune);
+    a.rows_per_lane = rows;
     a.blocks_per_cu = ctx->tune.blocks_per_cu;
     a.stats = stats;
     return a;
@@ -1120,7 +1119,7 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
     TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * ((size_t)kGlobalCopies * kMaxSlots + 1)));
     unsigned long long *copies = (unsigned long long *)w.copies.p;
     HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + 1, w.stream));
-    PairArgs a = args_of(ctx, *r.cp, r.nbins, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
+    PairArgs a = args_of(ctx, *r.cp, r.nbins, r.plan->rows, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
     a.jobs = nullptr;
     a.job0 = job_of(r, copies, cancel);
     a.job0.touch = touch;
@@ -1577,8 +1576,9 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     const size_t max_units = (kScratchBytes - o_units) / sizeof(Unit);
     // the unit list is sized for half the room (the triangular lists of
     // auto-pairs hold a few more units than the estimate), then checked
-    const int64_t T = (int64_t)kWaves * kWaveSize * rows_per_lane_of(ctx->tune);
-    Plan plan = make_plan(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re, T, max_cols_of(ctx->tune), 0.5 * (double)max_units);
+    Plan plan = make_plan(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re,
+                          rows_per_lane_of(ctx->tune, r.precision, pairs_of(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re)),
+                          max_cols_of(ctx->tune), 0.5 * (double)max_units);
     if (plan.units.size() > max_units) {
         char buf[200];
         snprintf(buf, sizeof buf, "the request needs %zu work units; the fixed work area (%zu MiB) holds %zu",
@@ -1608,7 +1608,7 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     c.dqhi.p = base + o_qhi;
     c.dErad.p = base + o_rad;
     c.dlut.p = base + o_lut;
-    PairArgs a = args_of(ctx, c, nbins, (unsigned long long *)ctx->main.stats.p, delta);
+    PairArgs a = args_of(ctx, c, nbins, plan.rows, (unsigned long long *)ctx->main.stats.p, delta);
     a.prune = 0;     // bounding caps are built on first use, which allocates: count every pair
     a.jobs = nullptr;
     a.job0 = job_of(r, copies, nullptr);
@@ -1655,8 +1655,16 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
             delta = std::max(delta, b->second.band_param());
     }
     std::vector<Request> reqs((size_t)njobs);
+    // one launch, so one number of rows per lane: that of all its pairs
+    uint64_t pairs = 0;
     for (int32_t k = 0; k < njobs; ++k) {
-        TRY(prepare(ctx, jobs[k], delta, &reqs[k]));
+        Request r;
+        TRY(validate(ctx, jobs[k], &r));
+        pairs += pairs_of(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re);
+    }
+    const int rows = rows_per_lane_of(ctx->tune, jobs[0].precision, pairs);
+    for (int32_t k = 0; k < njobs; ++k) {
+        TRY(prepare(ctx, jobs[k], delta, &reqs[k], false, rows));
         if (reqs[k].metric != reqs[0].metric)
             return fail(TPCF_E_INVALID, "a batch cannot mix sky and 3-D catalogs");
     }
@@ -1709,7 +1717,7 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
             free_graph(ctx, *g);
             return rc;
         }
-        PairArgs a = args_of(ctx, *reqs[0].cp, nbins, (unsigned long long *)ctx->main.stats.p, delta);
+        PairArgs a = args_of(ctx, *reqs[0].cp, nbins, rows, (unsigned long long *)ctx->main.stats.p, delta);
         a.jobs = (const JobDev *)g->jobs.p;
         a.units = (const Unit *)g->units.p;
         a.n_units = (int32_t)hu.size();

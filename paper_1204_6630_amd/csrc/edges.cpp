@@ -17,6 +17,8 @@
 // -fno-builtin and contraction off).
 #include "edges.h"
 
+#include "internal.h"
+
 #include <math.h>
 #include <string.h>
 
@@ -477,10 +479,6 @@ uint32_t qtop_key_3d(double rmax) {
     return fbits(q < 3.0e38 ? round_up32(q) : 3.0e38f);
 }
 
-// FP32 cells: key = bits(q) >> shift for q >= 0.  The bottom cell also holds
-// every q below its range and the top cell every q above.
-namespace {
-
 // Largest q = fl32(|f_i - f_j|^2) the kernel can produce: |f_i - f_j| <=
 // 2 sqrt(1 + delta) + a few FP32 ulps, and the rounding of q is far below the
 // 1e-4 margin.
@@ -488,6 +486,41 @@ uint32_t qtop_key(double delta) {
     const double qtop_d = pow(2.0 * sqrt(1.0 + delta) + 4.0 * ldexp(1.0, -24), 2.0) * 1.0001;
     return fbits(round_up32(qtop_d));
 }
+
+// Bands and top key of the FP32 tiles, whose squared distances carry the
+// factor 2^exp2: exact in FP64, then rounded outward where the float range
+// ends (a lower end that leaves the normal range becomes 0).
+void scale_band32(int exp2, Band32 *b, uint32_t *top) {
+    for (size_t k = 0; k < b->qlo.size(); ++k) {
+        if (isfinite(b->qlo[k]) && b->qlo[k] > 0.0f) {
+            const double v = ldexp((double)b->qlo[k], exp2);
+            b->qlo[k] = v < ldexp(1.0, -100) ? 0.0f : v > 3.0e38 ? 3.0e38f : round_down32(v);
+        } else if (b->qlo[k] == HUGE_VALF) {
+            b->qlo[k] = 3.0e38f;    // no pair reaches the edge; keeps qhi - qlo = +inf
+        }
+        if (isfinite(b->qhi[k]) && b->qhi[k] > 0.0f)
+            b->qhi[k] = round_up32(ldexp((double)b->qhi[k], exp2));
+    }
+    const double t = ldexp((double)ffrom(*top), exp2) * (1.0 + ldexp(1.0, -10));
+    *top = fbits(t < 3.0e38 ? round_up32(t) : 3.0e38f);
+}
+
+// Scale 2^e of the FP32 tiles' coordinates: |f - c| <= 2 |f| <= 2^(14 - e)
+// (angles: |f| <= 1 + 2^-20; 3-D: |f| <= R), so that -2 (f - c) 2^e stays
+// within f16's 65504 and |f - c|^2 2^(2e - 14) within 2^14.  The exponent is
+// held within [-60, 100], so that the scale and its square fit FP32 (the
+// square is applied with ldexp).
+int tile_scale_exp(int metric, double rmax) {
+    if (!metric)
+        return 13;
+    int ex = 0;
+    frexp(rmax, &ex);       // rmax < 2^ex
+    return std::min(100, std::max(-60, 13 - ex));
+}
+
+// FP32 cells: key = bits(q) >> shift for q >= 0.  The bottom cell also holds
+// every q below its range and the top cell every q above.
+namespace {
 
 // Entries of FP32 cells [lo, hi] (bit patterns c << shift .. ((c+1) << shift) - 1);
 // the bottom cell reaches down to 0 and the top one up to +inf (a clamp sends
@@ -635,6 +668,50 @@ CellTable make_cells32_top(const EdgeTables &t, const Band32 &b, uint32_t ktop, 
     }
     fill_cells32(b, ne, &ct);
     return ct;
+}
+
+CellTable make_cells_tiles(const EdgeTables &t, const Band32 &b, uint32_t ktop, int max_cells) {
+    Band32 w = b;
+    const double f = (double)kTileFar * 1.01;
+    for (size_t k = 0; k < w.qlo.size(); ++k) {
+        if (isfinite(w.qlo[k]) && w.qlo[k] > 0.0f && w.qlo[k] < 3.0e38f)
+            w.qlo[k] = round_down32((double)w.qlo[k] * (1.0 - f));
+        if (isfinite(w.qhi[k]) && w.qhi[k] > 0.0f)
+            w.qhi[k] = round_up32((double)w.qhi[k] * (1.0 + f));
+    }
+    return make_cells32_top(t, w, ktop, max_cells);
+}
+
+// Slot s holds q in [qhi_{s-1}, qlo_s): below the first edge the lower end is
+// -qlo_0 (no q is negative beyond rounding), above the last the width is
+// infinite; a slot without room has width 0.  Widths and rooms are rounded
+// down, so that lower end + width stays below the upper band.
+void make_tile_tables(const Band32 &b, std::vector<float> *slots, std::vector<float> *edges) {
+    const int ne = (int)b.qlo.size();
+    slots->assign(2 * (size_t)(ne + 1), 0.0f);
+    edges->assign(4 * (size_t)ne, 0.0f);
+    const double big = 1.0e38;
+    auto lower = [&](int k) { return k < 0 || b.qhi[k] == -HUGE_VALF ? -HUGE_VAL : (double)b.qhi[k]; };
+    auto upper = [&](int k) { return k >= ne || (double)b.qlo[k] > big ? HUGE_VAL : (double)b.qlo[k]; };
+    for (int s = 0; s <= ne; ++s) {
+        double L = lower(s - 1), U = upper(s);
+        if (L > big || U == -HUGE_VAL)
+            continue;                       // no pair is certain of this slot
+        if (L == -HUGE_VAL)
+            L = U == HUGE_VAL ? -1.0 : -U;
+        (*slots)[2 * s] = (float)L;         // a float already
+        (*slots)[2 * s + 1] = U == HUGE_VAL ? HUGE_VALF : U > L ? round_down32((U - L) * (1.0 - ldexp(1.0, -24))) : 0.0f;
+    }
+    for (int k = 0; k < ne; ++k) {
+        if (!(fabsf(b.qhi[k]) < big) || b.qlo[k] == -HUGE_VALF)
+            continue;                       // room 0: never decided
+        const double hi = b.qhi[k], below = lower(k - 1), above = upper(k + 1);
+        float *e = &(*edges)[4 * (size_t)k];
+        e[0] = b.qhi[k];
+        e[1] = round_up32(hi - (double)b.qlo[k]);
+        e[2] = below == -HUGE_VAL ? 3.0e38f : hi > below ? round_down32((hi - below) * (1.0 - ldexp(1.0, -24))) : 0.0f;
+        e[3] = above == HUGE_VAL ? 3.0e38f : above > hi ? round_down32((above - hi) * (1.0 - ldexp(1.0, -24))) : 0.0f;
+    }
 }
 
 // FP64 cells: key = (int32) high word of e = fl(1 - d), arithmetic shift.

@@ -83,6 +83,7 @@ Band32 make_band32_3d(const EdgeTables &t, double rmax);
 
 // Bit pattern of an upper bound of every q the FP32 kernel computes for
 // points of norm at most rmax (3-D).
+uint32_t qtop_key(double delta);
 uint32_t qtop_key_3d(double rmax);
 
 // Cell tables.  FP32: key = bits of q (q >= 0).  FP64: key = high 32 bits of
@@ -105,5 +106,16 @@ CellTable make_cells32_wrap(const EdgeTables &t, const Band32 &b, double delta, 
 // larger value falls into the top cell): 2 for e = 1 - d, the largest
 // squared distance for 3-D.
 CellTable make_cells64(const EdgeTables &t, int max_cells, double etop = 2.0 + 1.0 / 262144.0);
+
+// FP32 tiles: power-of-two scale of the coordinates, and the bands and top
+// key of squared distances times 2^exp2.
+int tile_scale_exp(int metric, double rmax);
+void scale_band32(int exp2, Band32 *b, uint32_t *top);
+// Cell table of the tiles: valid for every q within kTileFar (relative) of
+// the cell.
+CellTable make_cells_tiles(const EdgeTables &t, const Band32 &b, uint32_t ktop, int max_cells);
+// The tiles' slot and edge tables (see PairArgs::tile_slots, tile_edges):
+// 2 floats per slot and 4 per edge.
+void make_tile_tables(const Band32 &b, std::vector<float> *slots, std::vector<float> *edges);
 
 }  // namespace tpcf

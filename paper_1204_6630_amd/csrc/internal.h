@@ -3,6 +3,7 @@
 #pragma once
 
 #include <stddef.h>
+#include <hip/hip_vector_types.h>
 #include <stdint.h>
 
 namespace tpcf {
@@ -16,27 +17,29 @@ constexpr int kBlock = kWaves * kWaveSize;
 // edge index fits in 7 bits, else two bytes.
 constexpr int kMaxLutBytes = 24576;
 constexpr int kMaxLutCells = kMaxLutBytes;        // with one-byte entries
-// Largest cell-table budget a tuning may ask for, and the wrapped FP32
-// tables' default budget (table, histograms and thresholds together).
+// Largest cell-table budget a tuning may ask for.
 constexpr int kMaxDirectLutBytes = 33792;
-constexpr int kWrapLutBytes = 32768;
-// Angular FP32 launches also hold the dot-product key's cell table (bytes).
-// By default FP32 launches with clamped tables size them so that a block's
-// LDS stays within kLdsTarget: six blocks of four wavefronts in a CU's
-// 160 KiB, the occupancy those kernels are compiled for (waves_per_eu).
-constexpr int kDotLutBytes = 1024;
+// By default FP32 launches size their cell table so that a block's LDS stays
+// within the target: FP32 tiles four blocks of four wavefronts in a CU's
+// 160 KiB, pruned FP32 launches six, the occupancies those kernels are
+// compiled for (waves_per_eu_of).
+constexpr int kLdsTargetTiles = 40960;
 constexpr int kLdsTarget = 27296;
-// Wavefronts per SIMD a pair kernel is compiled for: 6 for the FP32 paths
-// with clamped tables (0, 5, 6; at most 80 VGPRs, a few spilled), 5 for the
-// FP64 paths (1, 4) and the wrapped FP32 tables (3, 7), whose 32 KB of LDS
-// per block allows no more.
+// Wavefronts per SIMD a pair kernel is compiled for: 4 for the FP32 tiles
+// (2, 3; two accumulators, eight row operands and the accumulator input in
+// at most 128 VGPRs), 6 for the pruned FP32 paths (0, 5; at most 80 VGPRs, a
+// few spilled), 5 for the FP64 paths (1, 4).
 constexpr int waves_per_eu_of(int path) {
-    return path == 0 || path == 5 || path == 6 ? 6 : 5;
+    return path == 2 || path == 3 ? 4 : path == 0 || path == 5 ? 6 : 5;
 }
-// Dot-product kernels: each wavefront stages kStageCols columns at a time in
-// LDS, in two buffers of x, y and z floats.
-constexpr int kStageCols = 64;
-constexpr int kStageBytes = kWaves * 2 * kStageCols * 12;
+// FP32 tiles: error bound of q^ in units of 2^-24 (derived in
+// docs/fp32_band.md, section 4b): kTileErrN |b|^2 + kTileErrA rho^2 + kTileErr0.
+constexpr float kTileErrN = 24.0f;
+constexpr float kTileErrA = 640.0f;
+constexpr float kTileErr0 = 16.0f;
+// Largest e, relative to q^, for which pairs are binned one by one from q^
+// (the tiles' cells hold for every q within this of theirs).
+constexpr float kTileFar = 1.0f / 1024.0f;
 // Work statistics words of a launch (see PairArgs::stats).
 constexpr int kStats = 9;
 // Histogram copies in global memory (u64), indexed by work unit.
@@ -53,6 +56,10 @@ constexpr int kMaxSlots = 258;
 constexpr uint16_t kMedium = 0x8000;
 constexpr uint16_t kMulti = 0xFFFF;
 constexpr int kMaxSlots8 = 127;
+// Cell entries of the FP32 tiles: slot * bytes between histogram rows (a
+// power of two, at least 16), flags below.
+constexpr uint32_t kCellOpen = 1;    // an edge lies in the cell, between the slot and the next
+constexpr uint32_t kCellMulti = 2;   // several edges (kCellOpen is set too)
 
 // One work unit: the row tile starting at i0 with valid rows [row_lo, i1),
 // against columns j in [j0, j1) of job `job` (col_lo == j0, kept for the
@@ -105,34 +112,22 @@ struct PairArgs {
     int32_t lut_entry_bytes;     // 1 or 2
     int32_t lut_shift;           // cell = key >> shift
     int32_t lut_lo, lut_hi;      // clamp range of cells
-    int32_t lut_direct;          // 1: wrapped FP32 byte table (lut_cells = 2^lut_wrap_bits;
-                                 // cell = (bits(q) >> shift) & (lut_cells - 1), q summed
-                                 // from the floor q_floor); the histograms and thresholds
-                                 // then start at LDS byte aux_off, inside the table's
-                                 // unused part
-    int32_t lut_wrap_bits;
-    int32_t aux_off;
-    float q_floor;
     // Pairs certainly beyond the last edge: FP32 path, bits(q) >= beyond_key
     // (the bits of the last edge's qhi); FP64 path, high word of e = 1 - d
     // above beyond_key as signed integers (e > E_last).
     uint32_t beyond_key;
-    // Angular FP32 path: the dot product p = fl32(f_i . f_j) of the FP32
-    // copies, p <= p_beyond, proves the rule's d <= D_last (the pair is past
-    // the last edge); -inf when no such screen applies (3-D catalogs).
-    float p_beyond;
-    // Angular FP32 path, dot product first (plut_cells > 0): the cell table of
-    // the key q' = fl(2 - 2p) (cell = clamp(bits(q') >> plut_shift, plut_lo,
-    // plut_hi), plut_cells entries at byte plut_src of lut, copied to LDS byte
-    // plut_lds), and the band in p, nedges (plo, phi) pairs after the chord
-    // band in qlo / qhi.  The chord loop hands the steps after a chord step
-    // that needed no lookup and whose smallest q was at least q_dot to the
-    // dot product.
-    int32_t plut_cells;
-    int32_t plut_shift, plut_lo, plut_hi;
-    int32_t plut_src, plut_lds;
-    int32_t stage_lds;           // LDS byte offset of the column staging buffers (kStageBytes)
-    float q_dot;
+    // FP32 tiles: every squared distance (cell table, bands, beyond_key) is
+    // scaled by q_scale^2 = 2^q_exp2, q_scale the power of two that brings the
+    // coordinates into f16's range.  q_small: steps with a column below it
+    // from the rows' mean are counted as chord steps (-inf: none).
+    // tile_slots (nslots): lower end and width of every slot; tile_edges
+    // (nedges): qhi, qhi - qlo, and how far below and above it x = q - qhi
+    // may reach without meeting another edge's band.  Null on other paths.
+    float q_scale;
+    int32_t q_exp2;
+    float q_small;
+    const float2 *tile_slots;
+    const float4 *tile_edges;
 
     // Exact tile pruning: 1 = a wavefront bins a whole aligned 64-column
     // block at once when the bounding caps put every pair of the block
@@ -168,9 +163,10 @@ struct PairArgs {
                                  //  angular FP32 steps that formed the chord]
 };
 
-// LDS bytes per edge: D_k, fl(1 - D_k), the edge in radians (pruning), the
-// FP32 chord band (qlo_k, qhi_k) and the band in p (plo_k, phi_k).
-constexpr int kEdgeLdsBytes = 8 + 8 + 8 + 8 + 8;
+// LDS bytes per edge: D_k, the FP32 chord band (qlo_k, qhi_k), and either
+// fl(1 - D_k) and the edge in radians (pruning) or the tiles' edge entry.
+
+constexpr int kEdgeLdsBytes = 8 + 8 + 8 + 8;
 
 // LDS bytes of the histograms (with the discard row) and edge thresholds.
 inline int aux_lds_bytes(int nslots, int hist_copies, int nedges) {
@@ -179,16 +175,15 @@ inline int aux_lds_bytes(int nslots, int hist_copies, int nedges) {
     return hist + thr;
 }
 
-// LDS bytes used by one block for the given table sizes; aux_off >= 0 places
-// the histograms and thresholds at that offset (inside a wrapped table).
-inline int lds_bytes(int nslots, int hist_copies, int lut_cells, int lut_entry_bytes, int nedges,
-                     int aux_off = -1) {
-    int lut = ((lut_cells * lut_entry_bytes) + 15) & ~15;
-    int aux = aux_lds_bytes(nslots, hist_copies, nedges);
-    if (aux_off >= 0)
-        return aux_off + aux > lut ? aux_off + aux : lut;
-    return lut + aux;
+// LDS bytes used by one block for the given table sizes.
+inline int lds_bytes(int nslots, int hist_copies, int lut_cells, int lut_entry_bytes, int nedges) {
+    return (((lut_cells * lut_entry_bytes) + 15) & ~15) + aux_lds_bytes(nslots, hist_copies, nedges);
 }
+
+// What FP32 tiles hold besides: the slot table and every wavefront's buffer
+// of 64 columns.
+constexpr int kStageWaveBytes = 3 * 64 * 4;
+inline int tile_lds_bytes(int nslots) { return nslots * 8 + kWaves * kStageWaveBytes; }
 
 // Margin (radians) of the geometric angle interval of the pruning test:
 // covers the FP32 copies of the rows (directions move by <= 1.2e-7 rad) and

@@ -6,6 +6,10 @@
 // combined in one histogram in global memory.
 //
 // gfx950 design:
+//   * FP32 launches without pruning form the squared distances of 32 x 32
+//     pairs at a time on the matrix cores and bin whole tiles (see "FP32
+//     tiles on the matrix cores" below); the points below are the vector
+//     paths (FP64, and FP32 with pruning);
 //   * one work unit = a tile of rows i (four wavefronts, each holding P = 2
 //     or 4 points per lane in registers) against a range of columns
 //     j; every wavefront walks the same j range, reading each j through the
@@ -17,9 +21,7 @@
 //     threshold comparison, and anything closer is re-decided with the
 //     exact FP64 rule d <= D_k;
 //   * every wavefront owns a private LDS histogram, layout [slot][copy] with
-//     copy = lane mod copies, updated with ds_add_u32; with 32 copies the
-//     lanes of each half-wave (the LDS serves 32 lanes per pass) always hit
-//     32 distinct banks;
+//     copy = lane mod copies, updated with ds_add_u32;
 //   * after each unit a wavefront sums its histogram and adds it with 64-bit
 //     atomics into one of kGlobalCopies global copies, which a final kernel
 //     reduces into the output slots.
@@ -200,34 +202,38 @@ struct Smem {
     double *D;
     double *E;
     float2 *qband;       // FP32 band (qlo_k, qhi_k), one 8-byte read per edge
-    float2 *pband;       // band in p (plo_k, phi_k), dot-product path
     double *erad;        // edges in radians (pruning)
+    float2 *slots;       // FP32 tiles: lower end and width of every slot
+    uint32_t stage_addr; // FP32 tiles: LDS byte address of the wavefronts' column buffers
+    float4 *edges;       // FP32 tiles: qhi, qhi - qlo, room below and above every edge
     unsigned char *lut;
     uint32_t hist_addr;  // LDS byte address of hist
     uint32_t lut_addr;   // LDS byte address of lut
-    uint32_t plut_addr;  // LDS byte address of the dot-product key's table
-    uint32_t stage_addr; // LDS byte address of the wavefronts' column staging buffers
 };
 
-// LDS layout: the cell table first (at the start of the block's LDS, so a
-// wrapped table is indexed by the masked key itself), then the histograms
-// and the edge thresholds: after the table, or for a wrapped table at
-// aux_off, inside the part of the table that no key reaches.
+// LDS layout: the cell table, then the histograms and the edge thresholds.
+template <bool TILES>
 __device__ __forceinline__ Smem carve(unsigned char *base, const PairArgs &a) {
-    Smem s;
-    const int aux = a.lut_direct ? a.aux_off : (a.lut_cells * a.lut_entry_bytes + 15) & ~15;
+    Smem s = {};
+    const int aux = (a.lut_cells * a.lut_entry_bytes + 15) & ~15;
     int hist_words = kWaves * (a.nslots + 1) * a.hist_copies;
     s.lut = base;
     s.hist = reinterpret_cast<uint32_t *>(base + aux);
-    s.D = reinterpret_cast<double *>(base + aux + hist_words * 4);
-    s.E = s.D + a.nedges;
-    s.erad = s.E + a.nedges;
-    s.qband = reinterpret_cast<float2 *>(s.erad + a.nedges);
-    s.pband = s.qband + a.nedges;
+    unsigned char *edges = base + aux + hist_words * 4;     // 16-aligned
+    if (TILES) {
+        s.edges = reinterpret_cast<float4 *>(edges);
+        s.D = reinterpret_cast<double *>(s.edges + a.nedges);
+        s.qband = reinterpret_cast<float2 *>(s.D + a.nedges);
+        s.slots = s.qband + a.nedges;
+        s.stage_addr = (uint32_t)(uintptr_t)(lds_u32 *)(s.slots + a.nslots);
+    } else {
+        s.D = reinterpret_cast<double *>(edges);
+        s.E = s.D + a.nedges;
+        s.erad = s.E + a.nedges;
+        s.qband = reinterpret_cast<float2 *>(s.erad + a.nedges);
+    }
     s.hist_addr = (uint32_t)(uintptr_t)(lds_u32 *)s.hist;
     s.lut_addr = (uint32_t)(uintptr_t)(lds_u8 *)s.lut;
-    s.plut_addr = s.lut_addr + (uint32_t)a.plut_lds;
-    s.stage_addr = s.lut_addr + (uint32_t)a.stage_lds;
     return s;
 }
 
@@ -320,11 +326,10 @@ __device__ __forceinline__ uint32_t resolve_fp64(uint32_t ent, uint32_t flag, do
 struct Counters {
     uint32_t flag = 0, exact = 0, rare = 0;
     uint32_t beyond = 0;        // this lane's pairs counted beyond the last edge (per unit)
-    // Step kinds of the current column range, 16 bits each (wavefront-
-    // uniform, kept in scalar registers): steps beyond the last edge, in one
-    // slot, in two slots, and (dot-product kernels) steps that formed the
-    // chord; folded into the totals below after every range of at most
-    // kFoldCols columns.
+    // Step kinds of the current column range on the vector paths, 16 bits
+    // each (wavefront-uniform, kept in scalar registers): steps beyond the
+    // last edge, in one slot, in two slots; folded into the totals below
+    // after every range of at most kFoldCols columns.
     uint64_t steps = 0;
     uint32_t beyond_steps = 0, one_slot_steps = 0, two_slot_steps = 0, chord_steps = 0;
     uint32_t pruned_blocks = 0;     // wavefront blocks (P x 64 rows x 64 columns) binned whole (uniform)
@@ -333,7 +338,6 @@ struct Counters {
         beyond_steps += (uint32_t)(steps & 0xFFFF);
         one_slot_steps += (uint32_t)((steps >> 16) & 0xFFFF);
         two_slot_steps += (uint32_t)((steps >> 32) & 0xFFFF);
-        chord_steps += (uint32_t)(steps >> 48);
         steps = 0;
     }
 };
@@ -344,8 +348,8 @@ constexpr int kFoldCols = 65536;
 
 // How a wavefront step was binned (wavefront-uniform).  A step beyond the
 // last edge adds nothing to the histograms: the caller counts its pairs in
-// the lane's register.  kUndecided: the dot product did not settle the step.
-enum : uint32_t { kBeyond = 0, kOneSlot = 1, kTwoSlot = 2, kLookup = 3, kUndecided = 4 };
+// the lane's register.
+enum : uint32_t { kBeyond = 0, kOneSlot = 1, kTwoSlot = 2, kLookup = 3 };
 
 // Per-step bookkeeping, done once after the step whichever way it went (so
 // the counters are not carried through the step's branches).  The step
@@ -361,34 +365,20 @@ __device__ __forceinline__ void account(uint32_t code, Counters &cnt) {
 // Loop constants of one wavefront.
 struct Consts {
     uint32_t shift;
-    uint32_t wbits;         // wrapped table: log2 of its entry count
-    float qfloor;           // wrapped table: the floor q is summed from
     uint32_t clo, chi;      // clamp range (VGPR copies)
     uint32_t lutbias;       // LDS address of cell c is c * entry_bytes + lutbias
     uint32_t rowstep;       // bytes between slots of the histogram
+    uint32_t rowlog;        // its logarithm
     uint32_t lanebase;      // LDS address of this lane's copy of slot 0
     uint32_t flag;          // flag bit of the cell entries (VGPR copy)
     uint32_t beyond;        // PairArgs::beyond_key (VGPR copy)
-    float pbeyond;          // PairArgs::p_beyond
-    // dot-product key's table: cell = bits(q') >> pshift clamped to
-    // [pclo, pchi], LDS address cell * entry_bytes + pbias (VGPR copies: the
-    // dot-product loop then needs no scalar registers for them)
-    uint32_t pshift, pclo, pchi, pbias;
-    uint32_t qdot;          // bits of PairArgs::q_dot
 };
 
 // LDS address of the cell-table entry of an FP32 key (the bit pattern of q)
 // and of an FP64 key (the high word of e; arithmetic shift, so e < 0 lands
 // in the bottom cell).
-template <bool LUT8, bool DIRECT>
+template <bool LUT8>
 __device__ __forceinline__ uint32_t addr32(uint32_t bits, const Consts &k) {
-    if (DIRECT) {
-        // wrapped byte table at LDS address 0 (the kernel has no static LDS,
-        // so its dynamic LDS starts there): the floor keeps every key within
-        // 2^wbits cells of bits(q_floor) >> shift (checked on the host), so
-        // the key's low wbits bits address it without a clamp
-        return __builtin_amdgcn_ubfe(bits, k.shift, k.wbits);
-    }
     return med3_u32(bits >> k.shift, k.clo, k.chi) * (LUT8 ? 1u : 2u) + k.lutbias;
 }
 
@@ -659,7 +649,7 @@ __device__ __forceinline__ int row_of(int ib, int lane, int p) {
 // One step: JN columns against the P rows of every lane.  All JN * P table
 // lookups are issued first; one test sends the wavefront to the rare path if
 // any lane needs it; then the JN * P histogram increments follow.
-template <bool LUT8, bool MASKED, int P, int JN, bool DIRECT, bool M3, bool ONE>
+template <bool LUT8, bool MASKED, int P, int JN, bool M3, bool ONE>
 __device__ __forceinline__ uint32_t step_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
                                           const float (&xi)[P], const float (&yi)[P],
                                           const float (&zi)[P], const int (&ii)[P],
@@ -675,8 +665,7 @@ __device__ __forceinline__ uint32_t step_fp32(const PairArgs &a, const JobDev &j
             float dx = xi[p] - xj[t];
             float dy = yi[p] - yj[t];
             float dz = zi[p] - zj[t];
-            // the wrapped table's sum starts at its floor (same instruction count)
-            float v = DIRECT ? __fmaf_rn(dx, dx, k.qfloor) : dx * dx;
+            float v = dx * dx;
             v = __fmaf_rn(dy, dy, v);
             v = __fmaf_rn(dz, dz, v);
             q[t][p] = v;
@@ -704,8 +693,8 @@ __device__ __forceinline__ uint32_t step_fp32(const PairArgs &a, const JobDev &j
             // save its registers)
             const uint32_t mx = tree_reduce(qb, [](uint32_t x, uint32_t y) { return max(x, y); });
             uint32_t base, span;
-            slot_range<LUT8>(lds_read_entry<LUT8>(addr32<LUT8, DIRECT>(m, k)),
-                             lds_read_entry<LUT8>(addr32<LUT8, DIRECT>(mx, k)), base, span);
+            slot_range<LUT8>(lds_read_entry<LUT8>(addr32<LUT8>(m, k)),
+                             lds_read_entry<LUT8>(addr32<LUT8>(mx, k)), base, span);
             if (one_slot_step(base, span, JN * P, k, cnt))
                 return kOneSlot;
             if (two_slot_range<LUT8>(base, span)) {
@@ -749,7 +738,7 @@ __device__ __forceinline__ uint32_t step_fp32(const PairArgs &a, const JobDev &j
     for (int t = 0; t < JN; ++t) {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            ent[t][p] = lds_read_entry<LUT8>(addr32<LUT8, DIRECT>(__float_as_uint(q[t][p]), k));
+            ent[t][p] = lds_read_entry<LUT8>(addr32<LUT8>(__float_as_uint(q[t][p]), k));
         }
     }
     uint32_t any = 0;
@@ -789,79 +778,6 @@ __device__ __forceinline__ uint32_t step_fp32(const PairArgs &a, const JobDev &j
             lds_inc(__umul24(e, k.rowstep) + k.lanebase);
         }
     return kLookup;
-}
-
-// LDS address of the dot-product key's cell: q' = fl(2 - 2p) as a bit
-// pattern, a negative q' (p > 1) read as +0 through a signed maximum.
-template <bool LUT8>
-__device__ __forceinline__ uint32_t paddr(float qd, const Consts &k) {
-    const uint32_t bits = (uint32_t)max((int32_t)__float_as_uint(qd), 0);
-    return med3_u32(bits >> k.pshift, k.pclo, k.pchi) * (LUT8 ? 1u : 2u) + k.pbias;
-}
-
-// One step of an angular FP32 wavefront decided from the dot product of the
-// FP32 copies, p = fl32(f_i . f_j) (one multiply and two FMAs per pair;
-// |p - d| is bounded by the host's dot_error32).  Whole steps only: all
-// pairs beyond the last edge (p <= p_beyond), every lane's pairs in one slot,
-// or in two adjacent slots with every pair outside the band in p of the edge
-// between them.  The slot range of a lane comes from the cells of the key
-// q' = fl(2 - 2p) of its largest and smallest p (q' does not increase with
-// p).  Returns the step's code, or kUndecided, having counted nothing, when
-// p does not decide the step; the caller then forms the chord.
-template <bool LUT8, int P, int JN>
-__device__ __forceinline__ uint32_t step_dot(const PairArgs &a, const Smem &s, const Consts &k, const float (&xi)[P],
-                                         const float (&yi)[P], const float (&zi)[P], const float (&xj)[JN],
-                                         const float (&yj)[JN], const float (&zj)[JN], Counters &cnt) {
-    float p[JN][P];
-#pragma unroll
-    for (int t = 0; t < JN; ++t)
-#pragma unroll
-        for (int r = 0; r < P; ++r)
-            p[t][r] = __fmaf_rn(zi[r], zj[t], __fmaf_rn(yi[r], yj[t], xi[r] * xj[t]));
-    float pf[JN * P];
-#pragma unroll
-    for (int t = 0; t < JN; ++t)
-#pragma unroll
-        for (int r = 0; r < P; ++r)
-            pf[t * P + r] = p[t][r];
-    const float pmax = tree_reduce(pf, [](float x, float y) { return fmaxf(x, y); });
-    if (wave_all(pmax <= k.pbeyond))
-        return kBeyond;
-    const float pmin = tree_reduce(pf, [](float x, float y) { return fminf(x, y); });
-    uint32_t base, span;
-    slot_range<LUT8>(lds_read_entry<LUT8>(paddr<LUT8>(__fmaf_rn(-2.0f, pmax, 2.0f), k)),
-                     lds_read_entry<LUT8>(paddr<LUT8>(__fmaf_rn(-2.0f, pmin, 2.0f), k)), base, span);
-    if (one_slot_step(base, span, JN * P, k, cnt))
-        return kOneSlot;
-    if (two_slot_range<LUT8>(base, span)) {
-        // a pair is past edge `base` when p <= plo and not past it when
-        // p >= phi.  x = fl(p - phi) is >= 0 exactly when p >= phi, and x < 0
-        // with |x| > w = fl(phi - plo) puts p below plo: these pairs are
-        // decided, the sign bit of x counting those in the upper slot, and
-        // as int32 bit patterns exactly they lie above that of -w (as on the
-        // chord path).  Lanes with one slot compare with -inf (x = +inf,
-        // lower slot) and decide everything; a NaN width decides nothing.
-        const float2 b = s.pband[min(base, (uint32_t)(a.nedges - 1))];
-        const float thr = span ? b.y : -__builtin_huge_valf();
-        const float nw = -(b.y - b.x);
-        const int32_t lim = !span ? INT32_MIN : nw == nw ? (int32_t)__float_as_uint(nw) : INT32_MAX;
-        uint32_t n_up = 0;
-        int32_t m = INT32_MAX;
-#pragma unroll
-        for (int t = 0; t < JN; ++t)
-#pragma unroll
-            for (int r = 0; r < P; ++r) {
-                const float x = p[t][r] - thr;
-                n_up += __float_as_uint(x) >> 31;
-                m = min(m, (int32_t)__float_as_uint(x));
-            }
-        asm volatile("" : "+v"(n_up));
-        if (wave_all(m > lim)) {
-            two_slot_add(base, JN * P, n_up, k, cnt);
-            return kTwoSlot;
-        }
-    }
-    return kUndecided;
 }
 
 template <bool LUT8, bool MASKED, int P, int JN, bool M3, bool ONE>
@@ -976,110 +892,8 @@ __device__ __forceinline__ uint32_t step_fp64(const PairArgs &a, const JobDev &j
     return kLookup;
 }
 
-// One wavefront's copy of columns [base, base + kStageCols) of the three
-// FP32 coordinate arrays (global addresses px, py, pz) into its LDS staging
-// buffer at byte address dst, as kStageCols x, then y, then z floats: lane L
-// below 3 kStageCols / 4 copies 16 bytes, columns [base + 4 sub, +4) of
-// coordinate L / 16 (sub = L % 16) to bytes [16 L, +16), with loads that
-// write LDS directly.  Columns are clamped to start at most at last (a
-// clamped slot is never read).  The lane index is an opaque copy, so that
-// nothing of this stays in registers through the steps.
-__device__ __forceinline__ void stage_columns(uint64_t px, uint64_t py, uint64_t pz, int lane, int base, int last,
-                                              uint32_t dst) {
-    typedef __attribute__((address_space(3))) void *lds_p;
-    typedef __attribute__((address_space(1))) void *glb_p;
-    constexpr int Q = kStageCols / 4;
-    static_assert(Q == 16, "16 lanes per coordinate");
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    if (ln < 3 * Q) {
-        const int coord = ln >> 4, sub = ln & 15;
-        const uint64_t p = coord == 0 ? px : coord == 1 ? py : pz;
-        const int col = min(base + 4 * sub, last);
-        __builtin_amdgcn_global_load_lds((glb_p)((const float *)(uintptr_t)p + col), (lds_p)(uintptr_t)dst, 16, 0,
-                                         0);
-    }
-}
-
-// Steps decided by the dot product alone (dot-product kernels): from column
-// j on, while step_dot settles each step of kColsPerStepF32 columns (beyond
-// the last edge, one slot, two slots).  Returns the first column of the
-// step it could not settle (or of the columns left over), which the chord
-// loop takes next.
-template <bool LUT8, int P>
-__device__ __forceinline__ int dot_run(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
-                                       const float (&xi)[P], const float (&yi)[P], const float (&zi)[P], int j,
-                                       int j1, int lane, Counters &cnt) {
-    // The columns go through LDS: the wavefront copies kStageCols of them at
-    // a time (stage_columns) into one of its two staging buffers, the next
-    // block's copy in flight while the current block is used, and every step
-    // reads its 4 columns' coordinates with three broadcast LDS reads.
-    // Scalar loads of every step's columns, whose waits stall the
-    // wavefront, are measured 1.1-1.2x slower.
-    constexpr int W = kColsPerStepF32, C = kStageCols, Q = C / 4;
-    if (j + W > j1)
-        return j;
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    typedef volatile __attribute__((address_space(3))) f4 *lf4_p;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t st0 = s.stage_addr + wave * (uint32_t)(2 * C * 12);
-    // (opaque copies of the column pointers: the choice among them in
-    // stage_columns is then made on values and never turned into a
-    // lane-indexed read of the job record, which would move it to scratch
-    // memory)
-    uint64_t px = (uint64_t)(uintptr_t)jb.bx32, py = (uint64_t)(uintptr_t)jb.by32,
-             pz = (uint64_t)(uintptr_t)jb.bz32;
-    asm volatile("" : "+s"(px), "+s"(py), "+s"(pz));
-    int cb = j;
-    uint32_t buf = 0;
-    // a copy still in flight from an earlier run (into either buffer) lands
-    // before the first block is copied, then the first block lands
-    __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
-    stage_columns(px, py, pz, lane, cb, j1 - W, st0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    bool more = cb + C + W <= j1;
-    if (more)
-        stage_columns(px, py, pz, lane, cb + C, j1 - W, st0 + C * 12);
-    uint64_t n = 0;     // steps beyond, in one slot, in two slots (16-bit fields)
-    for (;;) {
-        const lf4_p st = (lf4_p)(uintptr_t)(st0 + buf * (C * 12));
-        const int ce = min(cb + C, j1);
-        bool stop = false;
-        for (; j + W <= ce; j += W) {
-            const int q = (j - cb) >> 2;
-            const f4 vx = st[q], vy = st[q + Q], vz = st[q + 2 * Q];
-            const float xj[W] = {vx[0], vx[1], vx[2], vx[3]}, yj[W] = {vy[0], vy[1], vy[2], vy[3]},
-                        zj[W] = {vz[0], vz[1], vz[2], vz[3]};
-            const uint32_t code = step_dot<LUT8, P, W>(a, s, k, xi, yi, zi, xj, yj, zj, cnt);
-            if (code == kUndecided) {
-                stop = true;
-                break;
-            }
-            n += (uint64_t)1 << (16 * code);
-        }
-        if (stop || !more)
-            break;
-        // the block is used up (j == cb + C): wait for the other buffer's
-        // copy, then start the next one into this buffer
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        cb += C;
-        buf ^= 1;
-        more = cb + C + W <= j1;
-        if (more)
-            stage_columns(px, py, pz, lane, cb + C, j1 - W, st0 + (buf ^ 1) * (C * 12));
-    }
-    cnt.beyond += (uint32_t)(n & 0xFFFF) * (uint32_t)(W * P);
-    cnt.steps += n;
-    return j;
-}
-
-// Columns [j0, j1) against the P rows of every lane (FP32 path).  With DOT
-// (angular kernels with the dot-product table), after an unmasked chord step
-// that needed no per-pair lookup and whose smallest q reached q_dot on every
-// lane (the wavefront works at angles where p decides most steps), the
-// following steps go to dot_run; the chord loop resumes at the first step p
-// leaves undecided.
-template <bool LUT8, bool MASKED, int P, bool DIRECT, bool M3, bool ONE, bool DOT>
+// Columns [j0, j1) against the P rows of every lane (FP32 path).
+template <bool LUT8, bool MASKED, int P, bool M3, bool ONE>
 __device__ __forceinline__ void cols_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
                                           const float (&xi)[P], const float (&yi)[P], const float (&zi)[P],
                                           const int (&ii)[P], int ib, int lane, int ie, int j0, int j1,
@@ -1112,7 +926,7 @@ __device__ __forceinline__ void cols_fp32(const PairArgs &a, const JobDev &jb, c
             // keep the prefetch at the top of the step
             __builtin_amdgcn_sched_barrier(0);
             uint32_t qmin = 0;
-            const uint32_t code = __builtin_amdgcn_readfirstlane(step_fp32<LUT8, MASKED, P, JN, DIRECT, M3, ONE>(
+            const uint32_t code = __builtin_amdgcn_readfirstlane(step_fp32<LUT8, MASKED, P, JN, M3, ONE>(
                 a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, xj, yj, zj, qmin, cnt));
             account<JN * P>(code, cnt);
 #pragma unroll
@@ -1121,29 +935,12 @@ __device__ __forceinline__ void cols_fp32(const PairArgs &a, const JobDev &jb, c
                 yj[t] = yn[t];
                 zj[t] = zn[t];
             }
-            if constexpr (DOT && !MASKED && !M3) {
-                cnt.steps += (uint64_t)1 << 48;     // a step that formed the chord
-                if (code != kLookup && wave_all(qmin >= k.qdot)) {
-                    const int js = dot_run<LUT8, P>(a, jb, s, k, xi, yi, zi, j + JN, j1, lane, cnt);
-                    if (js != j + JN) {
-                        j = js - JN;
-                        if (js + JN <= j1) {
-#pragma unroll
-                            for (int t = 0; t < JN; ++t) {
-                                xj[t] = bx[js + t];
-                                yj[t] = by[js + t];
-                                zj[t] = bz[js + t];
-                            }
-                        }
-                    }
-                }
-            }
         }
     }
     for (; j < j1; ++j) {
         const float xj[1] = {bx[j]}, yj[1] = {by[j]}, zj[1] = {bz[j]};
         uint32_t qmin = 0;
-        account<P>(__builtin_amdgcn_readfirstlane(step_fp32<LUT8, MASKED, P, 1, DIRECT, M3, false>(
+        account<P>(__builtin_amdgcn_readfirstlane(step_fp32<LUT8, MASKED, P, 1, M3, false>(
                        a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, xj, yj, zj, qmin, cnt)),
                    cnt);
     }
@@ -1152,7 +949,7 @@ __device__ __forceinline__ void cols_fp32(const PairArgs &a, const JobDev &jb, c
 
 
 // One wavefront: rows [ib, ie) (at most P * 64) against columns [j0, j1).
-template <bool LUT8, bool MASKED, int P, bool DIRECT, bool PRUNE, bool M3, bool DOT>
+template <bool LUT8, bool MASKED, int P, bool PRUNE, bool M3>
 __device__ void rows_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k, int ib, int ie,
                           int j0, int j1, int lane, Counters &cnt) {
     float xi[P], yi[P], zi[P];
@@ -1186,13 +983,13 @@ __device__ void rows_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, co
                     continue;
                 }
             }
-            cols_fp32<LUT8, MASKED, P, DIRECT, M3, true, DOT>(a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, jn, cnt);
+            cols_fp32<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, jn, cnt);
             j = jn;
         }
         return;
     }
     for (int jc = j0; jc < j1; jc += kFoldCols)
-        cols_fp32<LUT8, MASKED, P, DIRECT, M3, true, DOT>(a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, jc,
+        cols_fp32<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, jc,
                                                           j1 - jc > kFoldCols ? jc + kFoldCols : j1, cnt);
 }
 
@@ -1254,63 +1051,763 @@ __device__ void rows_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, co
                                              j1 - jc > kFoldCols ? jc + kFoldCols : j1, cnt);
 }
 
-// PREC: 0 FP32 chord with a clamped table, 3 FP32 chord with a direct byte
-// table, 6 and 7 the same with the dot product tried first (angular), 1 FP64
-// vector; 3-D distances: 5 FP32 squared distance with a
-// clamped table, 4 FP64 vector.  P: rows per lane (a wavefront covers P * 64
-// rows of a unit).
+// ---------------------------------------------------------------------------
+// FP32 tiles on the matrix cores.
+//
+// A wavefront takes 32 G rows (G groups of 32) and walks its columns 32 at a
+// time.  One v_mfma_f32_32x32x16_f16 forms the squared distances of a tile
+// of 32 rows x 32 columns,
+//     q^ = |b'|^2 + |a'|^2 - 2 a'.b',   a' = S (f_i - c),  b' = S (f_j - c),
+// of the FP32 copies f relative to the rows' mean c, scaled by S = 2^e (a
+// power of two that keeps every operand within f16's range).  Each FP32
+// operand enters as the sum of two f16 values (high and low part, all four
+// products of a coordinate are formed), |a'|^2 as two more products with a
+// constant, and |b'|^2 as the FP32 accumulator input.  A lane holds one
+// column against 16 consecutive rows (rows of a group are dealt to the matrix
+// rows so that each half of the wavefront gets 16 consecutive ones), so its
+// pairs span a narrow range of distances.
+//
+// |q^ - S^2 |f_i - f_j|^2| <= e = u (kTileErrN |b'|^2 + kTileErrA rho^2 +
+// kTileErr0) with u = 2^-24 and rho the largest |a'| of the wavefront.  The
+// chord band [qlo_k, qhi_k) holds for |f_i - f_j|^2 itself, so q^ - e >= qhi_k
+// puts a pair past edge k and q^ + e < qlo_k before it.  The threshold that a
+// test compares with goes into the accumulator input, so the matrix core
+// delivers the difference.  Per 32 columns, cheapest first:
+//   1. every lane takes the slot of its column's distance from the rows' mean
+//      and forms x = q^ - (L + e) for the slot's lower end L: the lane's pairs
+//      of a tile are all in that slot when the largest x, as an unsigned bit
+//      pattern (negative values lie above all others), is below the slot's
+//      width.  No branch and no LDS access; the overflow slot is one of the
+//      slots, with an infinite width (tile_screen);
+//   2. tiles that fail take the edge nearest to the column's distance,
+//      x = q^ - (qhi + e): the sign of x is the pair's side while |x| stays
+//      within the neighbouring edges, and the few pairs that lie within e of
+//      the band are settled one by one from FP32 differences and, inside the
+//      band, by the FP64 rule (tile_split);
+//   3. the rest look every pair up in the cell table, by q^ where e is below
+//      2^-16 of it (tile_cells), else by FP32 differences (tile_lookup: close
+//      pairs).
+// Tiles with masked pairs (the diagonal, the rows' ends) go to 3.
+//
+// What bounds it: vector issue.  An instruction costs about 4 cycles of a
+// SIMD (2 for plain two-operand adds, moves and shifts), the MFMA 32 cycles
+// of the matrix core and about 9 of the vector unit's.  Reducing the 16
+// values of a lane takes 8 three-operand maxima, so a tile of stage 1 costs
+// at least 10 instructions; the preparation of 64 columns (each lane one,
+// dealt to two tiles of 32 with v_permlane32_swap) and the accumulator input
+// add 5.  Measured: 1e6 x 2e6 points to 30 deg 408 -> 228 ms a DD+DR+RR step
+// against the vector kernel it replaces (chord and FP32 dot product), edges
+// to 120 deg (2e5 x 4e5) 30.5 -> 18.4 ms, 200 bins 23.0 -> 15.3 ms, a 3-D
+// box of 5e5 x 1e6 112.9 -> 53.3 ms; on pairs all beyond the last edge 28
+// Tpairs/s (15 before).  Tried and slower: all decisions in one branchy pass
+// (307 ms), 32 columns prepared per pass (252), prefetched columns in
+// registers (they were spilled and waited for, 246).
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+union Frag {
+    uint32_t d[4];
+    half8 h;
+};
+
+__device__ __forceinline__ uint32_t pack_f16(_Float16 lo, _Float16 hi) {
+    union {
+        _Float16 h[2];
+        uint32_t u;
+    } x;
+    x.h[0] = lo;
+    x.h[1] = hi;
+    return x.u;
+}
+
+// v as high and low f16 parts, the low one times m (a power of two).
+__device__ __forceinline__ uint32_t split_f16(float v, float m) {
+    const _Float16 h = (_Float16)v;
+    const _Float16 l = (_Float16)((v - (float)h) * m);
+    return pack_f16(h, l);
+}
+
+__device__ __forceinline__ uint32_t swap_f16(uint32_t x) { return __builtin_amdgcn_alignbit(x, x, 16); }
+
+// |a'|^2 enters as (h 2^14 + l 2^4) with h + l 2^-10 = |a'|^2 2^-14.
+constexpr float kNormScale = 6.103515625e-05f;
+constexpr float kNormLow = 1024.0f;
+
+__device__ __forceinline__ float wave_sum_f(float v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+        v += __shfl_xor(v, off, kWaveSize);
+    return v;
+}
+
+__device__ __forceinline__ float wave_max_f(float v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+        v = fmaxf(v, __shfl_xor(v, off, kWaveSize));
+    return v;
+}
+
+// A wavefront-uniform float moved to a scalar register.
+__device__ __forceinline__ float uniform_f(float v) {
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+
+// Squared distance of the FP32 copies from their differences, times S^2.
+__device__ __forceinline__ float diff_q(float xi, float yi, float zi, float xj, float yj, float zj, int exp2) {
+    const float dx = xi - xj, dy = yi - yj, dz = zi - zj;
+    float v = dx * dx;
+    v = __fmaf_rn(dy, dy, v);
+    v = __fmaf_rn(dz, dz, v);
+    return ldexpf(v, exp2);
+}
+
+// Element i of the array that starts at the wavefront-uniform address base +
+// at: a scalar base and a 32-bit offset per lane.
+template <typename T>
+__device__ __forceinline__ T lane_load(const T *base, int64_t at, int i) {
+    typedef const __attribute__((address_space(1))) char *gchar_p;
+    typedef const __attribute__((address_space(1))) T *g_p;
+    return *(g_p)((gchar_p)(base + at) + (uint32_t)i * (uint32_t)sizeof(T));
+}
+
+// A tile's pairs: the lane's column is j0 + jo, its rows start at i0 + io
+// (i0 and j0 wavefront-uniform).
+struct TilePos {
+    int i0, j0, io, jo;
+};
+
+// The job record of the tiles, in constant memory: the paths that settle
+// pairs one by one read its pointers when they need them (through an opaque
+// copy of its address, so that the loads stay there), which leaves the scalar
+// registers to the column loop.
+typedef const __attribute__((address_space(4))) JobDev *cjob_p;
+typedef const __attribute__((address_space(4))) PairArgs *cargs_p;
+
+__device__ __forceinline__ cjob_p fresh(cjob_p p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// The rule's value of the pair at row offset i and column offset j.
+template <bool M3>
+__device__ __forceinline__ double rule_at(cjob_p job, const TilePos &t, int i, int j) {
+    const cjob_p p = fresh(job);
+    return rule_value<M3>(lane_load(p->ax64, t.i0, i), lane_load(p->ay64, t.i0, i), lane_load(p->az64, t.i0, i),
+                          lane_load(p->bx64, t.j0, j), lane_load(p->by64, t.j0, j), lane_load(p->bz64, t.j0, j));
+}
+
+// Is row io + r of the tile past edge k against the lane's column?  FP32
+// differences against the band, inside it the FP64 rule.
+template <bool M3>
+__device__ __forceinline__ bool past_edge(int q_exp2, cjob_p job, const Smem &s, int k, const TilePos &t, int r,
+                                          Counters &cnt) {
+    int i = t.io + r, j = t.jo;
+    const cjob_p p = fresh(job);
+    const float2 b = s.qband[k];
+    const float q = diff_q(lane_load(p->ax32, t.i0, i), lane_load(p->ay32, t.i0, i), lane_load(p->az32, t.i0, i),
+                           lane_load(p->bx32, t.j0, j), lane_load(p->by32, t.j0, j), lane_load(p->bz32, t.j0, j),
+                           q_exp2);
+    ++cnt.flag;
+    if (q < b.x)
+        return false;
+    if (q >= b.y)
+        return true;
+    ++cnt.exact;
+    return rule_at<M3>(job, t, i, j) <= s.D[k];
+}
+
+// The sixteen values of a lane as integers.
+__device__ __forceinline__ void tile_bits(const floatx16 &acc, int32_t (&b)[16]) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        b[r] = (int32_t)__float_as_uint(acc[r]);
+}
+
+// Cell entries of the tiles (16 bits): the histogram row of the cell's slot,
+// slot * rowstep, with kCellOpen set when an edge lies in the cell (the slot
+// is then the lower one) and kCellMulti too when several do.  Rows are at
+// least 16 bytes apart, so the flags are below them.
+constexpr uint32_t kCellFlags = 15u;
+
+__device__ __forceinline__ uint32_t cell_entry(float q, const Consts &k) {
+    const int32_t c = med3_i32((int32_t)__float_as_uint(q) >> (int)k.shift, (int32_t)k.clo, (int32_t)k.chi);
+    return *(const lds_u16 *)(uintptr_t)(((uint32_t)c << 1) + k.lutbias);
+}
+
+// What the tiles use of the launch's arguments.
+struct TileArgs {
+    int32_t nedges, q_exp2;
+};
+
+// Histogram row of one pair (row io, column jo) from FP32 differences and,
+// where its cell or an edge's band leaves it open, the FP64 rule.
+template <bool M3>
+__device__ __forceinline__ uint32_t settle_row(const TileArgs &a, cjob_p job, const Smem &s, const Consts &k,
+                                               const TilePos &t, Counters &cnt) {
+    const cjob_p p = fresh(job);
+    const float q = diff_q(lane_load(p->ax32, t.i0, t.io), lane_load(p->ay32, t.i0, t.io),
+                           lane_load(p->az32, t.i0, t.io), lane_load(p->bx32, t.j0, t.jo),
+                           lane_load(p->by32, t.j0, t.jo), lane_load(p->bz32, t.j0, t.jo), a.q_exp2);
+    const uint32_t ent = cell_entry(q, k), row = ent & ~kCellFlags;
+    if (!(ent & kCellOpen))
+        return row;
+    if (!(ent & kCellMulti)) {
+        const float2 b = s.qband[row >> k.rowlog];
+        if (q < b.x)
+            return row;
+        if (q >= b.y)
+            return row + k.rowstep;
+    }
+    ++cnt.exact;
+    return count_le(rule_at<M3>(job, t, t.io, t.jo), s.D, a.nedges) * k.rowstep;
+}
+
+// Bin one tile with a table lookup per pair, by squared distances q that lie
+// within e of those of the FP32 copies (and within 2^-16 of them, for which
+// the cells hold); the first w of the lane's rows count.  Pairs of cells that
+// hold an edge compare q -+ e with its band; those inside it go to the
+// discard row and are settled afterwards, from FP32 differences and by the
+// FP64 rule.
+template <bool M3>
+__device__ __forceinline__ void tile_cells(const TileArgs &a, cjob_p job, const Smem &s, const Consts &k,
+                                           const float (&q)[16], float e, const TilePos &t, uint32_t w,
+                                           Counters &cnt) {
+    uint32_t open = 0;      // bit r: pair r is not settled yet
+    const uint32_t discard = (uint32_t)(a.nedges + 1) * k.rowstep;
+    const bool part = __builtin_amdgcn_ballot_w64(w != 16u) != 0;
+#pragma unroll
+    for (int b = 0; b < 16; b += 4) {
+        uint32_t ent[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            ent[r] = cell_entry(q[b + r], k);
+        if (__builtin_amdgcn_ballot_w64(((ent[0] | ent[1] | ent[2] | ent[3]) & kCellOpen) != 0) != 0) {
+            // on every lane: a certain pair's row stays (an edge's band read
+            // for it decides nothing)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t row = ent[r] & ~kCellFlags;
+                const float2 bd = s.qband[min(row >> k.rowlog, (uint32_t)(a.nedges - 1))];
+                const bool one = (ent[r] & kCellFlags) == kCellOpen, edge = (ent[r] & kCellOpen) != 0;
+                const uint32_t up = q[b + r] - e >= bd.y ? row + k.rowstep : q[b + r] + e < bd.x ? row : discard;
+                ent[r] = edge ? one ? up : discard : row;
+                open |= edge && ent[r] == discard ? 1u << (b + r) : 0u;
+                cnt.flag += edge && (uint32_t)(b + r) < w ? 1u : 0u;
+            }
+        }
+        if (part) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                ent[r] = (uint32_t)(b + r) < w ? ent[r] : discard;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            lds_inc(ent[r] + k.lanebase);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    open &= (1u << w) - 1u;
+    if (__builtin_amdgcn_ballot_w64(open != 0) == 0)
+        return;
+    ++cnt.rare;
+    while (open) {
+        TilePos p = t;
+        p.io += __builtin_ctz(open);
+        open &= open - 1u;
+        lds_inc(settle_row<M3>(a, job, s, k, p, cnt) + k.lanebase);
+    }
+}
+
+// Squared distances of one tile from FP32 differences.  Rows past the last
+// (offset ilast) read that one.
+__device__ __forceinline__ void tile_diffs(const TileArgs &a, cjob_p job, const TilePos &t, int ilast,
+                                           float (&q)[16]) {
+    int io = t.io;
+    asm volatile("" : "+v"(io));
+    const cjob_p p = fresh(job);
+    const float xj = lane_load(p->bx32, t.j0, t.jo), yj = lane_load(p->by32, t.j0, t.jo),
+                zj = lane_load(p->bz32, t.j0, t.jo);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = min(io + r, ilast);
+        q[r] = diff_q(lane_load(p->ax32, t.i0, i), lane_load(p->ay32, t.i0, i), lane_load(p->az32, t.i0, i), xj, yj,
+                      zj, a.q_exp2);
+        if ((r & 3) == 3)
+            __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Longest run of edges tile_count compares every pair with: an edge costs
+// about 50 instructions a lane, a lookup tile as much as nine of them in LDS
+// reads and atomics.
+constexpr uint32_t kMaxSpan = 6;
+
+// Slots of a lane's pairs from the cells of its smallest and largest q
+// (within e): the lowest slot's histogram row and the number of edges above
+// it.
+__device__ __forceinline__ void tile_span(const float (&q)[16], float e, const Consts &k, uint32_t &row,
+                                          uint32_t &span) {
+    const float qmin = tree_reduce(q, [](float x, float y) { return fminf(x, y); });
+    const float qmax = tree_reduce(q, [](float x, float y) { return fmaxf(x, y); });
+    const uint32_t lo = cell_entry(qmin - e, k), hi = cell_entry(qmax + e, k);
+    row = lo & ~kCellFlags;
+    // a cell with several edges says nothing: too long a span
+    span = ((hi - row) >> k.rowlog) + (hi & kCellOpen);
+    span = (lo | hi) & kCellMulti ? ~0u : span;
+}
+
+// Bin one tile by comparing every pair with the lane's `span` edges above
+// histogram row `row`: the pairs before an edge and not before the one below
+// it go to the slot between them.  q lies within e of the squared distances
+// of the FP32 copies; the first w of the lane's rows count.
+template <bool M3>
+__device__ __forceinline__ void tile_count(const TileArgs &a, cjob_p job, const Smem &s, const Consts &k,
+                                           const float (&q)[16], float e, uint32_t row, uint32_t span,
+                                           const TilePos &t, uint32_t w, Counters &cnt) {
+    const uint32_t counted = 0xFFFF0000u >> w & 0xFFFFu;    // bit 15 - r: pair r counts
+    uint32_t prev = 0, at = row + k.lanebase, ke = row >> k.rowlog, rare = 0;
+#pragma unroll 1
+    for (;; ++ke, at += k.rowstep, --span) {
+        // span: edges left (counted down past 0 on lanes that are done)
+        const bool on = (int32_t)span > 0;
+        if (__builtin_amdgcn_ballot_w64(on) == 0)
+            break;
+        float2 b = s.qband[min(ke, (uint32_t)(a.nedges - 1))];
+        asm volatile("" : "+v"(b.x), "+v"(b.y));            // read on every lane: no branch
+        const float thr = b.y + e;
+        const int32_t lim = on ? (int32_t)__float_as_uint(__fmaf_rn(-2.0f, e, b.x - b.y)) : INT32_MIN;
+        uint32_t before = 0;
+        int32_t near = INT32_MAX;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint32_t x = __float_as_uint(q[r] - thr);
+            before = __builtin_amdgcn_alignbit(before, x, 31);
+            near = min(near, (int32_t)x);
+        }
+        asm volatile("" : "+v"(before));
+        if (__builtin_amdgcn_ballot_w64(near <= lim) != 0) {
+            uint32_t und = 0;   // bit 15 - r: pair r is undecided
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                und = und * 2u + ((int32_t)__float_as_uint(q[r] - thr) <= lim ? 1u : 0u);
+            und &= counted;
+            rare = 1;
+            while (und) {
+                const int bit = __builtin_ctz(und);
+                und &= und - 1u;
+                const bool past = past_edge<M3>(a.q_exp2, job, s, (int)ke, t, 15 - bit, cnt);
+                before = past ? before & ~(1u << bit) : before;
+            }
+        }
+        // a lane past its last edge adds what is left to that edge's upper
+        // slot, once
+        const uint32_t n = on ? (uint32_t)__builtin_popcount(before & counted) : w;
+        if ((int32_t)span >= 0)
+            lds_add(at, n - prev);
+        prev = n;
+    }
+    if (span == 0)
+        lds_add(at, w - prev);
+    cnt.rare += rare;
+}
+
+// q^ (less what c takes off) of one tile.
+__device__ __forceinline__ floatx16 tile_q(const Frag &fa, const Frag &fb, const floatx16 &c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(fa.h, fb.h, c, 0, 0, 0);
+}
+
+// Row operands of G groups, four words each.
+typedef uint32_t uintx32 __attribute__((ext_vector_type(32)));
+
+__device__ __forceinline__ Frag rows_at(const uintx32 &fa, int g) {
+    Frag f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        f.d[i] = fa[4 * g + i];
+    return f;
+}
+
+__device__ __forceinline__ void broadcast(floatx16 &c, float v) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        c[r] = v;
+}
+
+// bits = 2 bits + (any lane's bit set), on the scalar unit.
+__device__ __forceinline__ void push_any(uint32_t &bits, uint64_t lanes) {
+    asm("s_cmp_lg_u64 %1, 0\n\ts_addc_u32 %0, %0, %0" : "+s"(bits) : "s"(lanes) : "scc");
+}
+
+// Values of 64 columns, one per lane, dealt to the lanes of two tiles of 32
+// columns (each column in lane and lane + 32): lo holds those of columns
+// 0-31, hi those of columns 32-63.
+__device__ __forceinline__ void deal(uint32_t v, uint32_t &lo, uint32_t &hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    lo = r[0];
+    hi = r[1];
+}
+
+// The same for operands whose lower half takes v and whose upper half takes
+// u of the same columns.
+__device__ __forceinline__ void deal2(uint32_t v, uint32_t u, uint32_t &lo, uint32_t &hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, u, false, false);
+    lo = r[0];
+    hi = r[1];
+}
+
+// Is e at most kTileFar of every counted q of the wavefront?
+__device__ __forceinline__ bool far_enough(const float (&q)[16], float e, uint32_t w) {
+    const float qmin = tree_reduce(q, [](float x, float y) { return fminf(x, y); });
+    return __builtin_amdgcn_ballot_w64(!(qmin * kTileFar > e) && w) == 0;
+}
+
+// Columns [j, j + 64) of the three coordinate arrays into the wavefront's
+// LDS buffer (x, y, z of 64 floats at byte address dst) with loads that write
+// LDS directly: the copy in flight takes no registers.  Lanes past the last
+// column (last) read that one.
+__device__ __forceinline__ void stage_columns(const float *bx, const float *by, const float *bz, int j, int last,
+                                              int lane, uint32_t dst) {
+    typedef __attribute__((address_space(3))) void *lds_p;
+    typedef __attribute__((address_space(1))) void *glb_p;
+    const int jo = min(lane, last - j);
+    __builtin_amdgcn_global_load_lds((glb_p)(bx + j + jo), (lds_p)(uintptr_t)dst, 4, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_p)(by + j + jo), (lds_p)(uintptr_t)(dst + 256), 4, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_p)(bz + j + jo), (lds_p)(uintptr_t)(dst + 512), 4, 0, 0);
+}
+
+// nb and histogram row (~0 for a lane whose column does not exist) of the
+// lane's column in the tile of columns h (0 or 32) on.
+__device__ __forceinline__ void column_state(int h, float nb, uint32_t row, bool valid, float &nbh, uint32_t &rowh) {
+    uint32_t n0, n1, r0, r1;
+    deal(__float_as_uint(nb), n0, n1);
+    deal(valid ? row : ~0u, r0, r1);
+    nbh = __uint_as_float(h ? n1 : n0);
+    rowh = h ? r1 : r0;
+}
+
+// The G tiles of 32 columns, x = q^ - (L + e) from the accumulator input: bit
+// g is set when some lane's pairs of tile g are not all in the lane's slot (a
+// pattern at or above `width`).  No branch between the tiles, and the matrix
+// core works on the next tile while this one is reduced.
+template <int G>
+__device__ __forceinline__ uint32_t tile_screen(const uintx32 &fa, const Frag &fb, float base, uint32_t width) {
+    floatx16 c;
+    broadcast(c, base);
+    uint32_t mask = 0;
+    floatx16 acc = tile_q(rows_at(fa, G - 1), fb, c);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = G - 1; g >= 0; --g) {
+        const floatx16 cur = acc;
+        if (g > 0)
+            acc = tile_q(rows_at(fa, g - 1), fb, c);
+        __builtin_amdgcn_sched_barrier(0);
+        int32_t x[16];
+        tile_bits(cur, x);
+        const uint32_t top = (uint32_t)tree_reduce(
+            x, [](int32_t u, int32_t v) { return (int32_t)max((uint32_t)u, (uint32_t)v); });
+        push_any(mask, __builtin_amdgcn_ballot_w64(top >= width));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return mask;
+}
+
+// One tile against edge k, x = q^ - (qhi_k + e): adds the lane's number of
+// pairs before the edge to n_before.  room bounds |x| so that no other edge
+// is reached, lim is the bit pattern of -((qhi_k - qlo_k) + 2e): x in
+// [that, 0) leaves a pair undecided.  On signed bit patterns the decided x
+// lie above lim (a negative float's pattern grows with its magnitude), so one
+// signed minimum checks every pair.  False, with nothing counted, when some
+// lane needs more than one edge or has more than three undecided pairs.
+template <bool M3>
+__device__ __forceinline__ bool tile_split(int q_exp2, cjob_p job, const Smem &s, const floatx16 &x, int k,
+                                           float room, int32_t lim, const TilePos &t, uint32_t &n_before,
+                                           Counters &cnt) {
+    float ax[16];
+    int32_t b[16];
+    tile_bits(x, b);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        ax[r] = fabsf(x[r]);
+    const float far = tree_reduce(ax, [](float u, float v) { return fmaxf(u, v); });
+    if (__builtin_amdgcn_ballot_w64(!(far < room)) != 0)
+        return false;
+    const int32_t near = tree_reduce(b, [](int32_t u, int32_t v) { return min(u, v); });
+    uint32_t before = 0;    // bit 15 - r: pair r is before the edge
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        before = __builtin_amdgcn_alignbit(before, (uint32_t)b[r], 31);
+    if (__builtin_amdgcn_ballot_w64(near <= lim) != 0) {
+        uint32_t und = 0;   // bit 15 - r: pair r is undecided
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            und = und * 2u + (b[r] <= lim ? 1u : 0u);
+        if (__builtin_amdgcn_ballot_w64(__builtin_popcount(und) > 3) != 0)
+            return false;
+        ++cnt.rare;
+        while (und) {
+            const int bit = __builtin_ctz(und);
+            und &= und - 1u;
+            const bool past = past_edge<M3>(q_exp2, job, s, k, t, 15 - bit, cnt);
+            before = past ? before & ~(1u << bit) : before;
+        }
+    }
+    n_before += (uint32_t)__builtin_popcount(before);
+    return true;
+}
+
+// Low n bits, n clamped to [0, G].
+template <int G>
+__device__ __forceinline__ uint32_t low_bits(int n) {
+    return (1u << min(max(n, 0), G)) - 1u;
+}
+
+// One wavefront: rows [ib, ie) (at most 32 G) against columns [j0, j1).
+template <int G, bool M3>
+__device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts &k, int ib, int ie, int j0, int j1,
+                           int lane, Counters &cnt) {
+    const int half = lane >> 5;
+    const float S = args->q_scale, q_small = args->q_small;
+    const TileArgs a{args->nedges, args->q_exp2};
+    const bool auto_pairs = job->auto_pairs != 0;
+    uintx32 fa;
+    float cx, cy, cz, rho2 = 0.0f;
+    {
+        // matrix row m of a group is row 16 ((m >> 2) & 1) + 4 (m >> 3) + (m & 3)
+        const int m = lane & 31, row = 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3);
+        float x[G], y[G], z[G], sx = 0.0f, sy = 0.0f, sz = 0.0f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = min(32 * g + row, ie - 1 - ib);
+            x[g] = lane_load(job->ax32, ib, i);
+            y[g] = lane_load(job->ay32, ib, i);
+            z[g] = lane_load(job->az32, ib, i);
+            sx += x[g];
+            sy += y[g];
+            sz += z[g];
+        }
+        const float f = S / (float)(G * kWaveSize);
+        cx = uniform_f(wave_sum_f(sx) * f);
+        cy = uniform_f(wave_sum_f(sy) * f);
+        cz = uniform_f(wave_sum_f(sz) * f);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float xs = __fmaf_rn(x[g], S, -cx), ys = __fmaf_rn(y[g], S, -cy), zs = __fmaf_rn(z[g], S, -cz);
+            const float na = __fmaf_rn(zs, zs, __fmaf_rn(ys, ys, xs * xs));
+            rho2 = fmaxf(rho2, na);
+            const uint32_t v0 = split_f16(-2.0f * (half ? zs : xs), 1.0f);
+            const uint32_t v1 = split_f16(half ? na * kNormScale : -2.0f * ys, half ? kNormLow : 1.0f);
+            fa[4 * g] = v0;
+            fa[4 * g + 1] = swap_f16(v0);
+            fa[4 * g + 2] = v1;
+            fa[4 * g + 3] = half ? 0u : swap_f16(v1);
+        }
+        rho2 = uniform_f(wave_max_f(rho2));
+    }
+    const float u = 5.9604644775390625e-08f;
+    const float e_rows = uniform_f(u * (kTileErrA * rho2 + kTileErr0));
+    const uint32_t b_const = pack_f16((_Float16)16384.0f, (_Float16)16.0f);
+    const uint32_t overflow = (uint32_t)a.nedges << k.rowlog;
+    // tiles whose rows all exist, and those with any
+    const int nr = ie - ib;
+    const uint32_t rows_ok = low_bits<G>(nr >> 5), rows_any = low_bits<G>((nr + 31) >> 5);
+    uint32_t n_beyond = 0;
+    // columns up to the first row count nothing
+    if (auto_pairs && j0 <= ib)
+        j0 = ib + 1;
+    if (j0 >= j1)
+        return;
+    const float *bx = job->bx32, *by = job->by32, *bz = job->bz32;
+    // the next 64 columns are on their way into LDS while these are used
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t stage = s.stage_addr + wave * (uint32_t)kStageWaveBytes;
+    typedef volatile __attribute__((address_space(3))) float *lfloat_p;
+    const lfloat_p col = (lfloat_p)(uintptr_t)(stage + 4u * (uint32_t)lane);
+    stage_columns(bx, by, bz, j0, j1 - 1, lane, stage);
+    for (int j = j0; j < j1; j += 64) {
+        // each lane prepares one of 64 columns, then the values are dealt to
+        // the two tiles of 32
+        __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): the copy has landed
+        float xn = col[0], yn = col[64], zn = col[128];
+        // read before the next copy overwrites them
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(xn), "+v"(yn), "+v"(zn) : : "memory");
+        if (j + 64 < j1)
+            stage_columns(bx, by, bz, j + 64, j1 - 1, lane, stage);
+        const float xs = __fmaf_rn(xn, S, -cx), ys = __fmaf_rn(yn, S, -cy), zs = __fmaf_rn(zn, S, -cz);
+        const float nb = __fmaf_rn(zs, zs, __fmaf_rn(ys, ys, xs * xs));
+        Frag f;
+        uint32_t f1[2], base, base1, width, width1;
+        deal2(split_f16(xs, 1.0f), split_f16(zs, 1.0f), f.d[0], f1[0]);
+        deal2(split_f16(ys, 1.0f), b_const, f.d[2], f1[1]);
+        // the slot of the column's distance from the rows' mean: its row in
+        // the histogram, lower end and width
+        const uint32_t row = cell_entry(nb, k) & ~kCellFlags;
+        const bool valid = j + lane < j1;
+        {
+            const float2 sl = s.slots[row >> k.rowlog];
+            const float es = __fmaf_rn(8.0f * u, fabsf(sl.x), __fmaf_rn(u * kTileErrN, nb, e_rows));
+            const uint32_t wd = __float_as_uint(fmaxf(__fmaf_rn(-2.0f, es, sl.y), 0.0f));
+            deal(__float_as_uint(nb - (sl.x + es)), base, base1);
+            deal(valid ? wd : ~0u, width, width1);
+        }
+        uint32_t n_in = 0;      // tiles in one slot: columns 0-31, columns 32-63 (<< 16)
+#pragma unroll 1
+        for (int h = 0; h < 64; h += 32) {
+            f.d[1] = f.d[0];
+            f.d[3] = f.d[2];    // (the rows' fourth word is 0 in the upper half)
+            // tiles all of whose pairs count (for auto-pairs: every column
+            // after every row), and those where some do
+            uint32_t ok = rows_ok, any = rows_any;
+            const int jh = j + h;
+            if (auto_pairs) {
+                ok &= low_bits<G>((jh - ib) >> 5);
+                any &= low_bits<G>((min(jh + 31, j1 - 1) - ib + 31) >> 5);
+            }
+            if (jh >= j1)
+                any = ok = 0;
+            uint32_t rest = any & ~ok;
+            if (ok) {
+                uint32_t todo = ok & tile_screen<G>(fa, f, __uint_as_float(base), width);
+                n_in += (uint32_t)__builtin_popcount(ok & ~todo) << (h >> 1);
+                if (todo) {
+                    // the nearest edge of every column: its slot's upper one
+                    // above the slot's middle, else the lower one
+                    float nbh, eh;
+                    uint32_t ke;
+                    column_state(h, nb, row, valid, nbh, ke);
+                    const bool vh = ke != ~0u;
+                    ke >>= k.rowlog;
+                    eh = __fmaf_rn(u * kTileErrN, nbh, e_rows);
+                    const float2 sl = s.slots[min(ke, (uint32_t)a.nedges)];
+                    ke = nbh > __fmaf_rn(0.5f, sl.y, sl.x) ? ke : ke - 1u;
+                    const float4 ed = s.edges[min(ke, (uint32_t)(a.nedges - 1))];   // qhi, qhi - qlo, room below, above
+                    eh = __fmaf_rn(8.0f * u, ed.x, eh);
+                    const float room = vh ? fminf(ed.z, __fmaf_rn(-2.0f, eh, ed.w)) : __builtin_huge_valf();
+                    const int32_t lim = vh ? (int32_t)__float_as_uint(__fmaf_rn(-2.0f, eh, -ed.y)) : INT32_MIN;
+                    const float off = nbh - (ed.x + eh);
+                    uint32_t n_before = 0, nd = 0;
+                    while (todo) {
+                        const int g = __builtin_ctz(todo);
+                        todo &= todo - 1u;
+                        const TilePos t{ib, j, 32 * g + 16 * half, min(h + (lane & 31), j1 - 1 - j)};
+                        floatx16 c;
+                        broadcast(c, off);
+                        if (tile_split<M3>(a.q_exp2, job, s, tile_q(rows_at(fa, g), f, c), (int)ke, room, lim, t,
+                                           n_before, cnt))
+                            ++nd;
+                        else
+                            rest |= 1u << g;
+                    }
+                    if (nd) {
+                        if (vh) {
+                            const uint32_t at = (ke << k.rowlog) + k.lanebase;
+                            lds_add(at, n_before);
+                            lds_add(at + k.rowstep, 16u * nd - n_before);
+                        }
+                        cnt.two_slot_steps += nd;
+                    }
+                }
+            }
+            while (rest) {
+                const int g = __builtin_ctz(rest);
+                rest &= rest - 1u;
+                const TilePos t{ib, j, 32 * g + 16 * half, min(h + (lane & 31), j1 - 1 - j)};
+                const int jl = jh + (lane & 31), last = (auto_pairs ? min(ie, jl) : ie) - ib;
+                const uint32_t w = jl < j1 ? (uint32_t)min(max(last - t.io, 0), 16) : 0u;
+                float nbh;
+                uint32_t row_h;
+                column_state(h, nb, row, valid, nbh, row_h);
+                floatx16 c;
+                broadcast(c, nbh);
+                c = tile_q(rows_at(fa, g), f, c);
+                float q[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    q[r] = c[r];
+                float eh = __fmaf_rn(u * kTileErrN, nbh, e_rows);
+                // close pairs, where e is not small against q^, from FP32
+                // differences
+                uint32_t at, span;
+                if (!far_enough(q, eh, w)) {
+                    tile_diffs(a, job, t, ie - 1 - ib, q);
+                    eh = 0.0f;
+                }
+                tile_span(q, eh, k, at, span);
+                span = w ? span : 0u;
+                if (__builtin_amdgcn_ballot_w64(span > kMaxSpan) == 0)
+                    tile_count<M3>(a, job, s, k, q, eh, at, span, t, w, cnt);
+                else
+                    tile_cells<M3>(a, job, s, k, q, eh, t, w, cnt);
+            }
+            f.d[0] = f1[0];
+            f.d[2] = f1[1];
+            base = base1;
+            width = width1;
+        }
+        if (n_in) {
+            const uint32_t both = (n_in & 0xFFFFu) + (n_in >> 16);
+            if (j + 64 <= j1 && __builtin_amdgcn_ballot_w64(row != overflow) == 0) {
+                n_beyond += both;
+            } else {
+                lds_add(row + k.lanebase, valid ? 32u * (half ? n_in >> 16 : n_in & 0xFFFFu) : 0u);
+                cnt.one_slot_steps += both;
+            }
+        }
+        // work statistic: steps whose columns lie close to the rows
+        if (__builtin_amdgcn_ballot_w64(nb < q_small) != 0)
+            cnt.chord_steps += 2 * G;
+    }
+    cnt.beyond_steps += n_beyond;
+    cnt.beyond += n_beyond * 16u;
+}
+
+// PREC: 2 FP32 tiles, 0 FP32 chord (pruned launches), 1 FP64 vector; 3-D
+// distances: 3 FP32 tiles, 5 FP32 squared distance (pruned launches), 4 FP64
+// vector.  P: rows per lane (a wavefront covers P * 64 rows of a unit, for
+// tiles 2 P groups of 32).
 template <int PREC, bool LUT8, int P, bool PRUNE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_per_eu_of(PREC)))) void pairs_kernel(
     PairArgs a) {
     constexpr int kRowsPerWave = P * kWaveSize;
     extern __shared__ __align__(16) unsigned char smem[];
-    const Smem s = carve(smem, a);
+    const Smem s = carve<PREC == 2 || PREC == 3>(smem, a);
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = tid >> 6;
 
     const int hist_words = kWaves * (a.nslots + 1) * a.hist_copies;
-    for (int w = tid; w < hist_words; w += kBlock)
-        s.hist[w] = 0;
-    const int lut_bytes = a.lut_cells * (LUT8 ? 1 : 2);
-    const unsigned char *glut = reinterpret_cast<const unsigned char *>(a.lut);
-    // a wrapped table's unused piece holds the histograms and thresholds,
-    // which the copy must not overwrite
-    const uint32_t aux_lo = a.lut_direct ? (uint32_t)a.aux_off : (uint32_t)lut_bytes;
-    const uint32_t aux_n = (uint32_t)(hist_words * 4 + a.nedges * kEdgeLdsBytes);
-    for (int b = tid; b < lut_bytes; b += kBlock)
-        if ((uint32_t)b - aux_lo >= aux_n)
-            s.lut[b] = glut[b];
-    if (PREC >= 6) {
-        const int plut_bytes = a.plut_cells * (LUT8 ? 1 : 2);
-        for (int b = tid; b < plut_bytes; b += kBlock)
-            s.lut[a.plut_lds + b] = glut[a.plut_src + b];
-    }
+    // 16 bytes a lane (hist_words is a multiple of 16, the device table is
+    // padded to 16 bytes and so is its place in LDS): with one element a lane
+    // this copy took longer than the pairs of a small launch
+    for (int w = tid; w < hist_words / 4; w += kBlock)
+        reinterpret_cast<uint4 *>(s.hist)[w] = make_uint4(0, 0, 0, 0);
+    const int lut_words = (a.lut_cells * (LUT8 ? 1 : 2) + 15) / 16;
+    for (int w = tid; w < lut_words; w += kBlock)
+        reinterpret_cast<uint4 *>(s.lut)[w] = reinterpret_cast<const uint4 *>(a.lut)[w];
     for (int e = tid; e < a.nedges; e += kBlock) {
         s.D[e] = a.D[e];
-        s.E[e] = a.E[e];
         s.qband[e] = make_float2(a.qlo[e], a.qhi[e]);
-        s.pband[e] = PREC >= 6 ? make_float2(a.qlo[a.nedges + e], a.qhi[a.nedges + e]) : make_float2(0.0f, 0.0f);
-        s.erad[e] = a.erad ? a.erad[e] : 0.0;
+        if (PREC == 2 || PREC == 3) {
+            s.edges[e] = a.tile_edges[e];
+        } else {
+            s.E[e] = a.E[e];
+            s.erad[e] = a.erad ? a.erad[e] : 0.0;
+        }
     }
+    if (PREC == 2 || PREC == 3)
+        for (int e = tid; e < a.nslots; e += kBlock)
+            s.slots[e] = a.tile_slots[e];
     __syncthreads();
 
     Consts k;
     k.shift = (uint32_t)a.lut_shift;
-    k.wbits = (uint32_t)a.lut_wrap_bits;
-    k.qfloor = a.q_floor;
     k.clo = to_vgpr((uint32_t)a.lut_lo);
     k.chi = to_vgpr((uint32_t)a.lut_hi);
     k.lutbias = s.lut_addr - (uint32_t)a.lut_lo * (LUT8 ? 1u : 2u);
     k.rowstep = (uint32_t)a.hist_copies * 4u;
+    k.rowlog = 31u - (uint32_t)__builtin_clz(k.rowstep);
     k.flag = to_vgpr(Code<LUT8>::flag);
     k.beyond = to_vgpr(a.beyond_key);
-    k.pbeyond = a.p_beyond;
-    k.pshift = to_vgpr((uint32_t)a.plut_shift);
-    k.pclo = to_vgpr((uint32_t)a.plut_lo);
-    k.pchi = to_vgpr((uint32_t)a.plut_hi);
-    k.pbias = to_vgpr(s.plut_addr - (uint32_t)a.plut_lo * (LUT8 ? 1u : 2u));
-    k.qdot = __float_as_uint(a.q_dot);
     k.lanebase = s.hist_addr +
                  (uint32_t)((wave * (a.nslots + 1) * a.hist_copies + (lane & (a.hist_copies - 1))) * 4);
     Counters cnt;
@@ -1331,6 +1828,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
         const int u = (int)(item / kWaves);
         const int part = (int)(item % kWaves);
         const Unit un = load_uniform(a.units + u);
+        constexpr bool TILES = PREC == 2 || PREC == 3;
+        const cargs_p args = (cargs_p)__builtin_amdgcn_kernarg_segment_ptr();
+        const cjob_p job = a.jobs ? (cjob_p)(a.jobs + un.job) : &args->job0;
         const JobDev jb = a.jobs ? load_uniform(a.jobs + un.job) : a.job0;
         const int ib = un.i0 + part * kRowsPerWave;
         if (ib < un.i1) {
@@ -1343,16 +1843,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
             const int ie = min(un.i1, ib + kRowsPerWave);
             const int rlo = max(un.row_lo, ib);
             const bool masked = (ie - ib < kRowsPerWave) || (jb.auto_pairs && un.j0 < ie) || rlo > ib;
-            if (PREC == 0 || PREC == 3 || PREC == 5 || PREC == 6 || PREC == 7) {
+            if (PREC == 2 || PREC == 3) {
+                rows_tiles<2 * P, PREC == 3>(args, job, s, k, ib, ie, un.j0, un.j1, lane, cnt);
+            } else if (PREC == 0 || PREC == 5) {
                 constexpr bool M3 = PREC == 5;
-                constexpr bool DIRECT = PREC == 3 || PREC == 7;
-                // with pruning, the blocks left to evaluate lie across edges,
-                // where the dot product rarely settles a step: chord only
-                constexpr bool DOT = PREC >= 6 && !PRUNE;
                 if (masked)
-                    rows_fp32<LUT8, true, P, DIRECT, PRUNE, M3, DOT>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
+                    rows_fp32<LUT8, true, P, PRUNE, M3>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
                 else
-                    rows_fp32<LUT8, false, P, DIRECT, PRUNE, M3, DOT>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
+                    rows_fp32<LUT8, false, P, PRUNE, M3>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
             } else {
                 constexpr bool M3 = PREC == 4;
                 if (masked)
@@ -1378,9 +1876,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
             flush_wave(a, s, jb.hist, r0, r1, wave, lane, (int)(item & (kGlobalCopies - 1)));
         }
     }
-    // column copies into LDS still in flight land before the wavefront ends
-    if (PREC >= 6 && !PRUNE)
-        __builtin_amdgcn_s_waitcnt(0x0F70);
     uint32_t f = wave_sum(cnt.flag);
     uint32_t x = wave_sum(cnt.exact);
     if (lane == 0) {
@@ -1516,19 +2011,12 @@ int grid_for(int n_units, int lds, int blocks_per_cu) {
     return (int)g;
 }
 
-template <int PR, bool B8>
-void launch_pairs(int P, bool prune, int grid, int lds, hipStream_t st, const PairArgs &a) {
-    if (prune) {
-        if (P == 2)
-            hipLaunchKernelGGL((pairs_kernel<PR, B8, 2, true>), dim3(grid), dim3(kBlock), lds, st, a);
-        else
-            hipLaunchKernelGGL((pairs_kernel<PR, B8, 4, true>), dim3(grid), dim3(kBlock), lds, st, a);
-    } else {
-        if (P == 2)
-            hipLaunchKernelGGL((pairs_kernel<PR, B8, 2, false>), dim3(grid), dim3(kBlock), lds, st, a);
-        else
-            hipLaunchKernelGGL((pairs_kernel<PR, B8, 4, false>), dim3(grid), dim3(kBlock), lds, st, a);
-    }
+template <int PR, bool B8, bool PRUNE>
+void launch_pairs(int P, int grid, int lds, hipStream_t st, const PairArgs &a) {
+    if (P == 2)
+        hipLaunchKernelGGL((pairs_kernel<PR, B8, 2, PRUNE>), dim3(grid), dim3(kBlock), lds, st, a);
+    else
+        hipLaunchKernelGGL((pairs_kernel<PR, B8, 4, PRUNE>), dim3(grid), dim3(kBlock), lds, st, a);
 }
 
 
@@ -1537,10 +2025,8 @@ void launch_pairs(int P, bool prune, int grid, int lds, hipStream_t st, const Pa
 extern "C" int tpcf_launch_pairs(const PairArgs *args, int precision, void *stream) {
     if (args->n_units <= 0)
         return 0;
-    const int lds = args->plut_cells > 0 && precision == 0 && args->metric == 0
-                        ? args->stage_lds + kStageBytes
-                        : lds_bytes(args->nslots, args->hist_copies, args->lut_cells, args->lut_entry_bytes,
-                                    args->nedges, args->lut_direct ? args->aux_off : -1);
+    const int lds = lds_bytes(args->nslots, args->hist_copies, args->lut_cells, args->lut_entry_bytes, args->nedges) +
+                    (args->tile_slots ? tile_lds_bytes(args->nslots) : 0);
     const int grid = grid_for(args->n_units, lds, args->blocks_per_cu);
     hipStream_t st = (hipStream_t)stream;
     const bool b8 = args->lut_entry_bytes == 1;
@@ -1548,40 +2034,26 @@ extern "C" int tpcf_launch_pairs(const PairArgs *args, int precision, void *stre
     if (P != 2 && P != 4)
         return (int)hipErrorInvalidValue;
     const bool prune = args->prune != 0;
-    if (args->metric == 1) {
-        if (precision == 0 && b8)
-            launch_pairs<5, true>(P, prune, grid, lds, st, *args);
-        else if (precision == 0)
-            launch_pairs<5, false>(P, prune, grid, lds, st, *args);
-        else if (precision == 1 && b8)
-            launch_pairs<4, true>(P, prune, grid, lds, st, *args);
-        else if (precision == 1)
-            launch_pairs<4, false>(P, prune, grid, lds, st, *args);
-        else
-            return (int)hipErrorInvalidValue;
-        return (int)hipGetLastError();
-    }
-    if (precision == 0 && args->plut_cells > 0) {
-        if (b8 && args->lut_direct)
-            launch_pairs<7, true>(P, prune, grid, lds, st, *args);
-        else if (b8)
-            launch_pairs<6, true>(P, prune, grid, lds, st, *args);
-        else
-            launch_pairs<6, false>(P, prune, grid, lds, st, *args);
-    } else if (precision == 0) {
-        if (b8 && args->lut_direct)
-            launch_pairs<3, true>(P, prune, grid, lds, st, *args);
-        else if (b8)
-            launch_pairs<0, true>(P, prune, grid, lds, st, *args);
-        else
-            launch_pairs<0, false>(P, prune, grid, lds, st, *args);
-    } else if (precision == 1) {
-        if (b8)
-            launch_pairs<1, true>(P, prune, grid, lds, st, *args);
-        else
-            launch_pairs<1, false>(P, prune, grid, lds, st, *args);
-    } else {
+    if (precision != 0 && precision != 1)
         return (int)hipErrorInvalidValue;
+    if (args->metric == 1) {
+        if (precision == 0 && prune)
+            b8 ? launch_pairs<5, true, true>(P, grid, lds, st, *args) : launch_pairs<5, false, true>(P, grid, lds, st, *args);
+        else if (precision == 0)
+            launch_pairs<3, false, false>(P, grid, lds, st, *args);
+        else if (prune)
+            b8 ? launch_pairs<4, true, true>(P, grid, lds, st, *args) : launch_pairs<4, false, true>(P, grid, lds, st, *args);
+        else
+            b8 ? launch_pairs<4, true, false>(P, grid, lds, st, *args) : launch_pairs<4, false, false>(P, grid, lds, st, *args);
+    } else {
+        if (precision == 0 && prune)
+            b8 ? launch_pairs<0, true, true>(P, grid, lds, st, *args) : launch_pairs<0, false, true>(P, grid, lds, st, *args);
+        else if (precision == 0)
+            launch_pairs<2, false, false>(P, grid, lds, st, *args);
+        else if (prune)
+            b8 ? launch_pairs<1, true, true>(P, grid, lds, st, *args) : launch_pairs<1, false, true>(P, grid, lds, st, *args);
+        else
+            b8 ? launch_pairs<1, true, false>(P, grid, lds, st, *args) : launch_pairs<1, false, false>(P, grid, lds, st, *args);
     }
     return (int)hipGetLastError();
 }

@@ -1,0 +1,134 @@
+"""GPU parity of the FP32 tiles at the edges of their shapes (needs an MI355X).
+
+A wavefront takes 128 or 256 rows in groups of 32 against 64 columns at a
+time, in two tiles of 32; a lane holds one column against 16 consecutive rows.
+Row and column counts one below, at and one above each of these, and row
+ranges that start anywhere, must count every pair once, in the slot of the
+exact rule.  Counts are integers: they equal the oracle's, no tolerance.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1204_6630_amd as tp
+import synthcat
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1025]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = tp.Context(0)
+    yield c
+    c.close()
+
+
+def _stored(ctx, cat, xyz):
+    o = ctx.catalog_order(cat)
+    return tuple(np.ascontiguousarray(c[o]) for c in xyz)
+
+
+@pytest.mark.parametrize("rows", [2, 4])
+@pytest.mark.parametrize("n", SIZES)
+def test_ragged_sky_catalogs(ctx, n, rows):
+    """n rows against n + 31 columns on a 10 x 10 deg patch, 12 log bins to
+    the patch's size: near and far tiles, masked diagonals and tails."""
+    g = synthcat.rng_for(96, n)
+    fp = (20.0, 30.0, -5.0, 5.0)
+    d, r = synthcat.uniform_patch(n, fp, g), synthcat.uniform_patch(n + 31, fp, g)
+    e = synthcat.log_edges(0.01, 8.0, 12)
+    xd, xr = oracle.radec_to_xyz(*d), oracle.radec_to_xyz(*r)
+    a, b = ctx.upload_catalog(*d), ctx.upload_catalog(*r)
+    try:
+        ctx.set_tuning(rows_per_lane=rows)
+        assert np.array_equal(ctx.count(tp.DD, a, e), oracle.count(oracle.DD, xd, e))
+        assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b), oracle.count(oracle.DR, xd, e, b_xyz=xr))
+        if n > 2:
+            sa = _stored(ctx, a, xd)
+            lo, hi = n // 3, n - n // 5
+            assert np.array_equal(ctx.count(tp.DD, a, e, row_begin=lo, row_end=hi),
+                                  oracle.count(oracle.DD, sa, e, row_begin=lo, row_end=hi))
+    finally:
+        ctx.set_tuning()
+        ctx.release_catalog(a)
+        ctx.release_catalog(b)
+
+
+@pytest.mark.parametrize("n", [33, 257, 1025])
+@pytest.mark.parametrize("scale", [1e-30, 1.0, 3e9])
+def test_ragged_boxes_of_any_scale(ctx, n, scale):
+    """3-D points and edges times a scale factor: the tiles bring coordinates
+    into f16's range by a power of two of their own.  The box lies off the
+    origin, so the rows' mean carries the distances."""
+    g = synthcat.rng_for(96, 5000 + n)
+    p = synthcat.box_uniform(n, 100.0, g, origin=37.0)
+    q = synthcat.box_uniform(2 * n + 1, 100.0, g, origin=37.0)
+    e = np.concatenate([[0.0], np.geomspace(0.5, 120.0, 17)]) * scale
+    x, y = tuple(c * scale for c in p.xyz()), tuple(c * scale for c in q.xyz())
+    a, b = ctx.upload_catalog_3d(*x), ctx.upload_catalog_3d(*y)
+    try:
+        assert np.array_equal(ctx.count(tp.DD, a, e), oracle.count3d(oracle.DD, x, e))
+        assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b), oracle.count3d(oracle.DR, x, e, b_xyz=y))
+    finally:
+        ctx.release_catalog(a)
+        ctx.release_catalog(b)
+
+
+@pytest.mark.parametrize("nbins", [1, 7, 46, 125, 126, 200, 256])
+def test_bins_finer_than_a_tile(ctx, nbins):
+    """Bins from wider than a tile to far narrower (one slot, one edge, a few
+    edges and lookups), linear so that far bins are the narrow ones, on rows
+    in upload order (attached: no Morton order, tiles spread over the sky)
+    and in Morton order."""
+    import torch
+    g = synthcat.rng_for(96, 9000 + nbins)
+    d, r = synthcat.uniform_patch(1500, synthcat.OCTANT, g), synthcat.uniform_patch(1700, synthcat.OCTANT, g)
+    e = np.linspace(1e-3, 75.0, nbins + 1)
+    xd, xr = oracle.radec_to_xyz(*d), oracle.radec_to_xyz(*r)
+    ref = oracle.count(oracle.DR, xd, e, b_xyz=xr)
+    a, b = ctx.upload_catalog(*d), ctx.upload_catalog(*r)
+    t = torch.from_numpy(np.stack(xd)).cuda()
+    c = ctx.attach_catalog(t)
+    try:
+        assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b), ref)
+        assert np.array_equal(ctx.count(tp.DR, c, e, cat_b=b), ref)
+    finally:
+        for k in (a, b, c):
+            ctx.release_catalog(k)
+
+
+def test_pairs_at_every_edge_and_at_zero(ctx):
+    """Columns at theta = e_k (1 +- 10^-s), s = 2..12, from rows in a tight
+    clump, coincident and antipodal points among them: the matrix-core
+    distances are off by up to a few 1e-7 of the distance, so most of these
+    pairs lie within their error of an edge and are settled by differences
+    or the FP64 rule."""
+    g = synthcat.rng_for(96, 1)
+    e = synthcat.log_edges(0.05, 150.0, 14)
+    c = np.array([0.6, 0.64, np.sqrt(1 - 0.36 - 0.4096)])
+    t1 = np.cross(c, [0.0, 0.0, 1.0])
+    t1 /= np.linalg.norm(t1)
+    t2 = np.cross(c, t1)
+    rows = c[None, :] + g.normal(0.0, 1e-9, size=(300, 3))
+    rows /= np.linalg.norm(rows, axis=1)[:, None]
+    cols = [c, -c]
+    for k in e:
+        for s in range(2, 13):
+            for sign in (1.0, -1.0):
+                th, ph = np.radians(k * (1.0 + sign * 10.0 ** -s)), g.uniform(0, 2 * np.pi)
+                cols.append(np.cos(th) * c + np.sin(th) * (np.cos(ph) * t1 + np.sin(ph) * t2))
+    cols = np.array(cols)
+    cols /= np.linalg.norm(cols, axis=1)[:, None]
+    a, b = rows.T.copy(), cols.T.copy()
+    ca, cb = ctx.upload_catalog_xyz(*a), ctx.upload_catalog_xyz(*b)
+    try:
+        ctx.stats(reset=True)
+        assert np.array_equal(ctx.count(tp.DR, ca, e, cat_b=cb), oracle.count(oracle.DR, a, e, b_xyz=b))
+        assert ctx.stats(reset=True).exact > 0
+        assert np.array_equal(ctx.count(tp.DR, cb, e, cat_b=ca), oracle.count(oracle.DR, b, e, b_xyz=a))
+    finally:
+        ctx.release_catalog(ca)
+        ctx.release_catalog(cb)
