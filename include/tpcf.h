@@ -283,9 +283,9 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
  * tpcf_poll sets *done = 1 and writes nbins+2 slots to out_u64 (may be NULL)
  * when the job has finished, and then retires the id; *done = 0 otherwise.
  * tpcf_wait blocks until the job finishes, then acts like tpcf_poll.
- * tpcf_cancel sets a flag in host memory that the kernel reads before every
- * work unit; the job's poll/wait then returns TPCF_E_CANCELLED and retires
- * it.  A catalog cannot be released while an unretired job uses it. */
+ * tpcf_cancel sets a flag in host memory that every wavefront of the kernel
+ * reads at its first work unit and every few million pairs from then on; the
+ * job's poll/wait then returns TPCF_E_CANCELLED and retires it.  A catalog cannot be released while an unretired job uses it. */
 int tpcf_submit(tpcf_ctx *ctx, const tpcf_job_desc *job, int64_t *out_job);
 int tpcf_poll(tpcf_ctx *ctx, int64_t job, uint64_t *out_u64, int *done);
 int tpcf_wait(tpcf_ctx *ctx, int64_t job, uint64_t *out_u64);
@@ -294,13 +294,14 @@ int tpcf_cancel(tpcf_ctx *ctx, int64_t job);
 /* Launch shape of later launches (set by the autotuner; defaults are fine).
  * Every field 0 takes the default.
  * rows_per_lane   2 or 4: a wavefront covers 64 times as many rows (default
- *                 4; unpruned FP32 launches of fewer than 2^29 pairs: 2);
+ *                 4; unpruned FP32 launches of fewer than 2^22 pairs: 2);
  * hist_copies     LDS histogram copies per wavefront, 4, 8, 16 or 32
  *                 (default 16); a value above what the slot count allows
  *                 (32 up to 46 slots, 16 up to 94, 8 up to 190, else 4) is
  *                 lowered;
  * max_cols        largest column range of a work unit, multiple of 256 in
- *                 [256, 65536] (default 4096);
+ *                 [256, 65536] (default 2048, pruned launches 4096; single
+ *                 requests round it down to a power of two);
  * blocks_per_cu   grid size per compute unit, <= 64 (default: the blocks
  *                 that fit at once; wavefronts take work from a queue);
  * lut_bytes       largest cell table held in LDS, 4096..33792 bytes

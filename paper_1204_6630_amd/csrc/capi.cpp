@@ -68,16 +68,19 @@ struct Tuning {
 };
 
 // Rows per lane of a launch over `pairs` pairs: 4, but 2 for FP32 tiles below
-// 2^29 pairs, where items of 256 rows are too few to fill the 4096 wavefronts
-// of the device (DD of 1e3 points 251 -> 128 us, DD+DR+RR of 1e4 x 1e4 1160
-// -> 860 us; 1e5 x 2e5 in 64 regions 7.4 ms either way).
+// 2^22 pairs, where one item of 256 rows outlasts the rest of the launch (DD
+// of 1e3 points 75 -> 64 us; DD+DR+RR of 1e4 x 1e4 the other way, 488
+// against 624 us).
 int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs) {
     if (t.rows_per_lane)
         return t.rows_per_lane;
-    return precision == TPCF_FP32_CHORD && !t.prune && pairs < ((uint64_t)1 << 29) ? 2 : 4;
+    return precision == TPCF_FP32_CHORD && !t.prune && pairs < ((uint64_t)1 << 22) ? 2 : 4;
 }
 
-int max_cols_of(const Tuning &t) { return t.max_cols ? t.max_cols : 4096; }
+// Largest column chunk: 2048, and 4096 with pruning, whose items prepare more
+// (1e6 x 2e6: 4096 columns 228.9 ms, 2048 229.1, 1024 233, 512 245; a 3-D box
+// of 5e5 x 1e6 55.4, 54.9, 54.2, 57.0; pruned 5e5 x 1e6: 4096 95.7, 1024 98.0).
+int max_cols_of(const Tuning &t) { return t.max_cols ? t.max_cols : t.prune ? 4096 : 2048; }
 
 // Device memory of one context, with an optional budget on the total.
 struct MemAccount {
@@ -191,7 +194,10 @@ struct Request {
     int64_t rb = 0, re = 0;
     int nbins = 0, precision = 0;
     Compiled *cp = nullptr;
-    Plan *plan = nullptr;
+    Plan *plan = nullptr;    // a unit list (batches, jackknife regions), else:
+    UnitGrid grid{};
+    int rows = 4;            // rows per lane
+    int32_t n_units = 0;
     uint64_t pairs = 0;
     int metric = 0;
     std::string cache_key;   // RR requests: key of the result cache
@@ -260,8 +266,8 @@ int init_workspace(tpcf_ctx *ctx, Workspace &w, hipStream_t borrowed) {
         HIP_TRY(hipStreamCreateWithFlags(&w.stream, hipStreamNonBlocking));
         w.own = true;
     }
-    TRY(w.stats.ensure(ctx->mem, sizeof(unsigned long long) * kStats));
-    HIP_TRY((hipError_t)tpcf_launch_zero_u64((unsigned long long *)w.stats.p, kStats, w.stream));
+    TRY(w.stats.ensure(ctx->mem, sizeof(unsigned long long) * kStatWords));
+    HIP_TRY((hipError_t)tpcf_launch_zero_u64((unsigned long long *)w.stats.p, kStatWords, w.stream));
     return TPCF_OK;
 }
 
@@ -651,25 +657,6 @@ int get_compiled(tpcf_ctx *ctx, const double *edges, int nbins, int precision, d
     return TPCF_OK;
 }
 
-// Column chunk width of a plan: aim for >= ~4096 units, within [64,
-// max_cols] (multiples of 256 above 256), but wide enough that the unit list
-// stays below kMaxUnits (about 0.8 GB of units; catalogs of 1e8 points would
-// otherwise need tens of GB of them).
-constexpr double kMaxUnits = 16777216.0;
-
-int64_t chunk_width(uint64_t pairs, int64_t T, int64_t max_cols, double max_units = kMaxUnits) {
-    int64_t bj = (int64_t)((double)pairs / 4096.0 / (double)T);
-    bj = bj > 256 ? (bj + 255) / 256 * 256 : (bj + 63) / 64 * 64;
-    if (bj > max_cols)
-        bj = max_cols;
-    if (bj < 64)
-        bj = 64;
-    const double need = (double)pairs / (double)T / max_units;   // columns per unit for max_units units
-    if ((double)bj < need)
-        bj = ((int64_t)need + 256) / 256 * 256;
-    return bj;
-}
-
 // Work units.  DR: every row tile against column chunks of the B catalog.
 // DD/RR: every row tile [i0, i1) against j in [i0, n): one masked unit for the
 // diagonal block [i0, i0 + T), then unmasked chunks from i0 + T on.
@@ -688,24 +675,15 @@ Unit mk_unit(int64_t i0, int64_t i1, int64_t j0, int64_t j1, int64_t row_lo, int
     return u;
 }
 
-// Pairs of a request.
-uint64_t pairs_of(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re) {
-    if (!auto_pairs)
-        return (uint64_t)(re - rb) * (uint64_t)nb;
-    // sum over i in [rb, re) of (na - 1 - i)
-    const int64_t cnt = re - rb;
-    return (uint64_t)cnt * (uint64_t)(na - 1) - (uint64_t)((rb + re - 1) * cnt / 2);
-}
-
 Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows,
-               int64_t max_cols, double max_units = kMaxUnits) {
+               int64_t max_cols, uint64_t load = 0, double max_units = kMaxUnits) {
     Plan p;
     // 64 lanes x rows per lane rows per wavefront, four wavefronts per tile
     const int64_t T = (int64_t)kWaves * kWaveSize * rows;
     p.rows = rows;
     const uint64_t pairs = pairs_of(auto_pairs, na, nb, rb, re);
     p.pairs = pairs;
-    const int64_t bj = chunk_width(pairs, T, max_cols, max_units);
+    const int64_t bj = chunk_width(pairs, load ? load : pairs, T, max_cols, 512, max_units);
     // Row tiles start at rb (valid rows from row_lo = rb).
     // Column chunks lie on a common grid of multiples of bj, so units of
     // different row tiles cover the same column ranges; the list is ordered
@@ -718,8 +696,9 @@ Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, 
             const int64_t i1 = i0 + T < re ? i0 + T : re;
             const int32_t lo = (int32_t)(i0 > rb ? i0 : rb);
             const int64_t dend = i0 + T < na ? i0 + T : na;
-            if (lo + 1 < dend)
-                p.units.push_back(mk_unit(i0, i1, i0, dend, lo, i0, -1, -1));
+            // the diagonal block, in pieces where chunks are narrower than it
+            for (int64_t j = i0; j < dend && lo + 1 < dend; j += bj)
+                p.units.push_back(mk_unit(i0, i1, j, std::min(j + bj, dend), lo, j, -1, -1));
             int64_t j0 = dend;
             while (j0 < na) {
                 // up to the next multiple of bj; a short first piece joins the next chunk
@@ -760,7 +739,7 @@ Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int rows, int64_
     const int64_t T = (int64_t)kWaves * kWaveSize * rows;
     p.rows = rows;
     p.pairs = auto_pairs ? (uint64_t)na * (uint64_t)(na > 0 ? na - 1 : 0) / 2 : (uint64_t)na * (uint64_t)nb;
-    const int64_t bj = chunk_width(p.pairs, T, max_cols);
+    const int64_t bj = chunk_width(p.pairs, p.pairs, T, max_cols, 1024);
     const int nra = (int)sa.size() - 1;
     auto region_of = [](const std::vector<int64_t> &st, int64_t j) {
         return (int32_t)(std::upper_bound(st.begin(), st.end(), j) - st.begin() - 1);
@@ -807,14 +786,13 @@ Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int rows, int64_
     return p;
 }
 
-int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows, int precision,
+int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows, uint64_t load,
              Plan **out) {
-    if (!rows)
-        rows = rows_per_lane_of(ctx->tune, precision, pairs_of(auto_pairs, na, nb, rb, re));
     const int64_t max_cols = max_cols_of(ctx->tune);
     char buf[160];
-    snprintf(buf, sizeof buf, "%d:%lld:%lld:%lld:%lld:%lld:%lld", (int)auto_pairs, (long long)na,
-             (long long)nb, (long long)rb, (long long)re, (long long)rows, (long long)max_cols);
+    snprintf(buf, sizeof buf, "%d:%lld:%lld:%lld:%lld:%lld:%lld:%llu", (int)auto_pairs, (long long)na,
+             (long long)nb, (long long)rb, (long long)re, (long long)rows, (long long)max_cols,
+             (unsigned long long)load);
     auto it = ctx->plans.find(buf);
     if (it != ctx->plans.end()) {
         *out = it->second.get();
@@ -827,8 +805,7 @@ int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb,
             kv.second->dunits.release(ctx->mem);
         ctx->plans.clear();
     }
-    auto p = std::make_unique<Plan>(make_plan(auto_pairs, na, nb, rb, re, rows, max_cols));
-    TRY(upload_blocking(ctx->mem, p->dunits, p->units));
+    auto p = std::make_unique<Plan>(make_plan(auto_pairs, na, nb, rb, re, rows, max_cols, load));
     *out = p.get();
     ctx->plans[buf] = std::move(p);
     return TPCF_OK;
@@ -962,9 +939,11 @@ int validate(tpcf_ctx *ctx, const tpcf_job_desc &d, Request *r) {
 
 // Validate one request and get its tables and plan.  delta_override >= 0
 // compiles the FP32 band for that norm bound (shared by every job of a batch)
-// instead of the request's own; rows > 0 sets the rows per lane (likewise).
+// instead of the request's own; load > 0 makes the request part of a
+// launch over that many pairs with `rows` rows per lane: its units come as a
+// list.
 int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Request *r, bool regions = false,
-            int rows = 0) {
+            int rows = 0, uint64_t load = 0) {
     TRY(validate(ctx, d, r));
     const int64_t rb = r->rb, re = r->re;
     TRY(set_device(ctx));
@@ -981,10 +960,20 @@ int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Reques
         TRY(get_plan_regions(ctx, r->auto_pairs, r->cat_a, r->auto_pairs ? r->cat_a : r->cat_b, *r->A, *r->B,
                              d.precision, &r->plan));
         r->pairs = r->plan->pairs;
+        r->rows = r->plan->rows;
+        r->n_units = (int32_t)r->plan->units.size();
         return TPCF_OK;
     }
-    TRY(get_plan(ctx, r->auto_pairs, r->A->n, r->B->n, rb, re, rows, d.precision, &r->plan));
-    r->pairs = r->plan->pairs;
+    if (load) {
+        TRY(get_plan(ctx, r->auto_pairs, r->A->n, r->B->n, rb, re, rows, load, &r->plan));
+        r->pairs = r->plan->pairs;
+        r->n_units = (int32_t)r->plan->units.size();
+    } else {
+        r->pairs = pairs_of(r->auto_pairs, r->A->n, r->B->n, rb, re);
+        rows = rows_per_lane_of(ctx->tune, d.precision, r->pairs);
+        r->grid = make_grid(r->auto_pairs, r->A->n, r->B->n, rb, re, rows, max_cols_of(ctx->tune), &r->n_units);
+    }
+    r->rows = rows;
     if (d.kind == TPCF_RR)
         r->cache_key = cache_key(d.cat_a, d.bin_edges_deg, d.nbins, d.precision, rb, re);
     return TPCF_OK;
@@ -1119,12 +1108,13 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
     TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * ((size_t)kGlobalCopies * kMaxSlots + 1)));
     unsigned long long *copies = (unsigned long long *)w.copies.p;
     HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + 1, w.stream));
-    PairArgs a = args_of(ctx, *r.cp, r.nbins, r.plan->rows, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
+    PairArgs a = args_of(ctx, *r.cp, r.nbins, r.rows, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
     a.jobs = nullptr;
     a.job0 = job_of(r, copies, cancel);
     a.job0.touch = touch;
-    a.units = (const Unit *)r.plan->dunits.p;
-    a.n_units = (int32_t)r.plan->units.size();
+    a.units = r.plan ? (const Unit *)r.plan->dunits.p : nullptr;
+    a.grid = r.grid;
+    a.n_units = r.n_units;
     a.queue = (unsigned int *)(copies + (size_t)kGlobalCopies * nslots);
     hipEvent_t e0, e1;
     if (a.n_units > 0)
@@ -1578,7 +1568,7 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     // auto-pairs hold a few more units than the estimate), then checked
     Plan plan = make_plan(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re,
                           rows_per_lane_of(ctx->tune, r.precision, pairs_of(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re)),
-                          max_cols_of(ctx->tune), 0.5 * (double)max_units);
+                          max_cols_of(ctx->tune), 0, 0.5 * (double)max_units);
     if (plan.units.size() > max_units) {
         char buf[200];
         snprintf(buf, sizeof buf, "the request needs %zu work units; the fixed work area (%zu MiB) holds %zu",
@@ -1664,7 +1654,7 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
     }
     const int rows = rows_per_lane_of(ctx->tune, jobs[0].precision, pairs);
     for (int32_t k = 0; k < njobs; ++k) {
-        TRY(prepare(ctx, jobs[k], delta, &reqs[k], false, rows));
+        TRY(prepare(ctx, jobs[k], delta, &reqs[k], false, rows, pairs));
         if (reqs[k].metric != reqs[0].metric)
             return fail(TPCF_E_INVALID, "a batch cannot mix sky and 3-D catalogs");
     }
@@ -1996,12 +1986,13 @@ int tpcf_stats(tpcf_ctx *ctx, tpcf_counters *out, int reset) {
     for (auto &w : ctx->pool)
         ws.push_back(&w);
     for (Workspace *w : ws) {
-        unsigned long long h[kStats] = {};
+        unsigned long long h[kStatWords] = {};
         HIP_TRY(hipMemcpy(h, w->stats.p, sizeof h, hipMemcpyDeviceToHost));
-        for (int i = 0; i < kStats; ++i)
-            tot[i] += h[i];
+        for (int c = 0; c < kStatCopies; ++c)
+            for (int i = 0; i < kStats; ++i)
+                tot[i] += h[c * kStatStride + i];
         if (reset)
-            HIP_TRY((hipError_t)tpcf_launch_zero_u64((unsigned long long *)w->stats.p, kStats, w->stream));
+            HIP_TRY((hipError_t)tpcf_launch_zero_u64((unsigned long long *)w->stats.p, kStatWords, w->stream));
     }
     if (reset)
         TRY(sync_all(ctx));

@@ -6,12 +6,9 @@
 #include <hip/hip_vector_types.h>
 #include <stdint.h>
 
-namespace tpcf {
+#include "units.h"
 
-// Threads per block and the i-points each lane keeps in registers.
-constexpr int kWaves = 4;
-constexpr int kWaveSize = 64;
-constexpr int kBlock = kWaves * kWaveSize;
+namespace tpcf {
 
 // LDS budget of the cell table; entries are one byte when every slot and
 // edge index fits in 7 bits, else two bytes.
@@ -42,6 +39,10 @@ constexpr float kTileErr0 = 16.0f;
 constexpr float kTileFar = 1.0f / 1024.0f;
 // Work statistics words of a launch (see PairArgs::stats).
 constexpr int kStats = 9;
+// Their copies in device memory, spread over lines of 128 bytes and summed
+// when read.
+constexpr int kStatCopies = 32, kStatStride = 16;
+constexpr int kStatWords = kStatCopies * kStatStride;
 // Histogram copies in global memory (u64), indexed by work unit.
 constexpr int kGlobalCopies = 64;
 // Largest number of output slots (nbins <= 256 -> nbins + 2 slots).
@@ -99,7 +100,8 @@ struct JobDev {
 struct PairArgs {
     const JobDev *jobs;          // device job table, or null: every unit belongs to job0
     JobDev job0;                 // the job of a single-job launch (passed by value)
-    const Unit *units;           // device
+    const Unit *units;           // device, or null: units of `grid`
+    UnitGrid grid;
     int32_t n_units;
     // Work queue: item q is wavefront part q % kWaves of unit q / kWaves;
     // wavefronts take items in order with an atomic add on *queue (zeroed
@@ -157,7 +159,7 @@ struct PairArgs {
     int32_t rows_per_lane;       // 2 or 4: a unit spans kWaves * 64 * rows_per_lane rows
     int32_t blocks_per_cu;       // grid = CUs x this (0: the blocks that fit at once)
 
-    unsigned long long *stats;   // kStats words: [two-slot steps, flagged, exact, skipped
+    unsigned long long *stats;   // kStatCopies times kStats words: [two-slot steps, flagged, exact, skipped
                                  //  units, rare-path steps, steps counted beyond the last
                                  //  edge, one-slot steps, pairs binned by pruned blocks,
                                  //  angular FP32 steps that formed the chord]

@@ -1332,7 +1332,7 @@ __device__ __forceinline__ void tile_diffs(const TileArgs &a, cjob_p job, const 
         const int i = min(io + r, ilast);
         q[r] = diff_q(lane_load(p->ax32, t.i0, i), lane_load(p->ay32, t.i0, i), lane_load(p->az32, t.i0, i), xj, yj,
                       zj, a.q_exp2);
-        if ((r & 3) == 3)
+        if (r == 7)
             __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -1469,10 +1469,11 @@ __device__ __forceinline__ void stage_columns(const float *bx, const float *by, 
                                               int lane, uint32_t dst) {
     typedef __attribute__((address_space(3))) void *lds_p;
     typedef __attribute__((address_space(1))) void *glb_p;
-    const int jo = min(lane, last - j);
-    __builtin_amdgcn_global_load_lds((glb_p)(bx + j + jo), (lds_p)(uintptr_t)dst, 4, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_p)(by + j + jo), (lds_p)(uintptr_t)(dst + 256), 4, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_p)(bz + j + jo), (lds_p)(uintptr_t)(dst + 512), 4, 0, 0);
+    typedef const __attribute__((address_space(1))) char *gchar_p;
+    const uint32_t at = 4u * (uint32_t)min(lane, last - j);     // a scalar base and 32 bits a lane
+    __builtin_amdgcn_global_load_lds((glb_p)((gchar_p)(bx + j) + at), (lds_p)(uintptr_t)dst, 4, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_p)((gchar_p)(by + j) + at), (lds_p)(uintptr_t)(dst + 256), 4, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_p)((gchar_p)(bz + j) + at), (lds_p)(uintptr_t)(dst + 512), 4, 0, 0);
 }
 
 // nb and histogram row (~0 for a lane whose column does not exist) of the
@@ -1612,12 +1613,8 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
     const int nr = ie - ib;
     const uint32_t rows_ok = low_bits<G>(nr >> 5), rows_any = low_bits<G>((nr + 31) >> 5);
     uint32_t n_beyond = 0;
-    // columns up to the first row count nothing
-    if (auto_pairs && j0 <= ib)
-        j0 = ib + 1;
-    if (j0 >= j1)
-        return;
     const float *bx = job->bx32, *by = job->by32, *bz = job->bz32;
+    asm volatile("" : "+s"(bx), "+s"(by), "+s"(bz));    // (else reloaded from constant memory every pass)
     // the next 64 columns are on their way into LDS while these are used
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t stage = s.stage_addr + wave * (uint32_t)kStageWaveBytes;
@@ -1629,10 +1626,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
         // the two tiles of 32
         __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): the copy has landed
         float xn = col[0], yn = col[64], zn = col[128];
-        // read before the next copy overwrites them
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(xn), "+v"(yn), "+v"(zn) : : "memory");
-        if (j + 64 < j1)
-            stage_columns(bx, by, bz, j + 64, j1 - 1, lane, stage);
+        asm volatile("" : "+v"(xn), "+v"(yn), "+v"(zn));
         const float xs = __fmaf_rn(xn, S, -cx), ys = __fmaf_rn(yn, S, -cy), zs = __fmaf_rn(zn, S, -cz);
         const float nb = __fmaf_rn(zs, zs, __fmaf_rn(ys, ys, xs * xs));
         Frag f;
@@ -1650,6 +1644,12 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
             deal(__float_as_uint(nb - (sl.x + es)), base, base1);
             deal(valid ? wd : ~0u, width, width1);
         }
+        // the next copy starts here, when this one's columns and the tables
+        // have been read (the compiler waits for copies in flight before any
+        // LDS read) and the tiles of one pass are still to come
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(base), "+v"(width) : : "memory");
+        if (j + 64 < j1)
+            stage_columns(bx, by, bz, j + 64, j1 - 1, lane, stage);
         uint32_t n_in = 0;      // tiles in one slot: columns 0-31, columns 32-63 (<< 16)
 #pragma unroll 1
         for (int h = 0; h < 64; h += 32) {
@@ -1813,57 +1813,81 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
     Counters cnt;
 
     uint32_t n_skip = 0;
+    // Counts not flushed yet: where they go (the histogram and up to two
+    // regions of the last items) and how many pairs they hold.  A wavefront
+    // keeps them over its items until they go elsewhere or 2^31 pairs are
+    // near (one LDS count holds less than 2^32): flushing 42 slots with
+    // global atomics after every item, and one queue atomic per item, cost
+    // about 12 ns of the device an item.
+    unsigned long long *to = nullptr, *to_a = nullptr, *to_b = nullptr;
+    uint32_t held = 0;
+    const int copy = (int)((blockIdx.x * kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wave)) & (kGlobalCopies - 1));
+    auto flush = [&]() {
+        // pairs counted beyond the last edge go to this lane's copy of the
+        // overflow slot; then the wave's own LDS region is flushed (no block
+        // barrier needed)
+        if (cnt.beyond) {
+            lds_add(__umul24((uint32_t)(a.nslots - 1), k.rowstep) + k.lanebase, cnt.beyond);
+            cnt.beyond = 0;
+        }
+        flush_wave(a, s, to, to_a, to_b, wave, lane, copy);
+        held = 0;
+    };
     // Each wavefront takes work items in order from the queue, so the items in
     // flight are always a window of consecutive units that share their column
     // range (the plan orders units column chunk first) and the column data
-    // stays in L2.  Every wavefront leaves once the queue is exhausted.
-    const uint32_t n_items = (uint32_t)a.n_units * kWaves;
-    for (;;) {
-        uint32_t item = 0;
-        if (lane == 0)
-            item = atomicAdd(a.queue, 1u);
-        item = __builtin_amdgcn_readfirstlane(item);
-        if (item >= n_items)
-            break;
-        const int u = (int)(item / kWaves);
-        const int part = (int)(item % kWaves);
-        const Unit un = load_uniform(a.units + u);
-        constexpr bool TILES = PREC == 2 || PREC == 3;
+    // stays in L2.  While many are left it takes several at once: an eighth of
+    // its share of what was left when it last looked, at most kWaves (a whole
+    // unit's parts).  Every wavefront leaves once the queue is exhausted.
+    const uint32_t n_items = (uint32_t)a.n_units * kWaves, n_waves = gridDim.x * kWaves;
+    uint32_t next = 0, end = 0, unlooked = 1u << 21;    // (a cancellable launch holds one job)
+    bool gone = false;
+    for (;; ++next) {
+        if (next == end) {
+            const uint32_t left = n_items - min(end, n_items);
+            const uint32_t take = min(max(left / (8u * n_waves), 1u), (uint32_t)kWaves);
+            if (lane == 0)
+                next = atomicAdd(a.queue, take);
+            next = __builtin_amdgcn_readfirstlane(next);
+            if (next >= n_items)
+                break;
+            end = min(next + take, n_items);
+        }
+        const int u = (int)(next / kWaves);
+        const int part = (int)(next % kWaves);
+        Unit un;
+        if (a.units) {
+            un = load_uniform(a.units + u);
+        } else {
+            un.job = 0;
+            un.reg_a = un.reg_b = -1;
+            if (!grid_unit(a.grid, (uint32_t)u, &un.i0, &un.i1, &un.j0, &un.j1))
+                continue;
+        }
         const cargs_p args = (cargs_p)__builtin_amdgcn_kernarg_segment_ptr();
         const cjob_p job = a.jobs ? (cjob_p)(a.jobs + un.job) : &args->job0;
         const JobDev jb = a.jobs ? load_uniform(a.jobs + un.job) : a.job0;
         const int ib = un.i0 + part * kRowsPerWave;
-        if (ib < un.i1) {
-            // a cancelled job skips its remaining units (the flag lives in host memory)
-            if (jb.cancel && __builtin_amdgcn_readfirstlane(
-                                 __hip_atomic_load(jb.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))) {
-                ++n_skip;
-                continue;
-            }
+        // (auto-pairs: columns up to the first row count nothing)
+        const int jb0 = jb.auto_pairs ? max(un.j0, ib + 1) : un.j0;
+        if (ib < un.i1 && jb0 < un.j1) {
             const int ie = min(un.i1, ib + kRowsPerWave);
-            const int rlo = max(un.row_lo, ib);
-            const bool masked = (ie - ib < kRowsPerWave) || (jb.auto_pairs && un.j0 < ie) || rlo > ib;
-            if (PREC == 2 || PREC == 3) {
-                rows_tiles<2 * P, PREC == 3>(args, job, s, k, ib, ie, un.j0, un.j1, lane, cnt);
-            } else if (PREC == 0 || PREC == 5) {
-                constexpr bool M3 = PREC == 5;
-                if (masked)
-                    rows_fp32<LUT8, true, P, PRUNE, M3>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
-                else
-                    rows_fp32<LUT8, false, P, PRUNE, M3>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
-            } else {
-                constexpr bool M3 = PREC == 4;
-                if (masked)
-                    rows_fp64<LUT8, true, P, PRUNE, M3>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
-                else
-                    rows_fp64<LUT8, false, P, PRUNE, M3>(a, jb, s, k, ib, ie, un.j0, un.j1, lane, cnt);
-            }
-            // pairs counted beyond the last edge go to this lane's copy of the
-            // overflow slot; then the wave's own LDS region is flushed (no
-            // block barrier needed)
-            if (cnt.beyond) {
-                lds_add(__umul24((uint32_t)(a.nslots - 1), k.rowstep) + k.lanebase, cnt.beyond);
-                cnt.beyond = 0;
+            const uint64_t pairs = (uint64_t)(ie - ib) * (uint64_t)(un.j1 - un.j0);
+            // a cancelled job skips its remaining units; the flag lives in
+            // host memory, so a wavefront looks at it every 2^21 pairs (about
+            // 0.6 ms of its work): at every item, twelve jobs of up to 3e10
+            // pairs took 60 instead of 38 ms
+            if (jb.cancel) {
+                unlooked += (uint32_t)min(pairs, (uint64_t)1 << 21);
+                if (unlooked >= 1u << 21) {
+                    unlooked = 0;
+                    gone = __builtin_amdgcn_readfirstlane(
+                               __hip_atomic_load(jb.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) != 0;
+                }
+                if (gone) {
+                    ++n_skip;
+                    continue;
+                }
             }
             unsigned long long *r0 = nullptr, *r1 = nullptr;
             if (jb.touch) {
@@ -1873,31 +1897,56 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
                 if (un.reg_b >= 0 && un.reg_b != un.reg_a)
                     r1 = jb.touch + (size_t)un.reg_b * per_region;
             }
-            flush_wave(a, s, jb.hist, r0, r1, wave, lane, (int)(item & (kGlobalCopies - 1)));
+            // (the plan keeps a unit below 2^32 pairs; one near that is
+            // flushed on its own)
+            if (held && (to != jb.hist || to_a != r0 || to_b != r1 || held + pairs >= 0x80000000ull))
+                flush();
+            to = jb.hist;
+            to_a = r0;
+            to_b = r1;
+            held = (uint32_t)min((uint64_t)held + pairs, (uint64_t)0xFFFFFFFFu);
+            // columns [jb0, jm) need a test per pair: all of them when the
+            // rows do not fill the wavefront, for auto-pairs those up to the
+            // last row
+            const int jm = ie - ib < kRowsPerWave ? un.j1 : jb.auto_pairs ? min(max(ie, jb0), un.j1) : jb0;
+            if (PREC == 2 || PREC == 3) {
+                rows_tiles<2 * P, PREC == 3>(args, job, s, k, ib, ie, jb0, un.j1, lane, cnt);
+            } else if (PREC == 0 || PREC == 5) {
+                constexpr bool M3 = PREC == 5;
+                if (jb0 < jm)
+                    rows_fp32<LUT8, true, P, PRUNE, M3>(a, jb, s, k, ib, ie, jb0, jm, lane, cnt);
+                if (jm < un.j1)
+                    rows_fp32<LUT8, false, P, PRUNE, M3>(a, jb, s, k, ib, ie, jm, un.j1, lane, cnt);
+            } else {
+                constexpr bool M3 = PREC == 4;
+                if (jb0 < jm)
+                    rows_fp64<LUT8, true, P, PRUNE, M3>(a, jb, s, k, ib, ie, jb0, jm, lane, cnt);
+                if (jm < un.j1)
+                    rows_fp64<LUT8, false, P, PRUNE, M3>(a, jb, s, k, ib, ie, jm, un.j1, lane, cnt);
+            }
         }
     }
-    uint32_t f = wave_sum(cnt.flag);
-    uint32_t x = wave_sum(cnt.exact);
-    if (lane == 0) {
-        if (f)
-            atomicAdd(&a.stats[1], (unsigned long long)f);
-        if (x)
-            atomicAdd(&a.stats[2], (unsigned long long)x);
-        if (n_skip)
-            atomicAdd(&a.stats[3], (unsigned long long)n_skip);
-        if (cnt.rare)
-            atomicAdd(&a.stats[4], (unsigned long long)cnt.rare);
-        if (cnt.beyond_steps)
-            atomicAdd(&a.stats[5], (unsigned long long)cnt.beyond_steps);
-        if (cnt.one_slot_steps)
-            atomicAdd(&a.stats[6], (unsigned long long)cnt.one_slot_steps);
-        if (cnt.two_slot_steps)
-            atomicAdd(&a.stats[0], (unsigned long long)cnt.two_slot_steps);
-        if (cnt.pruned_blocks)
-            atomicAdd(&a.stats[7], (unsigned long long)cnt.pruned_blocks * (unsigned long long)(kRowsPerWave * 64));
-        if (cnt.chord_steps)
-            atomicAdd(&a.stats[8], (unsigned long long)cnt.chord_steps);
+    if (held)
+        flush();
+    // work statistics: one lane per word, into one of kStatCopies copies
+    // (thousands of wavefronts adding to one line would wait for each other
+    // longer than a small launch runs)
+    const uint32_t f = wave_sum(cnt.flag);
+    const uint32_t x = wave_sum(cnt.exact);
+    unsigned long long v = 0;
+    switch (lane) {
+    case 0: v = cnt.two_slot_steps; break;
+    case 1: v = f; break;
+    case 2: v = x; break;
+    case 3: v = n_skip; break;
+    case 4: v = cnt.rare; break;
+    case 5: v = cnt.beyond_steps; break;
+    case 6: v = cnt.one_slot_steps; break;
+    case 7: v = (unsigned long long)cnt.pruned_blocks * (unsigned long long)(kRowsPerWave * 64); break;
+    case 8: v = cnt.chord_steps; break;
     }
+    if (v)
+        atomicAdd(&a.stats[(size_t)(copy & (kStatCopies - 1)) * kStatStride + lane], v);
 }
 
 __global__ void zero_u64_kernel(unsigned long long *p, int64_t n) {
