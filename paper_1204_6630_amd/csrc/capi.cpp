@@ -74,12 +74,13 @@ struct Tuning {
 int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs) {
     if (t.rows_per_lane)
         return t.rows_per_lane;
-    return precision == TPCF_FP32_CHORD && !t.prune && pairs < ((uint64_t)1 << 22) ? 2 : 4;
+    return precision == TPCF_FP32_CHORD && pairs < ((uint64_t)1 << 22) ? 2 : 4;
 }
 
-// Largest column chunk: 2048, and 4096 with pruning, whose items prepare more
-// (1e6 x 2e6: 4096 columns 228.9 ms, 2048 229.1, 1024 233, 512 245; a 3-D box
-// of 5e5 x 1e6 55.4, 54.9, 54.2, 57.0; pruned 5e5 x 1e6: 4096 95.7, 1024 98.0).
+// Largest column chunk: 2048, and 4096 with pruning, where one test covers
+// 4096 columns (1e6 x 2e6: 4096 columns 241.0 ms, 2048 242.3, 1024 251.0; a
+// 3-D box of 5e5 x 1e6 56.0, 55.2, 56.6; pruned 5e5 x 1e6: 8192 52.1, 4096
+// 51.9, 1024 60.0).
 int max_cols_of(const Tuning &t) { return t.max_cols ? t.max_cols : t.prune ? 4096 : 2048; }
 
 // Device memory of one context, with an optional budget on the total.
@@ -154,7 +155,7 @@ struct Catalog {
 
 struct Compiled {
     EdgeTables edges;
-    DevBuf dD, dE, dqlo, dqhi, dlut, dErad;
+    DevBuf dD, dE, dqlo, dqhi, dlut;
     CellTable cells;
     Band32 band;
     int tile_edges_at = -1, tile_slots_at = -1;   // FP32 tiles: where their tables lie in dqlo (floats)
@@ -516,7 +517,6 @@ std::string edges_key(const double *edges, int nbins, int precision, double delt
         k.append((const char *)&delta, sizeof delta);
     k.append((const char *)&t.lut_bytes, sizeof t.lut_bytes);
     k.append((const char *)&t.hist_copies, sizeof t.hist_copies);   // the table takes the LDS they leave
-    k.append((const char *)&t.prune, sizeof t.prune);               // pruned: unscaled tables
     return k;
 }
 
@@ -534,7 +534,6 @@ void free_compiled(tpcf_ctx *ctx, Compiled &c) {
     c.dqlo.release(ctx->mem);
     c.dqhi.release(ctx->mem);
     c.dlut.release(ctx->mem);
-    c.dErad.release(ctx->mem);
 }
 
 int hist_copies_of(const Tuning &t, int nslots);
@@ -567,39 +566,34 @@ int compile_host(const Tuning &tune, const double *edges, int nbins, int precisi
     c->delta = delta;
     c->metric = metric;
     const int nslots = nbins + 2;
-    const bool tiles = precision == TPCF_FP32_CHORD && !tune.prune;
+    const bool tiles = precision == TPCF_FP32_CHORD;
     c->entry_bytes = nslots <= kMaxSlots8 && !tiles ? 1 : 2;
     // FP32: by default the table fits the LDS target of its kernel with the
     // histograms and edges
     const int aux = aux_lds_bytes(nslots, hist_copies_of(tune, nslots), nbins + 1);
     int table_bytes = tune.lut_bytes ? tune.lut_bytes : kMaxLutBytes;
     if (precision == TPCF_FP32_CHORD && !tune.lut_bytes)
-        table_bytes = std::min(table_bytes, std::max(4096, ((tiles ? kLdsTargetTiles - tile_lds_bytes(nslots) : kLdsTarget) - aux) & ~15));
+        table_bytes = std::min(table_bytes, std::max(4096, (kLdsTarget - tile_lds_bytes(nslots) - aux) & ~15));
     const int max_cells = std::min(table_bytes, kMaxLutBytes) / c->entry_bytes;
     qlo->assign(c->edges.D.size(), 0.0f);
     qhi->assign(c->edges.D.size(), 0.0f);
     if (precision == TPCF_FP32_CHORD) {
         c->band = metric ? make_band32_3d(c->edges, delta) : make_band32(c->edges, delta);
         uint32_t top = metric ? qtop_key_3d(delta) : qtop_key(delta);
-        if (tiles) {
-            c->q_exp = tile_scale_exp(metric, delta);
-            scale_band32(2 * c->q_exp, &c->band, &top);
-        }
-        c->cells = tiles ? make_cells_tiles(c->edges, c->band, top, max_cells)
-                         : make_cells32_top(c->edges, c->band, top, max_cells);
+        c->q_exp = tile_scale_exp(metric, delta);
+        scale_band32(2 * c->q_exp, &c->band, &top);
+        c->cells = make_cells_tiles(c->edges, c->band, top, max_cells);
         *qlo = c->band.qlo;
         *qhi = c->band.qhi;
-        if (tiles) {
-            // the kernel's slot and edge tables follow the lower ends (at a
-            // multiple of 4 floats, which the kernel reads whole)
-            std::vector<float> slots, edges;
-            make_tile_tables(c->band, &slots, &edges);
-            c->tile_edges_at = ((int)qlo->size() + 3) & ~3;
-            qlo->resize((size_t)c->tile_edges_at, 0.0f);
-            qlo->insert(qlo->end(), edges.begin(), edges.end());
-            c->tile_slots_at = (int)qlo->size();
-            qlo->insert(qlo->end(), slots.begin(), slots.end());
-        }
+        // the kernel's slot and edge tables follow the lower ends (at a
+        // multiple of 4 floats, which the kernel reads whole)
+        std::vector<float> slots, edges;
+        make_tile_tables(c->band, &slots, &edges);
+        c->tile_edges_at = ((int)qlo->size() + 3) & ~3;
+        qlo->resize((size_t)c->tile_edges_at, 0.0f);
+        qlo->insert(qlo->end(), edges.begin(), edges.end());
+        c->tile_slots_at = (int)qlo->size();
+        qlo->insert(qlo->end(), slots.begin(), slots.end());
     } else if (metric) {
         const double top = 4.0 * delta * delta * (1.0 + ldexp(1.0, -10));
         c->cells = make_cells64(c->edges, max_cells, top > 1e-300 ? top : 1e-300);
@@ -647,8 +641,7 @@ int get_compiled(tpcf_ctx *ctx, const double *edges, int nbins, int precision, d
     int rc;
     if ((rc = upload_blocking(ctx->mem, c->dD, c->edges.D)) || (rc = upload_blocking(ctx->mem, c->dE, c->edges.E)) ||
         (rc = upload_blocking(ctx->mem, c->dqlo, qlo)) || (rc = upload_blocking(ctx->mem, c->dqhi, qhi)) ||
-        (rc = upload_blocking(ctx->mem, c->dlut, packed)) ||
-        (rc = upload_blocking(ctx->mem, c->dErad, c->edges.edge_rad))) {
+        (rc = upload_blocking(ctx->mem, c->dlut, packed))) {
         free_compiled(ctx, *c);
         return rc;
     }
@@ -1038,7 +1031,6 @@ PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, int rows, u
     // component (sqrt(3) 2^-24 R in all); cp.delta holds R for 3-D edges
     a.prune_margin = cp.metric ? ldexp(cp.delta, -22) + 1e-300 : 0.0;
     a.prune_delta = cp.metric ? 0.0 : delta;
-    a.erad = (const double *)cp.dErad.p;
     // key of the last edge's certain side (see PairArgs::beyond_key)
     const size_t last = cp.edges.D.size() - 1;
     if (cp.precision == TPCF_FP32_CHORD) {
@@ -1558,7 +1550,6 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     const size_t o_out = take(sizeof(unsigned long long) * (size_t)nslots);
     const size_t o_D = take(sizeof(double) * nedges), o_E = take(sizeof(double) * nedges);
     const size_t o_qlo = take(sizeof(float) * qlo.size()), o_qhi = take(sizeof(float) * qhi.size());
-    const size_t o_rad = take(sizeof(double) * nedges);
     const size_t o_lut = take(packed.size());
     const size_t o_units = off;
     if (o_units >= kScratchBytes)
@@ -1586,7 +1577,6 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     HIP_TRY(h2d(o_E, c.edges.E.data(), sizeof(double) * c.edges.E.size()));
     HIP_TRY(h2d(o_qlo, qlo.data(), sizeof(float) * qlo.size()));
     HIP_TRY(h2d(o_qhi, qhi.data(), sizeof(float) * qhi.size()));
-    HIP_TRY(h2d(o_rad, c.edges.edge_rad.data(), sizeof(double) * c.edges.edge_rad.size()));
     HIP_TRY(h2d(o_lut, packed.data(), packed.size()));
     HIP_TRY(h2d(o_units, plan.units.data(), sizeof(Unit) * plan.units.size()));
     // the histogram copies and the queue counter start at zero (a kernel, not a memset)
@@ -1596,7 +1586,6 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     c.dE.p = base + o_E;
     c.dqlo.p = base + o_qlo;
     c.dqhi.p = base + o_qhi;
-    c.dErad.p = base + o_rad;
     c.dlut.p = base + o_lut;
     PairArgs a = args_of(ctx, c, nbins, plan.rows, (unsigned long long *)ctx->main.stats.p, delta);
     a.prune = 0;     // bounding caps are built on first use, which allocates: count every pair

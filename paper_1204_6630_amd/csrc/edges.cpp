@@ -181,12 +181,10 @@ bool compile_edges(const double *edges_deg, int nbins, EdgeTables *out, std::str
     const double deg = M_PI / 180.0;
     EdgeTables t;
     t.nbins = nbins;
-    t.edge_rad.resize(nbins + 1);
     t.D.resize(nbins + 1);
     t.E.resize(nbins + 1);
     for (int k = 0; k <= nbins; ++k) {
         double e = edges_deg[k] * deg;
-        t.edge_rad[k] = e;
         double D = threshold_of(e);
         std::string why;
         if (!verify_threshold(e, D, &why)) {
@@ -403,7 +401,6 @@ bool compile_edges_3d(const double *edges, int nbins, EdgeTables *out, std::stri
     EdgeTables t;
     t.nbins = nbins;
     t.metric = 1;
-    t.edge_rad.assign(edges, edges + nbins + 1);
     t.D.resize(nbins + 1);
     t.E.resize(nbins + 1);
     for (int k = 0; k <= nbins; ++k) {

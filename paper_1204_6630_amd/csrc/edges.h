@@ -16,7 +16,6 @@ namespace tpcf {
 struct EdgeTables {
     int nbins = 0;
     int metric = 0;                 // 0: angles on the sky, 1: 3-D distances
-    std::vector<double> edge_rad;   // e_k = edge_deg[k] * (pi / 180); 3-D: e_k itself
     std::vector<double> D;          // largest d with acos(d) >= e_k (+-inf at the ends); 3-D: -S_k
     std::vector<double> E;          // fl(1 - D_k); -inf where D_k = +inf, +inf where D_k = -inf; 3-D: S_k
 };

@@ -17,18 +17,13 @@ constexpr int kMaxLutCells = kMaxLutBytes;        // with one-byte entries
 // Largest cell-table budget a tuning may ask for.
 constexpr int kMaxDirectLutBytes = 33792;
 // By default FP32 launches size their cell table so that a block's LDS stays
-// within the target: FP32 tiles four blocks of four wavefronts in a CU's
-// 160 KiB, pruned FP32 launches six, the occupancies those kernels are
-// compiled for (waves_per_eu_of).
-constexpr int kLdsTargetTiles = 40960;
-constexpr int kLdsTarget = 27296;
+// within the target: four blocks of four wavefronts in a CU's 160 KiB, the
+// occupancy the kernel is compiled for (waves_per_eu_of).
+constexpr int kLdsTarget = 40960;
 // Wavefronts per SIMD a pair kernel is compiled for: 4 for the FP32 tiles
 // (2, 3; two accumulators, eight row operands and the accumulator input in
-// at most 128 VGPRs), 6 for the pruned FP32 paths (0, 5; at most 80 VGPRs, a
-// few spilled), 5 for the FP64 paths (1, 4).
-constexpr int waves_per_eu_of(int path) {
-    return path == 2 || path == 3 ? 4 : path == 0 || path == 5 ? 6 : 5;
-}
+// at most 128 VGPRs), 5 for the FP64 paths (1, 4).
+constexpr int waves_per_eu_of(int path) { return path == 2 || path == 3 ? 4 : 5; }
 // FP32 tiles: error bound of q^ in units of 2^-24 (derived in
 // docs/fp32_band.md, section 4b): kTileErrN |b|^2 + kTileErrA rho^2 + kTileErr0.
 constexpr float kTileErrN = 24.0f;
@@ -133,9 +128,8 @@ struct PairArgs {
 
     // Exact tile pruning: 1 = a wavefront bins a whole aligned 64-column
     // block at once when the bounding caps put every pair of the block
-    // strictly inside one slot (edges in radians, nedges, in erad).
+    // strictly inside one slot.
     int32_t prune;
-    const double *erad;
 
     // 0: angles on the sky (dot products against D_k); 1: 3-D distances
     // (squared distances of Cartesian points, D_k = -S_k, E_k = S_k).

@@ -6,25 +6,23 @@
 // combined in one histogram in global memory.
 //
 // gfx950 design:
-//   * FP32 launches without pruning form the squared distances of 32 x 32
-//     pairs at a time on the matrix cores and bin whole tiles (see "FP32
-//     tiles on the matrix cores" below); the points below are the vector
-//     paths (FP64, and FP32 with pruning);
+//   * FP32 launches form the squared distances of 32 x 32 pairs at a time on
+//     the matrix cores and bin whole tiles (see "FP32 tiles on the matrix
+//     cores" below); the points below are the FP64 vector path;
 //   * one work unit = a tile of rows i (four wavefronts, each holding P = 2
 //     or 4 points per lane in registers) against a range of columns
 //     j; every wavefront walks the same j range, reading each j through the
 //     scalar unit (the address is uniform), so no LDS staging of j is needed;
 //   * a pair is classified with one table lookup in LDS: the key is the top
-//     bits of q = fl32 |f_i - f_j|^2 (FP32_CHORD) or of e = fl64(1 - d)
-//     (FP64); a cell whose whole range lies between two edges gives the slot
-//     directly, a cell that straddles one edge's band is settled by one
-//     threshold comparison, and anything closer is re-decided with the
-//     exact FP64 rule d <= D_k;
+//     bits of e = fl64(1 - d); a cell whose whole range lies between two
+//     edges gives the slot directly, a cell that straddles one edge is
+//     settled by one threshold comparison, and anything closer is re-decided
+//     with the exact rule d <= D_k;
 //   * every wavefront owns a private LDS histogram, layout [slot][copy] with
 //     copy = lane mod copies, updated with ds_add_u32;
-//   * after each unit a wavefront sums its histogram and adds it with 64-bit
-//     atomics into one of kGlobalCopies global copies, which a final kernel
-//     reduces into the output slots.
+//   * a wavefront sums its histogram when its items go to another job (and
+//     at the end) and adds it with 64-bit atomics into one of kGlobalCopies
+//     global copies, which a final kernel reduces into the output slots.
 //
 // The whole file is compiled with -ffp-contract=off: the FP64 dot product is
 // evaluated unfused and left to right exactly like the counting rule; the
@@ -39,12 +37,9 @@ using namespace tpcf;
 
 namespace {
 
-// Columns per step of the vector paths (each lane evaluates P x this many
-// pairs between two wavefront-wide tests).  Measured on the octant workload:
-// 4 columns are 8 % faster than 2 on the FP32 path (fewer tests and loop
-// trips per pair), while the FP64 path, with twice the registers per value,
-// is 12 % slower at 4 than at 2.
-constexpr int kColsPerStepF32 = 4;
+// Columns per step of the FP64 vector path (each lane evaluates P x this many
+// pairs between two wavefront-wide tests): 12 % slower at 4 than at 2 on the
+// octant workload, for the registers.
 constexpr int kColsPerStepF64 = 2;
 
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
@@ -53,7 +48,6 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 // Column coordinates are read through the constant address space: every lane
 // of a wavefront reads the same j, so these become scalar loads into SGPRs.
-typedef const __attribute__((address_space(4))) float *cfloat_p;
 typedef const __attribute__((address_space(4))) double *cdouble_p;
 typedef const __attribute__((address_space(4))) uint32_t *cword_p;
 typedef const __attribute__((address_space(1))) double *gdouble_p;
@@ -202,7 +196,6 @@ struct Smem {
     double *D;
     double *E;
     float2 *qband;       // FP32 band (qlo_k, qhi_k), one 8-byte read per edge
-    double *erad;        // edges in radians (pruning)
     float2 *slots;       // FP32 tiles: lower end and width of every slot
     uint32_t stage_addr; // FP32 tiles: LDS byte address of the wavefronts' column buffers
     float4 *edges;       // FP32 tiles: qhi, qhi - qlo, room below and above every edge
@@ -229,8 +222,6 @@ __device__ __forceinline__ Smem carve(unsigned char *base, const PairArgs &a) {
     } else {
         s.D = reinterpret_cast<double *>(edges);
         s.E = s.D + a.nedges;
-        s.erad = s.E + a.nedges;
-        s.qband = reinterpret_cast<float2 *>(s.erad + a.nedges);
     }
     s.hist_addr = (uint32_t)(uintptr_t)(lds_u32 *)s.hist;
     s.lut_addr = (uint32_t)(uintptr_t)(lds_u8 *)s.lut;
@@ -283,26 +274,6 @@ __device__ void flush_wave(const PairArgs &a, const Smem &s, unsigned long long 
 // A flagged entry: edge k alone is undecided in the cell (its FP32 band,
 // one 8-byte LDS read, settles q outside [qlo_k, qhi_k); inside it the exact
 // FP64 rule compares d with D_k), or several are (the rule counts them).
-template <bool LUT8, bool M3>
-__device__ __forceinline__ uint32_t resolve_fp32(uint32_t ent, uint32_t flag, float q, const Smem &s,
-                                                 const PairArgs &a, const JobDev &jb, int i, int j,
-                                                 uint32_t &n_exact) {
-    if (ent != (flag | Code<LUT8>::kmask)) {
-        const int k = (int)(ent ^ flag);
-        const float2 b = s.qband[k];
-        if (q < b.x)
-            return (uint32_t)k;
-        if (q >= b.y)
-            return (uint32_t)(k + 1);
-        ++n_exact;
-        const double d = rule_value<M3>(jb.ax64[i], jb.ay64[i], jb.az64[i], jb.bx64[j], jb.by64[j], jb.bz64[j]);
-        return (uint32_t)k + (d <= s.D[k] ? 1u : 0u);
-    }
-    ++n_exact;
-    const double d = rule_value<M3>(jb.ax64[i], jb.ay64[i], jb.az64[i], jb.bx64[j], jb.by64[j], jb.bz64[j]);
-    return count_le(d, s.D, a.nedges);
-}
-
 template <bool LUT8>
 __device__ __forceinline__ uint32_t resolve_fp64(uint32_t ent, uint32_t flag, double e, double d,
                                                  const Smem &s, const PairArgs &a,
@@ -518,47 +489,27 @@ __device__ __forceinline__ Cap cap_of(const double (&x)[N], const double (&y)[N]
     return c;
 }
 
-// Number of thresholds (non-increasing, in LDS) that v passes (v <= T[k]),
-// and whether w passes the same ones: lane L compares both with T[L + 64 m],
-// one LDS read and two ballots per 64 thresholds.  -1 when they differ.
-// Wavefront-uniform.
-__device__ __forceinline__ int same_count_le(double v, double w, const double *T, int n, int lane) {
-    int count = 0;
-    for (int b = 0; b < n; b += kWaveSize) {
-        const double t = b + lane < n ? T[b + lane] : -__builtin_huge_val();
-        const uint64_t mv = __builtin_amdgcn_ballot_w64(v <= t);
-        if (mv != __builtin_amdgcn_ballot_w64(w <= t))
-            return -1;
-        count += __builtin_popcountll(mv);
-    }
-    return count;
-}
-
-// The slot of every pair between the row cap and the column block's cap, or
-// -1 when the test cannot prove one (see above; delta bounds the catalogs'
-// | |v|^2 - 1 |).  With c = cos(theta_c) the dot product of the two centres,
-// sn an upper bound of sin(theta_c) and rho the summed radii, every pair's
-// geometric angle is theta_c + t with |t| <= rho, and
+// Bounds of the rule's value over every pair between the row cap and a column
+// block's cap (delta bounds the catalogs' | |v|^2 - 1 |).  With
+// c = cos(theta_c) the dot product of the two centres, sn an upper bound of
+// sin(theta_c) and rho the summed radii, every pair's geometric angle is
+// theta_c + t with |t| <= rho, and
 // cos(theta_c + t) = c cos t - sin(theta_c) sin t lies within
 // [c - sn rho - max(c, 0) rho^2 / 2, c + sn rho + max(-c, 0) rho^2 / 2]
 // (1 - t^2 / 2 <= cos t <= 1, |sin t| <= |t|).  No trigonometric function is
 // evaluated; the margin in rho (1e-6 rad) widens the interval by at least
 // sn 1e-6 > 6e-14, far above the rounding of this arithmetic.
-__device__ __forceinline__ int prune_slot(const Cap &r, const double *bcap, const Smem &s, int nedges,
-                                          double delta, int lane) {
-    const cdouble_p bc = (cdouble_p)bcap;
-    const double c = fmin(fmax(r.x * bc[0] + r.y * bc[1] + r.z * bc[2], -1.0), 1.0);
-    const double rho = r.rho + bc[3] + kPruneMargin;
+__device__ __forceinline__ void dot_range(const Cap &r, const Cap &b, double delta, double &lo, double &hi) {
+    const double c = fmin(fmax(r.x * b.x + r.y * b.y + r.z * b.z, -1.0), 1.0);
+    const double rho = r.rho + b.rho + kPruneMargin;
     const double h = 0.5 * rho * rho;
     // an upper bound of the sine: 1 - c^2 formed as (1 - c)(1 + c), plus the
     // rounding of c and of that product
     const double sn = sqrt((1.0 - c) * (1.0 + c) + 4e-15);
-    double hi = c + sn * rho + fmax(-c, 0.0) * h;
-    double lo = c - sn * rho - fmax(c, 0.0) * h;
+    hi = c + sn * rho + fmax(-c, 0.0) * h;
+    lo = c - sn * rho - fmax(c, 0.0) * h;
     hi = hi + delta * fabs(hi) + kPruneDotSlack;
     lo = lo - delta * fabs(lo) - kPruneDotSlack;
-    // pairs with the largest d pass the fewest edges
-    return same_count_le(hi, lo, s.D, nedges, lane);
 }
 
 // 3-D: bounding ball of the points held by the lanes (centre = their mean,
@@ -588,52 +539,62 @@ __device__ __forceinline__ Cap ball_of(const double (&x)[N], const double (&y)[N
     return c;
 }
 
-// 3-D: the slot of every pair between the row ball and the column block's
-// ball, or -1.  Their distances lie within [|c_r - c_b| -+ (rho_r + rho_b)],
-// widened by margin (the FP32 copies of the rows, at most 2^-22 R) and by
-// 1e-12 relative (the rule's and this arithmetic's rounding).
-__device__ __forceinline__ int prune_slot3(const Cap &r, const double *bcap, const Smem &s, int nedges,
-                                           double margin, int lane) {
-    const cdouble_p bc = (cdouble_p)bcap;
-    const double dx = r.x - bc[0], dy = r.y - bc[1], dz = r.z - bc[2];
+// 3-D: bounds of the rule's value, minus the squared distance.  The distances
+// lie within [|c_r - c_b| -+ (rho_r + rho_b)], widened by margin (the FP32
+// copies of the rows, at most 2^-22 R) and by 1e-12 relative (the rule's and
+// this arithmetic's rounding, the squares below included; 1e-300 covers
+// squares that round to subnormal numbers).
+__device__ __forceinline__ void d2_range(const Cap &r, const Cap &b, double margin, double &lo, double &hi) {
+    const double dx = r.x - b.x, dy = r.y - b.y, dz = r.z - b.z;
     const double dc = sqrt(dx * dx + dy * dy + dz * dz);
-    const double spread = r.rho + bc[3];
+    const double spread = r.rho + b.rho;
     const double w = margin + 1e-12 * (dc + spread);
-    const double lo = dc - spread - w, hi = dc + spread + w;
-    // a pair at distance r passes edge k when e_k <= r: lane L compares
-    // both ends with edge L + 64 m
-    int count = 0;
-    for (int b = 0; b < nedges; b += kWaveSize) {
-        const double t = b + lane < nedges ? s.erad[b + lane] : __builtin_huge_val();
-        const uint64_t ml = __builtin_amdgcn_ballot_w64(t <= lo);
-        if (ml != __builtin_amdgcn_ballot_w64(t <= hi))
-            return -1;
-        count += __builtin_popcountll(ml);
-    }
-    return count;
+    const double near = fmax(dc - spread - w, 0.0), far = dc + spread + w;
+    hi = -fmax(near * near - 1e-300, 0.0);
+    lo = -(far * far) - 1e-300;
 }
 
-// Block cap and block slot for either metric.
+// Block cap for either metric.
 template <bool M3, int N>
 __device__ __forceinline__ Cap block_cap(const double (&x)[N], const double (&y)[N], const double (&z)[N]) {
     return uniform_cap(M3 ? ball_of<N>(x, y, z) : cap_of<N>(x, y, z));
 }
 
-template <bool M3>
-__device__ __forceinline__ int block_slot(const Cap &r, const double *bcap, const Smem &s, const PairArgs &a,
-                                          int lane) {
-    return M3 ? prune_slot3(r, bcap, s, a.nedges, a.prune_margin, lane)
-              : prune_slot(r, bcap, s, a.nedges, a.prune_delta, lane);
-}
+// Columns one call of prune_blocks covers, from an aligned one on.
+constexpr int kPruneCols = 64 * kWaveSize;
 
-// Add n pairs of this lane to `slot` (the overflow slot through the register
-// counter).
-__device__ __forceinline__ void bin_block(int slot, uint32_t n, const PairArgs &a, const Consts &k,
-                                          Counters &cnt) {
-    if (slot == a.nslots - 1)
-        cnt.beyond += n;
-    else
-        lds_add(__umul24((uint32_t)slot, k.rowstep) + k.lanebase, n);
+// The aligned 64-column blocks of [j0, j1) (64 of them at most), against the
+// row cap r of a wavefront with all of its rows: those that lie whole in the
+// range, past its masked columns (up to jm), and are proven to hold pairs of one slot only are binned (n pairs
+// each); bit b of the result is set for the others.  One lane per block and one binary search
+// over the thresholds for both ends of the range: testing the blocks one by
+// one, a lane per threshold, took the whole wavefront as long for one block
+// as this takes for all of them.
+template <bool M3>
+__device__ __forceinline__ uint64_t prune_blocks(const Cap &r, const double *bcaps, const Smem &s, const PairArgs &a,
+                                                 const Consts &k, int j0, int j1, int jm, uint32_t n, int lane,
+                                                 Counters &cnt) {
+    const int64_t b = (int64_t)(j0 >> 6) + lane;
+    bool one = 64 * b >= max(j0, jm) && 64 * b + 64 <= j1;
+    if (one) {
+        const double *c = bcaps + 4 * b;
+        const Cap bc{c[0], c[1], c[2], c[3]};
+        double lo, hi;
+        if (M3)
+            d2_range(r, bc, a.prune_margin, lo, hi);
+        else
+            dot_range(r, bc, a.prune_delta, lo, hi);
+        // pairs with the largest value pass the fewest edges
+        const uint32_t slot = count_le(hi, s.D, a.nedges);
+        one = slot == (uint32_t)a.nedges || lo > s.D[slot];
+        if (one && slot == (uint32_t)(a.nslots - 1))
+            cnt.beyond += n;
+        else if (one)
+            lds_add(__umul24(slot, k.rowstep) + k.lanebase, n);
+    }
+    const uint64_t done = __builtin_amdgcn_ballot_w64(one);
+    cnt.pruned_blocks += (uint32_t)__builtin_popcountll(done);
+    return __builtin_amdgcn_ballot_w64(64 * b < j1) & ~done;
 }
 
 // Row p of a wavefront lane whose rows start at ib: lane L holds the P
@@ -649,137 +610,6 @@ __device__ __forceinline__ int row_of(int ib, int lane, int p) {
 // One step: JN columns against the P rows of every lane.  All JN * P table
 // lookups are issued first; one test sends the wavefront to the rare path if
 // any lane needs it; then the JN * P histogram increments follow.
-template <bool LUT8, bool MASKED, int P, int JN, bool M3, bool ONE>
-__device__ __forceinline__ uint32_t step_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
-                                          const float (&xi)[P], const float (&yi)[P],
-                                          const float (&zi)[P], const int (&ii)[P],
-                                          int ib, int lane, int ie, int j, const float (&xj)[JN],
-                                          const float (&yj)[JN], const float (&zj)[JN], uint32_t &qmin,
-                                          Counters &cnt) {
-    float q[JN][P];
-    uint32_t ent[JN][P];
-#pragma unroll
-    for (int t = 0; t < JN; ++t) {
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            float dx = xi[p] - xj[t];
-            float dy = yi[p] - yj[t];
-            float dz = zi[p] - zj[t];
-            float v = dx * dx;
-            v = __fmaf_rn(dy, dy, v);
-            v = __fmaf_rn(dz, dz, v);
-            q[t][p] = v;
-        }
-    }
-    if (!MASKED) {
-        // every pair of the step certainly beyond the last edge (q >= 0, so the
-        // bit patterns order like the values): count them in a register
-        uint32_t qb[JN * P];
-#pragma unroll
-        for (int t = 0; t < JN; ++t)
-#pragma unroll
-            for (int p = 0; p < P; ++p)
-                qb[t * P + p] = __float_as_uint(q[t][p]);
-        const uint32_t m = tree_reduce(qb, [](uint32_t x, uint32_t y) { return min(x, y); });
-        qmin = m;
-        if (wave_all(m >= k.beyond))
-            return kBeyond;
-        if constexpr (ONE) {
-            // every pair of the step in one slot: the cells of each lane's
-            // smallest and largest key hold the same certain slot on every lane
-            // (a wavefront's 4 x 64 rows are consecutive in the Morton order, so
-            // at angles large against their extent this is common; with pruning
-            // such blocks are mostly pruned, and the kernel skips the test to
-            // save its registers)
-            const uint32_t mx = tree_reduce(qb, [](uint32_t x, uint32_t y) { return max(x, y); });
-            uint32_t base, span;
-            slot_range<LUT8>(lds_read_entry<LUT8>(addr32<LUT8>(m, k)),
-                             lds_read_entry<LUT8>(addr32<LUT8>(mx, k)), base, span);
-            if (one_slot_step(base, span, JN * P, k, cnt))
-                return kOneSlot;
-            if (two_slot_range<LUT8>(base, span)) {
-                // a pair is past edge `base` when q >= qhi and not past it when
-                // q < qlo.  x = fl(q - qhi) is >= 0 exactly when q >= qhi
-                // (a difference of floats rounds to zero only when they are
-                // equal, and then to +0), and x < 0 with |x| > w = fl(qhi - qlo)
-                // puts q below qlo (fl is monotone): these pairs are decided,
-                // the sign bit of x marking those not past.  As int32 bit
-                // patterns, exactly the decided x lie above that of -w (a
-                // negative float's pattern grows with its magnitude), so one
-                // signed minimum checks every pair.  Lanes with one slot
-                // compare with +inf (x = -inf) and decide everything; a NaN
-                // width (an edge at 0) decides nothing.  (The sign bit counts
-                // the pairs: no compare-and-carry, whose mask hazard costs
-                // wait states on gfx950.)
-                const float2 b = s.qband[min(base, (uint32_t)(a.nedges - 1))];
-                const float thr = span ? b.y : __builtin_huge_valf();
-                const float nw = -(b.y - b.x);
-                const int32_t lim = !span ? INT32_MIN : nw == nw ? (int32_t)__float_as_uint(nw) : INT32_MAX;
-                uint32_t n_below = 0;
-                int32_t m = INT32_MAX;
-#pragma unroll
-                for (int t = 0; t < JN; ++t)
-#pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        const float x = q[t][p] - thr;
-                        n_below += __float_as_uint(x) >> 31;
-                        m = min(m, (int32_t)__float_as_uint(x));
-                    }
-                // count before the test, so the differences die here
-                asm volatile("" : "+v"(n_below));
-                if (wave_all(m > lim)) {
-                    two_slot_add(base, JN * P, JN * P - n_below, k, cnt);
-                    return kTwoSlot;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < JN; ++t) {
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            ent[t][p] = lds_read_entry<LUT8>(addr32<LUT8>(__float_as_uint(q[t][p]), k));
-        }
-    }
-    uint32_t any = 0;
-#pragma unroll
-    for (int t = 0; t < JN; ++t)
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-            any |= ent[t][p];
-    if (any & k.flag) {
-        ++cnt.rare;             // wavefront steps that took the rare path
-#pragma unroll
-        for (int t = 0; t < JN; ++t)
-#pragma unroll
-            for (int p = 0; p < P; ++p)
-                if (ent[t][p] & k.flag) {
-                    ++cnt.flag;
-                    // the row is formed here, on demand, from an opaque copy
-                    // of the lane index, so no row index or address of this
-                    // rare path is hoisted into registers of the loop (tail
-                    // lanes read row ib)
-                    int l = lane;
-                    asm volatile("" : "+v"(l));
-                    int i = row_of<P>(ib, l, p);
-                    i = i < ie ? i : ib;
-                    ent[t][p] = resolve_fp32<LUT8, M3>(ent[t][p], k.flag, q[t][p], s, a, jb, i, j + t, cnt.exact);
-                }
-    }
-#pragma unroll
-    for (int t = 0; t < JN; ++t)
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            uint32_t e = ent[t][p];
-            if (MASKED) {
-                bool ok = ii[p] < ie && (!jb.auto_pairs || j + t > ii[p]);
-                e = ok ? e : (uint32_t)a.nslots;
-            }
-            lds_inc(__umul24(e, k.rowstep) + k.lanebase);
-        }
-    return kLookup;
-}
-
 template <bool LUT8, bool MASKED, int P, int JN, bool M3, bool ONE>
 __device__ __forceinline__ uint32_t step_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
                                           const double (&xi)[P], const double (&yi)[P],
@@ -892,107 +722,6 @@ __device__ __forceinline__ uint32_t step_fp64(const PairArgs &a, const JobDev &j
     return kLookup;
 }
 
-// Columns [j0, j1) against the P rows of every lane (FP32 path).
-template <bool LUT8, bool MASKED, int P, bool M3, bool ONE>
-__device__ __forceinline__ void cols_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
-                                          const float (&xi)[P], const float (&yi)[P], const float (&zi)[P],
-                                          const int (&ii)[P], int ib, int lane, int ie, int j0, int j1,
-                                          Counters &cnt) {
-    cfloat_p bx = (cfloat_p)jb.bx32;
-    cfloat_p by = (cfloat_p)jb.by32;
-    cfloat_p bz = (cfloat_p)jb.bz32;
-    constexpr int JN = kColsPerStepF32;
-    int j = j0;
-    if (j + JN <= j1) {
-        // the columns of the next step are read (through the scalar unit)
-        // while the current step computes; the last prefetch re-reads the
-        // current columns, so no read leaves [j0, j1)
-        float xj[JN], yj[JN], zj[JN];
-#pragma unroll
-        for (int t = 0; t < JN; ++t) {
-            xj[t] = bx[j + t];
-            yj[t] = by[j + t];
-            zj[t] = bz[j + t];
-        }
-        for (; j + JN <= j1; j += JN) {
-            const int jn = j + 2 * JN <= j1 ? j + JN : j;
-            float xn[JN], yn[JN], zn[JN];
-#pragma unroll
-            for (int t = 0; t < JN; ++t) {
-                xn[t] = bx[jn + t];
-                yn[t] = by[jn + t];
-                zn[t] = bz[jn + t];
-            }
-            // keep the prefetch at the top of the step
-            __builtin_amdgcn_sched_barrier(0);
-            uint32_t qmin = 0;
-            const uint32_t code = __builtin_amdgcn_readfirstlane(step_fp32<LUT8, MASKED, P, JN, M3, ONE>(
-                a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, xj, yj, zj, qmin, cnt));
-            account<JN * P>(code, cnt);
-#pragma unroll
-            for (int t = 0; t < JN; ++t) {
-                xj[t] = xn[t];
-                yj[t] = yn[t];
-                zj[t] = zn[t];
-            }
-        }
-    }
-    for (; j < j1; ++j) {
-        const float xj[1] = {bx[j]}, yj[1] = {by[j]}, zj[1] = {bz[j]};
-        uint32_t qmin = 0;
-        account<P>(__builtin_amdgcn_readfirstlane(step_fp32<LUT8, MASKED, P, 1, M3, false>(
-                       a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, xj, yj, zj, qmin, cnt)),
-                   cnt);
-    }
-    cnt.fold();
-}
-
-
-// One wavefront: rows [ib, ie) (at most P * 64) against columns [j0, j1).
-template <bool LUT8, bool MASKED, int P, bool PRUNE, bool M3>
-__device__ void rows_fp32(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k, int ib, int ie,
-                          int j0, int j1, int lane, Counters &cnt) {
-    float xi[P], yi[P], zi[P];
-    int ii[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        int i = row_of<P>(ib, lane, p);
-        ii[p] = i;
-        const int il = i < ie ? i : ib;    // tail lanes read a valid row; masked below
-        xi[p] = jb.ax32[il];
-        yi[p] = jb.ay32[il];
-        zi[p] = jb.az32[il];
-    }
-    if (PRUNE && !MASKED && jb.bcaps) {
-        double xd[P], yd[P], zd[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            xd[p] = xi[p];
-            yd[p] = yi[p];
-            zd[p] = zi[p];
-        }
-        const Cap rc = block_cap<M3, P>(xd, yd, zd);
-        for (int j = j0; j < j1;) {
-            const int jn = min(j1, (j & ~63) + 64);
-            if ((j & 63) == 0 && jn - j == 64) {
-                const int slot = block_slot<M3>(rc, jb.bcaps + (size_t)(j >> 6) * 4, s, a, lane);
-                if (slot >= 0) {
-                    bin_block(slot, P * 64, a, k, cnt);
-                    ++cnt.pruned_blocks;
-                    j = jn;
-                    continue;
-                }
-            }
-            cols_fp32<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, j, jn, cnt);
-            j = jn;
-        }
-        return;
-    }
-    for (int jc = j0; jc < j1; jc += kFoldCols)
-        cols_fp32<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ib, lane, ie, jc,
-                                                          j1 - jc > kFoldCols ? jc + kFoldCols : j1, cnt);
-}
-
 // Columns [j0, j1) against the P rows of every lane (FP64 vector path).
 template <bool LUT8, bool MASKED, int P, bool M3, bool ONE>
 __device__ __forceinline__ void cols_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, const Consts &k,
@@ -1030,19 +759,18 @@ __device__ void rows_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, co
     }
     if (PRUNE && !MASKED && jb.bcaps) {
         const Cap rc = block_cap<M3, P>(xi, yi, zi);
-        for (int j = j0; j < j1;) {
-            const int jn = min(j1, (j & ~63) + 64);
-            if ((j & 63) == 0 && jn - j == 64) {
-                const int slot = block_slot<M3>(rc, jb.bcaps + (size_t)(j >> 6) * 4, s, a, lane);
-                if (slot >= 0) {
-                    bin_block(slot, P * 64, a, k, cnt);
-                    ++cnt.pruned_blocks;
-                    j = jn;
-                    continue;
-                }
+        for (int jr = j0, je; jr < j1; jr = je) {
+            const int to = kPruneCols - (jr & 63), b0 = jr >> 6;
+            je = j1 - jr > to ? jr + to : j1;
+            uint64_t left = prune_blocks<M3>(rc, jb.bcaps, s, a, k, jr, je, jr, P * 64 * 64, lane, cnt);
+            while (left) {      // runs of blocks that are left
+                const int f = __builtin_ctzll(left);
+                const uint64_t gap = ~(left >> f);
+                const int e = f + (gap ? __builtin_ctzll(gap) : 64);
+                cols_fp64<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ie, max(jr, (b0 + f) << 6),
+                                                     min(je, (b0 + e) << 6), cnt);
+                left = e < 64 ? left & (~0ull << e) : 0;
             }
-            cols_fp64<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ie, j, jn, cnt);
-            j = jn;
         }
         return;
     }
@@ -1563,10 +1291,11 @@ __device__ __forceinline__ uint32_t low_bits(int n) {
     return (1u << min(max(n, 0), G)) - 1u;
 }
 
-// One wavefront: rows [ib, ie) (at most 32 G) against columns [j0, j1).
-template <int G, bool M3>
+// One wavefront: rows [ib, ie) (at most 32 G) against columns [j0, j1), with
+// PRUNE those of the aligned blocks that `left` names (bit 0: j0's).
+template <int G, bool M3, bool PRUNE>
 __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts &k, int ib, int ie, int j0, int j1,
-                           int lane, Counters &cnt) {
+                           uint64_t left, int lane, Counters &cnt) {
     const int half = lane >> 5;
     const float S = args->q_scale, q_small = args->q_small;
     const TileArgs a{args->nedges, args->q_exp2};
@@ -1620,8 +1349,20 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
     const uint32_t stage = s.stage_addr + wave * (uint32_t)kStageWaveBytes;
     typedef volatile __attribute__((address_space(3))) float *lfloat_p;
     const lfloat_p col = (lfloat_p)(uintptr_t)(stage + 4u * (uint32_t)lane);
-    stage_columns(bx, by, bz, j0, j1 - 1, lane, stage);
-    for (int j = j0; j < j1; j += 64) {
+    const int b0 = j0 >> 6;
+    int j = j0, jn;
+    if (PRUNE)
+        j = max(j0, (b0 + __builtin_ctzll(left)) << 6);
+    stage_columns(bx, by, bz, j, j1 - 1, lane, stage);
+    for (; j < j1; j = jn) {
+        // this pass's columns end at jl (pruned launches: with their block),
+        // the next one's start at jn
+        const int jl = PRUNE ? min(j1, (j & ~63) + 64) : j1;
+        jn = j + 64;
+        if (PRUNE) {
+            left &= left - 1u;
+            jn = left ? (b0 + __builtin_ctzll(left)) << 6 : j1;
+        }
         // each lane prepares one of 64 columns, then the values are dealt to
         // the two tiles of 32
         __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): the copy has landed
@@ -1636,7 +1377,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
         // the slot of the column's distance from the rows' mean: its row in
         // the histogram, lower end and width
         const uint32_t row = cell_entry(nb, k) & ~kCellFlags;
-        const bool valid = j + lane < j1;
+        const bool valid = j + lane < jl;
         {
             const float2 sl = s.slots[row >> k.rowlog];
             const float es = __fmaf_rn(8.0f * u, fabsf(sl.x), __fmaf_rn(u * kTileErrN, nb, e_rows));
@@ -1648,8 +1389,8 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
         // have been read (the compiler waits for copies in flight before any
         // LDS read) and the tiles of one pass are still to come
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(base), "+v"(width) : : "memory");
-        if (j + 64 < j1)
-            stage_columns(bx, by, bz, j + 64, j1 - 1, lane, stage);
+        if (jn < j1)
+            stage_columns(bx, by, bz, jn, j1 - 1, lane, stage);
         uint32_t n_in = 0;      // tiles in one slot: columns 0-31, columns 32-63 (<< 16)
 #pragma unroll 1
         for (int h = 0; h < 64; h += 32) {
@@ -1661,9 +1402,9 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
             const int jh = j + h;
             if (auto_pairs) {
                 ok &= low_bits<G>((jh - ib) >> 5);
-                any &= low_bits<G>((min(jh + 31, j1 - 1) - ib + 31) >> 5);
+                any &= low_bits<G>((min(jh + 31, jl - 1) - ib + 31) >> 5);
             }
-            if (jh >= j1)
+            if (jh >= jl)
                 any = ok = 0;
             uint32_t rest = any & ~ok;
             if (ok) {
@@ -1689,7 +1430,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
                     while (todo) {
                         const int g = __builtin_ctz(todo);
                         todo &= todo - 1u;
-                        const TilePos t{ib, j, 32 * g + 16 * half, min(h + (lane & 31), j1 - 1 - j)};
+                        const TilePos t{ib, j, 32 * g + 16 * half, min(h + (lane & 31), jl - 1 - j)};
                         floatx16 c;
                         broadcast(c, off);
                         if (tile_split<M3>(a.q_exp2, job, s, tile_q(rows_at(fa, g), f, c), (int)ke, room, lim, t,
@@ -1711,9 +1452,9 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
             while (rest) {
                 const int g = __builtin_ctz(rest);
                 rest &= rest - 1u;
-                const TilePos t{ib, j, 32 * g + 16 * half, min(h + (lane & 31), j1 - 1 - j)};
-                const int jl = jh + (lane & 31), last = (auto_pairs ? min(ie, jl) : ie) - ib;
-                const uint32_t w = jl < j1 ? (uint32_t)min(max(last - t.io, 0), 16) : 0u;
+                const TilePos t{ib, j, 32 * g + 16 * half, min(h + (lane & 31), jl - 1 - j)};
+                const int jc = jh + (lane & 31), last = (auto_pairs ? min(ie, jc) : ie) - ib;
+                const uint32_t w = jc < jl ? (uint32_t)min(max(last - t.io, 0), 16) : 0u;
                 float nbh;
                 uint32_t row_h;
                 column_state(h, nb, row, valid, nbh, row_h);
@@ -1746,7 +1487,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
         }
         if (n_in) {
             const uint32_t both = (n_in & 0xFFFFu) + (n_in >> 16);
-            if (j + 64 <= j1 && __builtin_amdgcn_ballot_w64(row != overflow) == 0) {
+            if (j + 64 <= jl && __builtin_amdgcn_ballot_w64(row != overflow) == 0) {
                 n_beyond += both;
             } else {
                 lds_add(row + k.lanebase, valid ? 32u * (half ? n_in >> 16 : n_in & 0xFFFFu) : 0u);
@@ -1761,8 +1502,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
     cnt.beyond += n_beyond * 16u;
 }
 
-// PREC: 2 FP32 tiles, 0 FP32 chord (pruned launches), 1 FP64 vector; 3-D
-// distances: 3 FP32 tiles, 5 FP32 squared distance (pruned launches), 4 FP64
+// PREC: 2 FP32 tiles, 1 FP64 vector; 3-D distances: 3 FP32 tiles, 4 FP64
 // vector.  P: rows per lane (a wavefront covers P * 64 rows of a unit, for
 // tiles 2 P groups of 32).
 template <int PREC, bool LUT8, int P, bool PRUNE>
@@ -1786,12 +1526,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
         reinterpret_cast<uint4 *>(s.lut)[w] = reinterpret_cast<const uint4 *>(a.lut)[w];
     for (int e = tid; e < a.nedges; e += kBlock) {
         s.D[e] = a.D[e];
-        s.qband[e] = make_float2(a.qlo[e], a.qhi[e]);
         if (PREC == 2 || PREC == 3) {
+            s.qband[e] = make_float2(a.qlo[e], a.qhi[e]);
             s.edges[e] = a.tile_edges[e];
         } else {
             s.E[e] = a.E[e];
-            s.erad[e] = a.erad ? a.erad[e] : 0.0;
         }
     }
     if (PREC == 2 || PREC == 3)
@@ -1817,8 +1556,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
     // regions of the last items) and how many pairs they hold.  A wavefront
     // keeps them over its items until they go elsewhere or 2^31 pairs are
     // near (one LDS count holds less than 2^32): flushing 42 slots with
-    // global atomics after every item, and one queue atomic per item, cost
-    // about 12 ns of the device an item.
+    // global atomics after every item cost about 12 ns of the device an item.
     unsigned long long *to = nullptr, *to_a = nullptr, *to_b = nullptr;
     uint32_t held = 0;
     const int copy = (int)((blockIdx.x * kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wave)) & (kGlobalCopies - 1));
@@ -1836,23 +1574,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
     // Each wavefront takes work items in order from the queue, so the items in
     // flight are always a window of consecutive units that share their column
     // range (the plan orders units column chunk first) and the column data
-    // stays in L2.  While many are left it takes several at once: an eighth of
-    // its share of what was left when it last looked, at most kWaves (a whole
-    // unit's parts).  Every wavefront leaves once the queue is exhausted.
-    const uint32_t n_items = (uint32_t)a.n_units * kWaves, n_waves = gridDim.x * kWaves;
-    uint32_t next = 0, end = 0, unlooked = 1u << 21;    // (a cancellable launch holds one job)
+    // stays in L2.  One at a time, also where many are left: taking a whole
+    // unit's four parts at once slowed every large launch (a 3-D box of 5e5 x
+    // 1e6 55.2 -> 59.7 ms, 64 regions 6.4 -> 7.5, pruned 5e5 x 1e6 52 -> 58).
+    // Every wavefront leaves once the queue is exhausted.
+    const uint32_t n_items = (uint32_t)a.n_units * kWaves;
+    uint32_t unlooked = 1u << 21;   // (a cancellable launch holds one job)
     bool gone = false;
-    for (;; ++next) {
-        if (next == end) {
-            const uint32_t left = n_items - min(end, n_items);
-            const uint32_t take = min(max(left / (8u * n_waves), 1u), (uint32_t)kWaves);
-            if (lane == 0)
-                next = atomicAdd(a.queue, take);
-            next = __builtin_amdgcn_readfirstlane(next);
-            if (next >= n_items)
-                break;
-            end = min(next + take, n_items);
-        }
+    for (;;) {
+        uint32_t next = 0;
+        if (lane == 0)
+            next = atomicAdd(a.queue, 1u);
+        next = __builtin_amdgcn_readfirstlane(next);
+        if (next >= n_items)
+            break;
         const int u = (int)(next / kWaves);
         const int part = (int)(next % kWaves);
         Unit un;
@@ -1910,13 +1645,32 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
             // last row
             const int jm = ie - ib < kRowsPerWave ? un.j1 : jb.auto_pairs ? min(max(ie, jb0), un.j1) : jb0;
             if (PREC == 2 || PREC == 3) {
-                rows_tiles<2 * P, PREC == 3>(args, job, s, k, ib, ie, jb0, un.j1, lane, cnt);
-            } else if (PREC == 0 || PREC == 5) {
-                constexpr bool M3 = PREC == 5;
-                if (jb0 < jm)
-                    rows_fp32<LUT8, true, P, PRUNE, M3>(a, jb, s, k, ib, ie, jb0, jm, lane, cnt);
-                if (jm < un.j1)
-                    rows_fp32<LUT8, false, P, PRUNE, M3>(a, jb, s, k, ib, ie, jm, un.j1, lane, cnt);
+                constexpr bool M3 = PREC == 3;
+                if (!PRUNE) {
+                    rows_tiles<2 * P, M3, false>(args, job, s, k, ib, ie, jb0, un.j1, 0, lane, cnt);
+                } else {
+                    // aligned blocks past the masked columns, when every row
+                    // exists and the catalog has caps
+                    const bool caps = ie - ib == kRowsPerWave && jb.bcaps;
+                    for (int jr = jb0, je; jr < un.j1; jr = je) {
+                        const int to = kPruneCols - (jr & 63);
+                        je = un.j1 - jr > to ? jr + to : un.j1;
+                        uint64_t left = ~0ull;
+                        if (caps) {
+                            double x[P], y[P], z[P];
+#pragma unroll
+                            for (int p = 0; p < P; ++p) {
+                                x[p] = lane_load(job->ax32, ib, kWaveSize * p + lane);
+                                y[p] = lane_load(job->ay32, ib, kWaveSize * p + lane);
+                                z[p] = lane_load(job->az32, ib, kWaveSize * p + lane);
+                            }
+                            left = prune_blocks<M3>(block_cap<M3, P>(x, y, z), jb.bcaps, s, a, k, jr, je, jm,
+                                                    kRowsPerWave * 64, lane, cnt);
+                        }
+                        if (left)
+                            rows_tiles<2 * P, M3, true>(args, job, s, k, ib, ie, jr, je, left, lane, cnt);
+                    }
+                }
             } else {
                 constexpr bool M3 = PREC == 4;
                 if (jb0 < jm)
@@ -2086,19 +1840,15 @@ extern "C" int tpcf_launch_pairs(const PairArgs *args, int precision, void *stre
     if (precision != 0 && precision != 1)
         return (int)hipErrorInvalidValue;
     if (args->metric == 1) {
-        if (precision == 0 && prune)
-            b8 ? launch_pairs<5, true, true>(P, grid, lds, st, *args) : launch_pairs<5, false, true>(P, grid, lds, st, *args);
-        else if (precision == 0)
-            launch_pairs<3, false, false>(P, grid, lds, st, *args);
+        if (precision == 0)
+            prune ? launch_pairs<3, false, true>(P, grid, lds, st, *args) : launch_pairs<3, false, false>(P, grid, lds, st, *args);
         else if (prune)
             b8 ? launch_pairs<4, true, true>(P, grid, lds, st, *args) : launch_pairs<4, false, true>(P, grid, lds, st, *args);
         else
             b8 ? launch_pairs<4, true, false>(P, grid, lds, st, *args) : launch_pairs<4, false, false>(P, grid, lds, st, *args);
     } else {
-        if (precision == 0 && prune)
-            b8 ? launch_pairs<0, true, true>(P, grid, lds, st, *args) : launch_pairs<0, false, true>(P, grid, lds, st, *args);
-        else if (precision == 0)
-            launch_pairs<2, false, false>(P, grid, lds, st, *args);
+        if (precision == 0)
+            prune ? launch_pairs<2, false, true>(P, grid, lds, st, *args) : launch_pairs<2, false, false>(P, grid, lds, st, *args);
         else if (prune)
             b8 ? launch_pairs<1, true, true>(P, grid, lds, st, *args) : launch_pairs<1, false, true>(P, grid, lds, st, *args);
         else
