@@ -227,7 +227,7 @@ int tpcf_count_async(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b,
  * must not call hipMalloc or hipFree, such as tight serving loops or hosts
  * that forbid allocation during a run).  Same arguments, result, totals check
  * and errors as tpcf_count, and the same kernels, but every work buffer (the
- * histogram copies, the work-queue counter, the output slots, the edge and
+ * histogram copies, the work queues, the output slots, the edge and
  * cell tables and the work-unit list) lives in a fixed 16 MiB array in device
  * memory, one per device, set up by tpcf_open and held until the process
  * ends.  The call allocates no device memory, creates no event and does not

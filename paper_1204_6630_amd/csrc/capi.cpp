@@ -1096,10 +1096,10 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
         touch = (unsigned long long *)w.touch.p;
         HIP_TRY((hipError_t)tpcf_launch_zero_u64(touch, (int64_t)(per * (size_t)nreg), w.stream));
     }
-    // the histogram copies, then the work-queue counter, zeroed together
-    TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * ((size_t)kGlobalCopies * kMaxSlots + 1)));
+    // the histogram copies, then the work queues, zeroed together
+    TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * ((size_t)kGlobalCopies * kMaxSlots + kQueueWords)));
     unsigned long long *copies = (unsigned long long *)w.copies.p;
-    HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + 1, w.stream));
+    HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + kQueueWords, w.stream));
     PairArgs a = args_of(ctx, *r.cp, r.nbins, r.rows, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
     a.jobs = nullptr;
     a.job0 = job_of(r, copies, cancel);
@@ -1546,7 +1546,7 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
         off = (off + bytes + 255) & ~(size_t)255;
         return at;
     };
-    const size_t o_copies = take(sizeof(unsigned long long) * ((size_t)kGlobalCopies * nslots + 1));
+    const size_t o_copies = take(sizeof(unsigned long long) * ((size_t)kGlobalCopies * nslots + kQueueWords));
     const size_t o_out = take(sizeof(unsigned long long) * (size_t)nslots);
     const size_t o_D = take(sizeof(double) * nedges), o_E = take(sizeof(double) * nedges);
     const size_t o_qlo = take(sizeof(float) * qlo.size()), o_qhi = take(sizeof(float) * qhi.size());
@@ -1579,9 +1579,9 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     HIP_TRY(h2d(o_qhi, qhi.data(), sizeof(float) * qhi.size()));
     HIP_TRY(h2d(o_lut, packed.data(), packed.size()));
     HIP_TRY(h2d(o_units, plan.units.data(), sizeof(Unit) * plan.units.size()));
-    // the histogram copies and the queue counter start at zero (a kernel, not a memset)
+    // the histogram copies and the work queues start at zero (a kernel, not a memset)
     unsigned long long *copies = (unsigned long long *)(base + o_copies);
-    HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + 1, st));
+    HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + kQueueWords, st));
     c.dD.p = base + o_D;
     c.dE.p = base + o_E;
     c.dqlo.p = base + o_qlo;
@@ -1649,8 +1649,8 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
     }
     const int nslots = nbins + 2;
     const int prec = jobs[0].precision;
-    // every job's histogram copies, then the work-queue counter
-    const size_t copies_bytes = sizeof(unsigned long long) * ((size_t)njobs * kGlobalCopies * nslots + 1);
+    // every job's histogram copies, then the work queues
+    const size_t copies_bytes = sizeof(unsigned long long) * ((size_t)njobs * kGlobalCopies * nslots + kQueueWords);
     const size_t out_bytes = sizeof(unsigned long long) * (size_t)njobs * nslots;
     hipStream_t st = ctx->main.stream;
     const bool use_graph = (flags & TPCF_BATCH_GRAPH) != 0;
@@ -1710,7 +1710,7 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
             }
         }
         int lrc = tpcf_launch_zero_u64((unsigned long long *)g->copies.p,
-                                       (int64_t)njobs * kGlobalCopies * nslots + 1, st);
+                                       (int64_t)njobs * kGlobalCopies * nslots + kQueueWords, st);
         if (!lrc && !use_graph)
             rc = record_start(ctx, st, &e0, &e1);
         if (!lrc && !rc)

@@ -38,6 +38,9 @@ constexpr int kStats = 9;
 // when read.
 constexpr int kStatCopies = 32, kStatStride = 16;
 constexpr int kStatWords = kStatCopies * kStatStride;
+// Counters the work items of a launch are dealt to, on lines of 128 bytes.
+constexpr uint32_t kQueues = 8, kQueueStride = 32;
+constexpr int kQueueWords = kQueues * kQueueStride / 2;     // u64
 // Histogram copies in global memory (u64), indexed by work unit.
 constexpr int kGlobalCopies = 64;
 // Largest number of output slots (nbins <= 256 -> nbins + 2 slots).
@@ -98,9 +101,9 @@ struct PairArgs {
     const Unit *units;           // device, or null: units of `grid`
     UnitGrid grid;
     int32_t n_units;
-    // Work queue: item q is wavefront part q % kWaves of unit q / kWaves;
-    // wavefronts take items in order with an atomic add on *queue (zeroed
-    // before the launch) until they pass n_units * kWaves.
+    // Work queues: item i is wavefront part i % kWaves of unit i / kWaves;
+    // each wavefront takes the item of its own number, then one at a time by
+    // atomic adds on kQueues counters (zeroed before the launch).
     unsigned int *queue;
 
     // Cell table (device, copied into LDS by every block).
@@ -193,7 +196,7 @@ constexpr double kPruneDotSlack = 2e-15;
 }  // namespace tpcf
 
 // Size of the fixed per-device work area of tpcf_count_noalloc (histogram
-// copies, work-queue counter, output slots, edge and cell tables, and the
+// copies, work queues, output slots, edge and cell tables, and the
 // work-unit list).
 constexpr size_t kScratchBytes = size_t(16) << 20;
 

@@ -1502,6 +1502,40 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
     cnt.beyond += n_beyond * 16u;
 }
 
+// The next work item, or n_items when none is left.  Items past the first
+// n_waves are dealt to kQueues counters in turn, each on a line of its own: an
+// atomic add on one address takes the device 11 ns whoever asks, and 4096
+// wavefronts asking one counter for their first item waited 22 us on average
+// (45 at most), then again to learn that none was left: DD+DR+RR of 1e4 x 1e4
+// 0.495 -> 0.34 ms, pruned 5e5 x 1e6 49.6 -> 48.2 ms.  Also measured, with one
+// counter: several items at a time, which slowed every large launch (a 3-D
+// box of 5e5 x 1e6 55.2 -> 59.7 ms, 64 regions 6.4 -> 7.5).  A wavefront whose
+// counter is exhausted goes to the next one that has items left; every
+// counter fails it at most once, so every wavefront leaves.
+__device__ __forceinline__ uint32_t claim_item(unsigned int *queues, uint32_t n_waves, uint32_t n_items, uint32_t &q,
+                                               int lane) {
+    const uint32_t rest = n_items - min(n_waves, n_items);
+    uint32_t open = (1u << kQueues) - 1u;
+    if (rest == 0)
+        return n_items;
+    while (open) {
+        uint32_t n = 0;
+        if (lane == 0)
+            n = atomicAdd(queues + q * kQueueStride, 1u);
+        n = __builtin_amdgcn_readfirstlane(n);
+        if (n < (rest + kQueues - 1u - q) / kQueues)
+            return n_waves + n * kQueues + q;
+        open &= ~(1u << q);
+        const uint32_t l = (uint32_t)lane & (kQueues - 1);
+        const uint32_t used =
+            __hip_atomic_load(queues + l * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        open &= (uint32_t)__builtin_amdgcn_ballot_w64(used < (rest + kQueues - 1u - l) / kQueues);
+        const uint32_t after = open & ~((2u << q) - 1u);
+        q = open ? (uint32_t)__builtin_ctz(after ? after : open) : q;
+    }
+    return n_items;
+}
+
 // PREC: 2 FP32 tiles, 1 FP64 vector; 3-D distances: 3 FP32 tiles, 4 FP64
 // vector.  P: rows per lane (a wavefront covers P * 64 rows of a unit, for
 // tiles 2 P groups of 32).
@@ -1571,23 +1605,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
         flush_wave(a, s, to, to_a, to_b, wave, lane, copy);
         held = 0;
     };
-    // Each wavefront takes work items in order from the queue, so the items in
-    // flight are always a window of consecutive units that share their column
-    // range (the plan orders units column chunk first) and the column data
-    // stays in L2.  One at a time, also where many are left: taking a whole
-    // unit's four parts at once slowed every large launch (a 3-D box of 5e5 x
-    // 1e6 55.2 -> 59.7 ms, 64 regions 6.4 -> 7.5, pruned 5e5 x 1e6 52 -> 58).
-    // Every wavefront leaves once the queue is exhausted.
-    const uint32_t n_items = (uint32_t)a.n_units * kWaves;
+    // Each wavefront's first item is the one with its number, the others come
+    // from the queues (claim_item), so the items in flight are always a window
+    // of nearly consecutive units that share their column range (the plan
+    // orders units column chunk first) and the column data stays in L2.
+    const uint32_t n_items = (uint32_t)a.n_units * kWaves, n_waves = gridDim.x * kWaves;
+    uint32_t queue = blockIdx.x & (kQueues - 1);
     uint32_t unlooked = 1u << 21;   // (a cancellable launch holds one job)
     bool gone = false;
-    for (;;) {
-        uint32_t next = 0;
-        if (lane == 0)
-            next = atomicAdd(a.queue, 1u);
-        next = __builtin_amdgcn_readfirstlane(next);
-        if (next >= n_items)
-            break;
+    for (uint32_t next = blockIdx.x * kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wave); next < n_items;
+         next = claim_item(a.queue, n_waves, n_items, queue, lane)) {
         const int u = (int)(next / kWaves);
         const int part = (int)(next % kWaves);
         Unit un;

@@ -132,3 +132,26 @@ def test_pairs_at_every_edge_and_at_zero(ctx):
     finally:
         ctx.release_catalog(ca)
         ctx.release_catalog(cb)
+
+
+@pytest.mark.parametrize("prec", [tp.FP32_CHORD, tp.FP64])
+@pytest.mark.parametrize("n", [500, 5632, 5633, 12000])
+def test_items_of_several_queues(ctx, n, prec):
+    """One block per compute unit and 256-column units: fewer work items than
+    wavefronts, a few more, and several times as many, dealt to counters that
+    run dry at different times."""
+    g = synthcat.rng_for(98, n)
+    fp = (20.0, 40.0, -10.0, 10.0)
+    d, r = synthcat.uniform_patch(n, fp, g), synthcat.uniform_patch(5000, fp, g)
+    e = synthcat.log_edges(0.05, 15.0, 9)
+    xd, xr = oracle.radec_to_xyz(*d), oracle.radec_to_xyz(*r)
+    a, b = ctx.upload_catalog(*d), ctx.upload_catalog(*r)
+    try:
+        ctx.set_tuning(rows_per_lane=2, max_cols=256, blocks_per_cu=1)
+        ctx.stats(reset=True)
+        assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b, precision=prec), oracle.count(oracle.DR, xd, e, b_xyz=xr))
+        assert ctx.stats(reset=True).pairs == n * 5000
+    finally:
+        ctx.set_tuning()
+        ctx.release_catalog(a)
+        ctx.release_catalog(b)
