@@ -899,6 +899,16 @@ __device__ __forceinline__ T lane_load(const T *base, int64_t at, int i) {
     return *(g_p)((gchar_p)(base + at) + (uint32_t)i * (uint32_t)sizeof(T));
 }
 
+// Elements i to i + 3 of a float array, as lane_load (at any multiple of 4
+// bytes).
+typedef float rows4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ rows4 lane_load4(const float *base, int64_t at, int i) {
+    typedef const __attribute__((address_space(1))) char *gchar_p;
+    typedef const __attribute__((address_space(1))) rows4 *g_p;
+    return *(g_p)((gchar_p)(base + at) + (uint32_t)i * 4u);
+}
+
 // A tile's pairs: the lane's column is j0 + jo, its rows start at i0 + io
 // (i0 and j0 wavefront-uniform).
 struct TilePos {
@@ -1046,8 +1056,11 @@ __device__ __forceinline__ void tile_cells(const TileArgs &a, cjob_p job, const 
     }
 }
 
-// Squared distances of one tile from FP32 differences.  Rows past the last
-// (offset ilast) read that one.
+// Squared distances of one tile from FP32 differences.  Four rows a load: with
+// one, the 51 loads of a tile took a compute unit's address unit 816 cycles,
+// 6 us a tile where every wavefront had one (DR of 1e4 x 1e4), and 12 to 20 %
+// of all wavefront time from 1e4 to 1.5e5 points.  Where rows are missing,
+// those past the last (offset ilast) read that one.
 __device__ __forceinline__ void tile_diffs(const TileArgs &a, cjob_p job, const TilePos &t, int ilast,
                                            float (&q)[16]) {
     int io = t.io;
@@ -1055,6 +1068,23 @@ __device__ __forceinline__ void tile_diffs(const TileArgs &a, cjob_p job, const 
     const cjob_p p = fresh(job);
     const float xj = lane_load(p->bx32, t.j0, t.jo), yj = lane_load(p->by32, t.j0, t.jo),
                 zj = lane_load(p->bz32, t.j0, t.jo);
+    if (__builtin_amdgcn_ballot_w64(io + 15 > ilast) == 0) {
+#pragma unroll
+        for (int b = 0; b < 16; b += 8) {
+            rows4 x[2], y[2], z[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                x[h] = lane_load4(p->ax32, t.i0, io + b + 4 * h);
+                y[h] = lane_load4(p->ay32, t.i0, io + b + 4 * h);
+                z[h] = lane_load4(p->az32, t.i0, io + b + 4 * h);
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                q[b + r] = diff_q(x[r >> 2][r & 3], y[r >> 2][r & 3], z[r >> 2][r & 3], xj, yj, zj, a.q_exp2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int i = min(io + r, ilast);
