@@ -1219,19 +1219,22 @@ __device__ __forceinline__ bool far_enough(const float (&q)[16], float e, uint32
     return __builtin_amdgcn_ballot_w64(!(qmin * kTileFar > e) && w) == 0;
 }
 
-// Columns [j, j + 64) of the three coordinate arrays into the wavefront's
-// LDS buffer (x, y, z of 64 floats at byte address dst) with loads that write
-// LDS directly: the copy in flight takes no registers.  Lanes past the last
-// column (last) read that one.
-__device__ __forceinline__ void stage_columns(const float *bx, const float *by, const float *bz, int j, int last,
-                                              int lane, uint32_t dst) {
+// Columns [j, j + 64) of a catalog (x at b, y and z each `stride` elements
+// further) into the wavefront's LDS buffer (x, y, z of 64 floats at byte
+// address dst), straight from memory: the copy in flight takes no registers.
+// Buffer loads, whose lane offset never changes and whose range makes columns
+// from `end` on read as 0: with global loads each pass of 64 columns formed
+// three 64-bit addresses a lane from three kept pointers.
+__device__ __forceinline__ void stage_columns(const float *b, int64_t stride, int j, int end, int lane,
+                                              uint32_t dst) {
     typedef __attribute__((address_space(3))) void *lds_p;
-    typedef __attribute__((address_space(1))) void *glb_p;
-    typedef const __attribute__((address_space(1))) char *gchar_p;
-    const uint32_t at = 4u * (uint32_t)min(lane, last - j);     // a scalar base and 32 bits a lane
-    __builtin_amdgcn_global_load_lds((glb_p)((gchar_p)(bx + j) + at), (lds_p)(uintptr_t)dst, 4, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_p)((gchar_p)(by + j) + at), (lds_p)(uintptr_t)(dst + 256), 4, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_p)((gchar_p)(bz + j) + at), (lds_p)(uintptr_t)(dst + 512), 4, 0, 0);
+    const uint32_t bytes = 4u * (uint32_t)min(end - j, 64);
+    asm volatile("" : "+v"(lane), "+s"(dst));       // (addresses formed here, not kept)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const auto r = __builtin_amdgcn_make_buffer_rsrc((void *)(b + c * stride + j), 0, bytes, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_p)(uintptr_t)(dst + 256u * c), 4, 4 * lane, 0, 0, 0);
+    }
 }
 
 // nb and histogram row (~0 for a lane whose column does not exist) of the
@@ -1372,8 +1375,12 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
     const int nr = ie - ib;
     const uint32_t rows_ok = low_bits<G>(nr >> 5), rows_any = low_bits<G>((nr + 31) >> 5);
     uint32_t n_beyond = 0;
-    const float *bx = job->bx32, *by = job->by32, *bz = job->bz32;
-    asm volatile("" : "+s"(bx), "+s"(by), "+s"(bz));    // (else reloaded from constant memory every pass)
+    // (registers of their own: else every pass reloads the eight that the job's
+    // pointers were read into)
+    const float *b;
+    asm volatile("s_mov_b64 %0, %1" : "=s"(b) : "s"(job->bx32));
+    uint32_t stride = (uint32_t)(job->by32 - job->bx32);
+    asm volatile("" : "+s"(stride));
     // the next 64 columns are on their way into LDS while these are used
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t stage = s.stage_addr + wave * (uint32_t)kStageWaveBytes;
@@ -1383,7 +1390,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
     int j = j0, jn;
     if (PRUNE)
         j = max(j0, (b0 + __builtin_ctzll(left)) << 6);
-    stage_columns(bx, by, bz, j, j1 - 1, lane, stage);
+    stage_columns(b, stride, j, j1, lane, stage);
     for (; j < j1; j = jn) {
         // this pass's columns end at jl (pruned launches: with their block),
         // the next one's start at jn
@@ -1420,7 +1427,7 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
         // LDS read) and the tiles of one pass are still to come
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(base), "+v"(width) : : "memory");
         if (jn < j1)
-            stage_columns(bx, by, bz, jn, j1 - 1, lane, stage);
+            stage_columns(b, stride, jn, j1, lane, stage);
         uint32_t n_in = 0;      // tiles in one slot: columns 0-31, columns 32-63 (<< 16)
 #pragma unroll 1
         for (int h = 0; h < 64; h += 32) {
