@@ -11,12 +11,13 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <map>
 #include <memory>
 #include <string>
+#include <system_error>
 #include <thread>
-#include <tuple>
 #include <vector>
 
 #include "edges.h"
@@ -302,27 +303,6 @@ void drop_graphs(tpcf_ctx *ctx) {
     ctx->graphs.clear();
 }
 
-// Bound on the exact | |v|^2 - 1 | of FP64 vectors: the largest computed
-// deviation plus the rounding of computing it (a few units of 2^-53).
-double norm_bound(const double *x, const double *y, const double *z, int64_t n, bool *finite) {
-    double m = 0.0;
-    *finite = true;
-    for (int64_t i = 0; i < n; ++i) {
-        if (!isfinite(x[i]) || !isfinite(y[i]) || !isfinite(z[i])) {
-            *finite = false;
-            return HUGE_VAL;
-        }
-        double t = x[i] * x[i];
-        double u = y[i] * y[i];
-        double v = z[i] * z[i];
-        double r = (t + u) + v;
-        double dev = fabs(r - 1.0);
-        if (dev > m)
-            m = dev;
-    }
-    return m + 4.0 * ldexp(1.0, -53);
-}
-
 // Spatially coherent storage order: sort the points along a Morton (Z-order)
 // curve of their unit vectors, 21 bits per coordinate.  Neighbouring rows are
 // then close on the sky, so the 64 lanes of a wavefront see nearly the same
@@ -346,70 +326,178 @@ uint64_t quant21(double c, double lo = -1.0, double hi = 1.0) {
     return (uint64_t)t;
 }
 
-// Host threads for catalog preparation: large catalogs are split into
-// contiguous chunks, at most 16, none smaller than 32768 points.  Every
-// per-point result is computed exactly as in a serial loop, so the stored
-// catalog does not depend on the thread count.
-int host_threads(int64_t n) {
+// Host threads for catalog preparation: at most 16, none with less than
+// `grain` points (starting one takes 15 us, preparing 4096 points 0.3 ms).
+// Every per-point result is computed exactly as in a serial loop, so the
+// stored catalog does not depend on the thread count.
+int host_threads(int64_t n, int64_t grain = 4096) {
     const int64_t hw = std::max<int64_t>(1, (int64_t)std::thread::hardware_concurrency());
-    return (int)std::max<int64_t>(1, std::min<int64_t>({hw, 16, n / 32768}));
+    return (int)std::max<int64_t>(1, std::min<int64_t>({hw, 16, n / grain}));
 }
 
-template <typename F>
-void parallel_chunks(int64_t n, int nt, F fn) {
-    if (nt <= 1) {
-        fn(0, 0, n);
-        return;
+// A few threads that work through common phases.
+struct Team {
+    int size = 0;
+    std::atomic<int> started{0}, waiting{0}, phase{0};
+
+    // Every member has come this far.
+    void sync() {
+        const int p = phase.load(std::memory_order_acquire);
+        if (waiting.fetch_add(1, std::memory_order_acq_rel) + 1 == size) {
+            waiting.store(0, std::memory_order_relaxed);
+            phase.store(p + 1, std::memory_order_release);
+        } else {
+            while (phase.load(std::memory_order_acquire) == p)
+                std::this_thread::yield();
+        }
     }
+};
+
+// fn(team, t) on this thread (t = 0) and on up to nt - 1 others; fewer where
+// they cannot be started.
+template <typename F>
+void run_team(int nt, F fn) {
+    Team team;
     std::vector<std::thread> th;
     th.reserve((size_t)nt);
-    for (int t = 0; t < nt; ++t)
-        th.emplace_back(fn, t, n * t / nt, n * (t + 1) / nt);
+    for (int t = 1; t < nt; ++t) {
+        try {
+            th.emplace_back([&team, &fn, t] {
+                while (!team.started.load(std::memory_order_acquire))
+                    std::this_thread::yield();
+                fn(team, t);
+            });
+        } catch (const std::system_error &) {
+            break;
+        }
+    }
+    team.size = (int)th.size() + 1;
+    team.started.store(1, std::memory_order_release);
+    fn(team, 0);
     for (auto &t : th)
         t.join();
 }
 
-// Stored order: Morton order of the unit vectors, grouped by region first
-// when labels are given (so each region is a contiguous range of rows).  The
-// key ends in the point index, so it is a strict total order: chunks sorted
-// on their own and merged pairwise give the one sorted sequence.
-std::vector<int64_t> morton_order(const double *x, const double *y, const double *z, int64_t n,
-                                  const int32_t *region = nullptr, double lo = -1.0, double hi = 1.0) {
-    using Key = std::tuple<int32_t, uint64_t, int64_t>;
-    std::vector<Key> k((size_t)n), tmp;
-    const int nt = host_threads(n);
-    std::vector<int64_t> bound((size_t)nt + 1);
-    for (int t = 0; t <= nt; ++t)
-        bound[t] = n * t / nt;
-    parallel_chunks(n, nt, [&](int, int64_t b, int64_t e) {
-        for (int64_t i = b; i < e; ++i)
-            k[i] = std::make_tuple(region ? region[i] : 0,
-                                   spread3(quant21(x[i], lo, hi)) | spread3(quant21(y[i], lo, hi)) << 1 |
-                                       spread3(quant21(z[i], lo, hi)) << 2,
-                                   i);
-        std::sort(k.begin() + b, k.begin() + e);
-    });
-    if (nt > 1)
-        tmp.resize((size_t)n);
-    // merge rounds: runs of w chunks become runs of 2w chunks
-    for (int w = 1; w < nt; w *= 2) {
-        std::vector<std::thread> th;
-        for (int t = 0; t < nt; t += 2 * w) {
-            const int64_t b = bound[t], m = bound[std::min(t + w, nt)], e = bound[std::min(t + 2 * w, nt)];
-            th.emplace_back([&, b, m, e] {
-                std::merge(k.begin() + b, k.begin() + m, k.begin() + m, k.begin() + e, tmp.begin() + b);
-            });
+// fn(begin, end) for equal chunks of [0, n), one per thread.
+template <typename F>
+void parallel_chunks(int64_t n, int nt, F fn) {
+    run_team(nt, [&](Team &team, int t) { fn(n * t / team.size, n * (t + 1) / team.size); });
+}
+
+// Bound on the exact | |v|^2 - 1 | of FP64 vectors: the largest computed
+// deviation plus the rounding of computing it (a few units of 2^-53).
+double norm_bound(const double *x, const double *y, const double *z, int64_t n, bool *finite) {
+    std::atomic<uint64_t> most{0};       // (a non-negative double's bits order like its value)
+    std::atomic<bool> all{true};
+    parallel_chunks(n, host_threads(n, 1 << 17), [&](int64_t b, int64_t e) {
+        double m = 0.0;
+        for (int64_t i = b; i < e; ++i) {
+            if (!isfinite(x[i]) || !isfinite(y[i]) || !isfinite(z[i])) {
+                all = false;
+                return;
+            }
+            double t = x[i] * x[i];
+            double u = y[i] * y[i];
+            double v = z[i] * z[i];
+            double r = (t + u) + v;
+            double dev = fabs(r - 1.0);
+            if (dev > m)
+                m = dev;
         }
-        for (auto &t : th)
-            t.join();
-        k.swap(tmp);
-    }
-    std::vector<int64_t> order((size_t)n);
-    parallel_chunks(n, nt, [&](int, int64_t b, int64_t e) {
-        for (int64_t i = b; i < e; ++i)
-            order[i] = std::get<2>(k[i]);
+        uint64_t bits, seen = most.load();
+        memcpy(&bits, &m, sizeof bits);
+        while (seen < bits && !most.compare_exchange_weak(seen, bits)) {
+        }
     });
-    return order;
+    *finite = all;
+    if (!all)
+        return HUGE_VAL;
+    const uint64_t bits = most.load();
+    double m;
+    memcpy(&m, &bits, sizeof m);
+    return m + 4.0 * ldexp(1.0, -53);
+}
+
+// A point's sort key: its place on the Morton curve and its region.
+struct SortKey {
+    uint64_t at;
+    uint32_t region, i;
+    bool operator<(const SortKey &o) const { return region != o.region ? region < o.region : at < o.at; }
+};
+
+// k[0, n) by (region, place), points of equal keys in their order: a radix
+// sort from the lowest digit, 11 bits a pass, without the passes whose digit
+// is the same everywhere.  (A comparison sort of these took 60 ns a point,
+// two thirds of an upload.)
+void radix_sort(SortKey *k, SortKey *tmp, int64_t n) {
+    constexpr int kBits = 11, kDigits = 6, kRadix = 1 << kBits;     // 63 bits of the curve
+    static_assert(TPCF_MAX_REGIONS <= kRadix, "a region is one digit");
+    uint32_t count[(kDigits + 1) * kRadix] = {};
+    auto digit = [](const SortKey &e, int d) {
+        return d < kDigits ? (uint32_t)(e.at >> (kBits * d)) & (kRadix - 1)
+                           : e.region;
+    };
+    for (int64_t i = 0; i < n; ++i)
+        for (int d = 0; d < kDigits + 1; ++d)
+            ++count[d * kRadix + digit(k[i], d)];
+    SortKey *from = k, *to = tmp;
+    for (int d = 0; d < kDigits + 1; ++d) {
+        uint32_t *c = count + d * kRadix;
+        if (n == 0 || c[digit(k[0], d)] == (uint32_t)n)
+            continue;
+        uint32_t at = 0;
+        for (int v = 0; v < kRadix; ++v) {
+            const uint32_t m = c[v];
+            c[v] = at;
+            at += m;
+        }
+        for (int64_t i = 0; i < n; ++i)
+            to[c[digit(from[i], d)]++] = from[i];
+        std::swap(from, to);
+    }
+    if (from != k)
+        std::copy(from, from + n, k);
+}
+
+// Stored order: Morton order of the unit vectors, grouped by region first
+// when labels are given (so each region is a contiguous range of rows), equal
+// keys by point index: chunks sorted on their own and merged pairwise, both
+// stably, give one sequence whatever the number of chunks.  The coordinates
+// in that order go to h64 and h32 (x, y, z of n each).
+void store_in_order(const double *x, const double *y, const double *z, int64_t n, const int32_t *region, double lo,
+                    double hi, int64_t *order, double *h64, float *h32) {
+    const std::unique_ptr<SortKey[]> a(new SortKey[(size_t)n]), b(new SortKey[(size_t)n]);
+    run_team(host_threads(n), [&](Team &team, int t) {
+        const int nt = team.size;
+        auto bound = [&](int c) { return n * std::min(c, nt) / nt; };
+        const int64_t first = bound(t), last = bound(t + 1);
+        SortKey *k = a.get(), *to = b.get();
+        for (int64_t i = first; i < last; ++i) {
+            k[i].at = spread3(quant21(x[i], lo, hi)) | spread3(quant21(y[i], lo, hi)) << 1 |
+                      spread3(quant21(z[i], lo, hi)) << 2;
+            k[i].region = region ? (uint32_t)region[i] : 0u;
+            k[i].i = (uint32_t)i;
+        }
+        radix_sort(k + first, to + first, last - first);
+        // runs of w chunks become runs of 2 w chunks
+        for (int w = 1; w < nt; w *= 2) {
+            team.sync();
+            if (t % (2 * w) == 0)
+                std::merge(k + bound(t), k + bound(t + w), k + bound(t + w), k + bound(t + 2 * w), to + bound(t));
+            std::swap(k, to);
+        }
+        team.sync();
+        for (int64_t r = first; r < last; ++r) {
+            const int64_t i = k[r].i;
+            order[r] = i;
+            h64[r] = x[i];
+            h64[n + r] = y[i];
+            h64[2 * n + r] = z[i];
+            h32[r] = (float)x[i];
+            h32[n + r] = (float)y[i];
+            h32[2 * n + r] = (float)z[i];
+        }
+    });
 }
 
 int add_catalog(tpcf_ctx *ctx, const double *x, const double *y, const double *z, int64_t n,
@@ -462,7 +550,6 @@ int add_catalog(tpcf_ctx *ctx, const double *x, const double *y, const double *z
         }
     }
     TRY(set_device(ctx));
-    c.order = morton_order(x, y, z, n, region, lo, hi);
     if (region) {
         c.nreg = nreg;
         c.reg_start.assign((size_t)nreg + 1, 0);
@@ -472,19 +559,12 @@ int add_catalog(tpcf_ctx *ctx, const double *x, const double *y, const double *z
             c.reg_start[(size_t)r + 1] += c.reg_start[(size_t)r];
     }
     size_t alloc_n = (size_t)(n > 0 ? n : 1);
-    std::vector<double> h64(3 * alloc_n, 0.0);
-    std::vector<float> h32(3 * alloc_n, 0.0f);
-    parallel_chunks(n, host_threads(n), [&](int, int64_t b, int64_t e) {
-        for (int64_t r = b; r < e; ++r) {
-            const int64_t i = c.order[r];
-            h64[r] = x[i];
-            h64[alloc_n + r] = y[i];
-            h64[2 * alloc_n + r] = z[i];
-            h32[r] = (float)x[i];
-            h32[alloc_n + r] = (float)y[i];
-            h32[2 * alloc_n + r] = (float)z[i];
-        }
-    });
+    const std::unique_ptr<double[]> h64(new double[3 * alloc_n]);
+    const std::unique_ptr<float[]> h32(new float[3 * alloc_n]);
+    std::fill(h64.get(), h64.get() + (n > 0 ? 0 : 3), 0.0);
+    std::fill(h32.get(), h32.get() + (n > 0 ? 0 : 3), 0.0f);
+    c.order.resize((size_t)n);
+    store_in_order(x, y, z, n, region, lo, hi, c.order.data(), h64.get(), h32.get());
     c.bytes64 = sizeof(double) * 3 * alloc_n;
     c.bytes32 = sizeof(float) * 3 * alloc_n;
     TRY(dev_alloc(ctx->mem, (void **)&c.d64, c.bytes64));
@@ -494,9 +574,9 @@ int add_catalog(tpcf_ctx *ctx, const double *x, const double *y, const double *z
         return rc;
     }
     // blocking copies: the host vectors go out of scope on return
-    hipError_t e = hipMemcpy(c.d64, h64.data(), c.bytes64, hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(c.d64, h64.get(), c.bytes64, hipMemcpyHostToDevice);
     if (e == hipSuccess)
-        e = hipMemcpy(c.d32, h32.data(), c.bytes32, hipMemcpyHostToDevice);
+        e = hipMemcpy(c.d32, h32.get(), c.bytes32, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         dev_free(ctx->mem, c.d64, c.bytes64);
         dev_free(ctx->mem, c.d32, c.bytes32);
@@ -1271,12 +1351,14 @@ int tpcf_upload_catalog_regions(tpcf_ctx *ctx, const double *ra_deg, const doubl
     if (n > 0 && (!ra_deg || !dec_deg))
         return fail(TPCF_E_INVALID, "ra_deg/dec_deg is NULL");
     const double deg = M_PI / 180.0;
-    for (int64_t i = 0; i < n; ++i)
-        if (!isfinite(ra_deg[i]) || !isfinite(dec_deg[i]))
-            return fail(TPCF_E_INVALID, "ra/dec must be finite");
-    std::vector<double> x((size_t)n), y((size_t)n), z((size_t)n);
-    parallel_chunks(n, host_threads(n), [&](int, int64_t b0, int64_t e0) {
+    const std::unique_ptr<double[]> x(new double[(size_t)n]), y(new double[(size_t)n]), z(new double[(size_t)n]);
+    std::atomic<bool> finite{true};
+    parallel_chunks(n, host_threads(n), [&](int64_t b0, int64_t e0) {
         for (int64_t i = b0; i < e0; ++i) {
+            if (!isfinite(ra_deg[i]) || !isfinite(dec_deg[i])) {
+                finite = false;
+                return;
+            }
             double a = ra_deg[i] * deg;
             double b = dec_deg[i] * deg;
             x[i] = cos(b) * cos(a);
@@ -1284,7 +1366,9 @@ int tpcf_upload_catalog_regions(tpcf_ctx *ctx, const double *ra_deg, const doubl
             z[i] = sin(b);
         }
     });
-    return add_catalog(ctx, x.data(), y.data(), z.data(), n, out_cat, region, region ? nreg : 0);
+    if (!finite)
+        return fail(TPCF_E_INVALID, "ra/dec must be finite");
+    return add_catalog(ctx, x.get(), y.get(), z.get(), n, out_cat, region, region ? nreg : 0);
 }
 
 int tpcf_upload_catalog(tpcf_ctx *ctx, const double *ra_deg, const double *dec_deg, int64_t n,
