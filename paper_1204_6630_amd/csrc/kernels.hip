@@ -1555,7 +1555,19 @@ __device__ __forceinline__ uint32_t claim_item(unsigned int *queues, uint32_t n_
     uint32_t open = (1u << kQueues) - 1u;
     if (rest == 0)
         return n_items;
+    // where most wavefronts have no second item, they look before they ask
+    bool look = rest < n_waves;
     while (open) {
+        if (look) {
+            const uint32_t l = (uint32_t)lane & (kQueues - 1);
+            const uint32_t used =
+                __hip_atomic_load(queues + l * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            open &= (uint32_t)__builtin_amdgcn_ballot_w64(used < (rest + kQueues - 1u - l) / kQueues);
+            if (!open)
+                break;
+            const uint32_t from = open & ~((1u << q) - 1u);     // this one or the next with items left
+            q = (uint32_t)__builtin_ctz(from ? from : open);
+        }
         uint32_t n = 0;
         if (lane == 0)
             n = atomicAdd(queues + q * kQueueStride, 1u);
@@ -1563,12 +1575,7 @@ __device__ __forceinline__ uint32_t claim_item(unsigned int *queues, uint32_t n_
         if (n < (rest + kQueues - 1u - q) / kQueues)
             return n_waves + n * kQueues + q;
         open &= ~(1u << q);
-        const uint32_t l = (uint32_t)lane & (kQueues - 1);
-        const uint32_t used =
-            __hip_atomic_load(queues + l * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        open &= (uint32_t)__builtin_amdgcn_ballot_w64(used < (rest + kQueues - 1u - l) / kQueues);
-        const uint32_t after = open & ~((2u << q) - 1u);
-        q = open ? (uint32_t)__builtin_ctz(after ? after : open) : q;
+        look = true;
     }
     return n_items;
 }
