@@ -179,7 +179,8 @@ struct Plan {
 struct Workspace {
     hipStream_t stream = nullptr;
     bool own = false;
-    DevBuf copies;   // kGlobalCopies x nslots u64
+    DevBuf copies;   // kGlobalCopies x nslots u64, work queues
+    bool clear = false;     // `copies` is all zero whenever the stream is idle
     DevBuf out;      // kMaxSlots u64
     DevBuf stats;    // kStats u64
     DevBuf touch;    // nreg x kGlobalCopies x nslots u64 (jackknife regions)
@@ -240,6 +241,7 @@ struct tpcf_ctx {
     // pinned result buffers of retired jobs, reused by later submits:
     // hipHostFree would wait for the whole device at every completion
     std::vector<uint64_t *> pinned_free;
+    uint64_t *hout = nullptr;            // pinned, kMaxSlots: results of tpcf_count
     bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
     uint64_t pairs_since_reset = 0;
@@ -1176,10 +1178,21 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
         touch = (unsigned long long *)w.touch.p;
         HIP_TRY((hipError_t)tpcf_launch_zero_u64(touch, (int64_t)(per * (size_t)nreg), w.stream));
     }
-    // the histogram copies, then the work queues, zeroed together
-    TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * ((size_t)kGlobalCopies * kMaxSlots + kQueueWords)));
+    // the histogram copies, then the work queues; zeroed once, then by every
+    // launch's reduction for the next one (a clearing launch of its own took
+    // 5 us, of 60 for DD of 1e3 points)
+    const size_t words = (size_t)kGlobalCopies * kMaxSlots + kQueueWords;
+    TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * words));
     unsigned long long *copies = (unsigned long long *)w.copies.p;
-    HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)kGlobalCopies * nslots + kQueueWords, w.stream));
+    bool clear = w.clear;
+    w.clear = false;        // until the reduction is enqueued
+    if (!clear) {
+        HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)words, w.stream));
+        // (a capturing stream has not run it yet)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(w.stream, &capture));
+        clear = capture == hipStreamCaptureStatusNone;
+    }
     PairArgs a = args_of(ctx, *r.cp, r.nbins, r.rows, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
     a.jobs = nullptr;
     a.job0 = job_of(r, copies, cancel);
@@ -1197,7 +1210,8 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
     if (lrc)
         return fail(TPCF_E_HIP, std::string("pair kernel launch: ") + hipGetErrorString((hipError_t)lrc));
     TRY(record_stop(ctx, w.stream, e0, e1));
-    lrc = tpcf_launch_reduce_copies(copies, nslots, 1, d_out, w.stream);
+    lrc = tpcf_launch_reduce_clear(copies, nslots, kQueueWords, d_out, w.stream);
+    w.clear = clear && lrc == 0;
     if (lrc == 0 && touch)
         lrc = tpcf_launch_reduce_copies(touch, nslots, nreg, d_touch, w.stream);
     if (lrc)
@@ -1319,6 +1333,8 @@ int tpcf_close(tpcf_ctx *ctx) {
     for (uint64_t *p : ctx->pinned_free)
         (void)hipHostFree(p);
     ctx->pinned_free.clear();
+    if (ctx->hout)
+        (void)hipHostFree(ctx->hout);
     drop_graphs(ctx);
     for (auto &kv : ctx->cats) {
         if (kv.second.owns64)
@@ -1543,12 +1559,13 @@ int tpcf_count(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, const doub
             return TPCF_OK;
         }
     }
+    // the reduction writes the counts to host memory
     Workspace &w = ctx->main;
-    TRY(w.out.ensure(ctx->mem, sizeof(unsigned long long) * kMaxSlots));
-    TRY(launch_one(ctx, w, r, (unsigned long long *)w.out.p, nullptr));
-    std::vector<uint64_t> h((size_t)nslots);
-    HIP_TRY(hipMemcpyAsync(h.data(), w.out.p, sizeof(uint64_t) * h.size(), hipMemcpyDeviceToHost, w.stream));
+    if (!ctx->hout)
+        HIP_TRY(hipHostMalloc((void **)&ctx->hout, sizeof(uint64_t) * kMaxSlots, hipHostMallocCoherent));
+    TRY(launch_one(ctx, w, r, (unsigned long long *)ctx->hout, nullptr));
     HIP_TRY(hipStreamSynchronize(w.stream));
+    const std::vector<uint64_t> h(ctx->hout, ctx->hout + nslots);
     TRY(check_total(h.data(), nslots, r.pairs));
     if (!r.cache_key.empty())
         ctx->result_cache[r.cache_key] = h;

@@ -211,8 +211,12 @@ int tpcf_launch_pairs(const tpcf::PairArgs *args, int precision, void *stream);
 int tpcf_launch_zero_u64(unsigned long long *p, int64_t n, void *stream);
 // Sum the kGlobalCopies copies of each of njobs histograms (contiguous,
 // njobs x kGlobalCopies x nslots) into out (njobs x nslots).
-int tpcf_launch_reduce_copies(const unsigned long long *copies, int32_t nslots, int32_t njobs,
+int tpcf_launch_reduce_copies(unsigned long long *copies, int32_t nslots, int32_t njobs,
                               unsigned long long *out, void *stream);
+// The same for one histogram, leaving its copies and the queue_words after
+// them zero.
+int tpcf_launch_reduce_clear(unsigned long long *copies, int32_t nslots, int32_t queue_words,
+                             unsigned long long *out, void *stream);
 // FP32 copies of an FP64 SoA catalog, or (given32 non-null) a check that
 // given32 holds them; check_out[0] receives the largest | |v|^2 - 1 | (bits
 // of a double, +inf for a non-finite value), check_out[1] a non-zero value

@@ -1781,16 +1781,26 @@ __global__ void zero_u64_kernel(unsigned long long *p, int64_t n) {
         p[i] = 0ull;
 }
 
-// One block per job: sum its kGlobalCopies histogram copies.
-__global__ void reduce_copies_kernel(const unsigned long long *copies, int32_t nslots,
-                                     unsigned long long *out) {
-    const unsigned long long *c = copies + (size_t)blockIdx.x * kGlobalCopies * nslots;
+// One block per job: sum its kGlobalCopies histogram copies.  CLEAR (one job):
+// also leave them, and the `queue` words after them, zero for the next launch.
+template <bool CLEAR>
+__global__ void reduce_copies_kernel(unsigned long long *copies, int32_t nslots, unsigned long long *out,
+                                     int32_t queue) {
+    unsigned long long *c = copies + (size_t)blockIdx.x * kGlobalCopies * nslots;
     for (int s = threadIdx.x; s < nslots; s += blockDim.x) {
         unsigned long long acc = 0;
+#pragma unroll 16
         for (int g = 0; g < kGlobalCopies; ++g)
             acc += c[(size_t)g * nslots + s];
         out[(size_t)blockIdx.x * nslots + s] = acc;
+        if (CLEAR)
+#pragma unroll 16
+            for (int g = 0; g < kGlobalCopies; ++g)
+                c[(size_t)g * nslots + s] = 0;
     }
+    if (CLEAR)
+        for (int i = threadIdx.x; i < queue; i += blockDim.x)
+            copies[(size_t)kGlobalCopies * nslots + i] = 0;
 }
 
 // FP32 copies (round to nearest) of an FP64 SoA block of 3n values, and the
@@ -1950,12 +1960,19 @@ extern "C" int tpcf_launch_zero_u64(unsigned long long *p, int64_t n, void *stre
     return (int)hipGetLastError();
 }
 
-extern "C" int tpcf_launch_reduce_copies(const unsigned long long *copies, int32_t nslots,
-                                         int32_t njobs, unsigned long long *out, void *stream) {
+extern "C" int tpcf_launch_reduce_copies(unsigned long long *copies, int32_t nslots, int32_t njobs,
+                                         unsigned long long *out, void *stream) {
     if (njobs <= 0)
         return 0;
-    hipLaunchKernelGGL(reduce_copies_kernel, dim3((unsigned)njobs), dim3(256), 0, (hipStream_t)stream,
-                       copies, nslots, out);
+    hipLaunchKernelGGL(reduce_copies_kernel<false>, dim3((unsigned)njobs), dim3(256), 0, (hipStream_t)stream,
+                       copies, nslots, out, 0);
+    return (int)hipGetLastError();
+}
+
+extern "C" int tpcf_launch_reduce_clear(unsigned long long *copies, int32_t nslots, int32_t queue_words,
+                                        unsigned long long *out, void *stream) {
+    hipLaunchKernelGGL(reduce_copies_kernel<true>, dim3(1), dim3(256), 0, (hipStream_t)stream, copies, nslots, out,
+                       queue_words);
     return (int)hipGetLastError();
 }
 

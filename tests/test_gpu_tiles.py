@@ -155,3 +155,23 @@ def test_items_of_several_queues(ctx, n, prec):
         ctx.set_tuning()
         ctx.release_catalog(a)
         ctx.release_catalog(b)
+
+
+def test_launches_leave_nothing_behind(ctx):
+    """Requests of different slot counts, empty ones and repeated ones after
+    each other on one stream: each finds its histogram copies and queues
+    cleared by the one before."""
+    g = synthcat.rng_for(98, 77)
+    fp = (20.0, 30.0, -5.0, 5.0)
+    d = synthcat.uniform_patch(1500, fp, g)
+    xd = oracle.radec_to_xyz(*d)
+    a = ctx.upload_catalog(*d)
+    try:
+        for nbins in (256, 3, 40, 1, 126, 256):
+            e = np.linspace(0.1, 9.0, nbins + 1)
+            want = oracle.count(oracle.DD, xd, e)
+            assert not ctx.count(tp.DD, a, e, row_begin=7, row_end=7).any()
+            for prec in (tp.FP32_CHORD, tp.FP64, tp.FP32_CHORD):
+                assert np.array_equal(ctx.count(tp.DD, a, e, precision=prec), want)
+    finally:
+        ctx.release_catalog(a)
