@@ -68,14 +68,17 @@ struct Tuning {
     int prune = 0;           // 1: exact tile pruning
 };
 
-// Rows per lane of a launch over `pairs` pairs: 4, but 2 for FP32 tiles below
-// 2^22 pairs, where one item of 256 rows outlasts the rest of the launch (DD
-// of 1e3 points 75 -> 64 us; DD+DR+RR of 1e4 x 1e4 the other way, 488
-// against 624 us).
+// Rows per lane of a launch over `pairs` pairs: 4, but 2 for FP32 launches
+// below 2^23 pairs and 1 below 2^20, where a wavefront has one item at most
+// and the launch lasts as long as the slowest (DD of 4000 points: 4 rows 57.7
+// us, 2 rows 46.6; of 1400: 55, 46 and, with 1 row, 37.0; of 2000: 2 rows
+// 45.2.  DD+DR+RR of 1e4 x 1e4 the other way: 4 rows 222 us, 2 rows 317).
 int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs) {
     if (t.rows_per_lane)
         return t.rows_per_lane;
-    return precision == TPCF_FP32_CHORD && pairs < ((uint64_t)1 << 22) ? 2 : 4;
+    if (precision != TPCF_FP32_CHORD || pairs >= (uint64_t)1 << 23)
+        return 4;
+    return pairs < (uint64_t)1 << 20 && !t.prune ? 1 : 2;
 }
 
 // Largest column chunk: 2048, and 4096 with pruning, where one test covers

@@ -153,7 +153,7 @@ struct PairArgs {
 
     // Per-wave LDS histogram copies (layout [slot][copy]).
     int32_t hist_copies;         // 32, 16, 8 or 4
-    int32_t rows_per_lane;       // 2 or 4: a unit spans kWaves * 64 * rows_per_lane rows
+    int32_t rows_per_lane;       // 2 or 4 (FP32 without pruning: or 1): a unit spans kWaves * 64 * rows_per_lane rows
     int32_t blocks_per_cu;       // grid = CUs x this (0: the blocks that fit at once)
 
     unsigned long long *stats;   // kStatCopies times kStats words: [two-slot steps, flagged, exact, skipped

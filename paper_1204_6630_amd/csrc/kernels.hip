@@ -50,7 +50,6 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 // of a wavefront reads the same j, so these become scalar loads into SGPRs.
 typedef const __attribute__((address_space(4))) double *cdouble_p;
 typedef const __attribute__((address_space(4))) uint32_t *cword_p;
-typedef const __attribute__((address_space(1))) double *gdouble_p;
 
 // Unit and job descriptors are read-only and wavefront-uniform as well: copy
 // them word by word through the constant address space (scalar loads).
@@ -68,12 +67,6 @@ __device__ __forceinline__ T load_uniform(const T *p) {
 
 // Clamp into [lo, hi] in one instruction (all operands in VGPRs: gfx9 VOP3
 // reads at most one SGPR, which keeps the compiler from forming v_med3).
-__device__ __forceinline__ uint32_t med3_u32(uint32_t x, uint32_t lo, uint32_t hi) {
-    uint32_t r;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "v"(hi));
-    return r;
-}
-
 __device__ __forceinline__ int32_t med3_i32(int32_t x, int32_t lo, int32_t hi) {
     int32_t r;
     asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "v"(hi));
@@ -271,9 +264,8 @@ __device__ void flush_wave(const PairArgs &a, const Smem &s, unsigned long long 
     }
 }
 
-// A flagged entry: edge k alone is undecided in the cell (its FP32 band,
-// one 8-byte LDS read, settles q outside [qlo_k, qhi_k); inside it the exact
-// FP64 rule compares d with D_k), or several are (the rule counts them).
+// A flagged entry: edge k alone is undecided in the cell (e against E_k, a tie
+// by the rule), or several are (the rule counts them).
 template <bool LUT8>
 __device__ __forceinline__ uint32_t resolve_fp64(uint32_t ent, uint32_t flag, double e, double d,
                                                  const Smem &s, const PairArgs &a,
@@ -345,14 +337,8 @@ struct Consts {
     uint32_t beyond;        // PairArgs::beyond_key (VGPR copy)
 };
 
-// LDS address of the cell-table entry of an FP32 key (the bit pattern of q)
-// and of an FP64 key (the high word of e; arithmetic shift, so e < 0 lands
-// in the bottom cell).
-template <bool LUT8>
-__device__ __forceinline__ uint32_t addr32(uint32_t bits, const Consts &k) {
-    return med3_u32(bits >> k.shift, k.clo, k.chi) * (LUT8 ? 1u : 2u) + k.lutbias;
-}
-
+// LDS address of the cell-table entry of an FP64 key (the high word of e;
+// arithmetic shift, so e < 0 lands in the bottom cell).
 template <bool LUT8>
 __device__ __forceinline__ uint32_t addr64(int32_t hi, const Consts &k) {
     const int32_t c = med3_i32(hi >> (int)k.shift, (int32_t)k.clo, (int32_t)k.chi);
@@ -1897,6 +1883,12 @@ int grid_for(int n_units, int lds, int blocks_per_cu) {
 
 template <int PR, bool B8, bool PRUNE>
 void launch_pairs(int P, int grid, int lds, hipStream_t st, const PairArgs &a) {
+    if constexpr ((PR == 2 || PR == 3) && !PRUNE) {
+        if (P == 1) {
+            hipLaunchKernelGGL((pairs_kernel<PR, B8, 1, PRUNE>), dim3(grid), dim3(kBlock), lds, st, a);
+            return;
+        }
+    }
     if (P == 2)
         hipLaunchKernelGGL((pairs_kernel<PR, B8, 2, PRUNE>), dim3(grid), dim3(kBlock), lds, st, a);
     else
@@ -1915,7 +1907,7 @@ extern "C" int tpcf_launch_pairs(const PairArgs *args, int precision, void *stre
     hipStream_t st = (hipStream_t)stream;
     const bool b8 = args->lut_entry_bytes == 1;
     const int P = args->rows_per_lane;
-    if (P != 2 && P != 4)
+    if (P != 2 && P != 4 && !(P == 1 && precision == 0 && !args->prune))
         return (int)hipErrorInvalidValue;
     const bool prune = args->prune != 0;
     if (precision != 0 && precision != 1)

@@ -37,7 +37,7 @@ int main() {
     int done = 0;
     for (int64_t na : sizes)
         for (int64_t max_cols : caps)
-            for (int rows = 2; rows <= 4; rows += 2) {
+            for (int rows = 1; rows <= 4; rows *= 2) {
                 const int64_t ranges[][2] = {{0, na}, {na / 3, na}, {na / 7, na - na / 5}, {na / 2, na / 2}};
                 for (auto &r : ranges) {
                     if (check(true, na, na, r[0], r[1], rows, max_cols)) {
