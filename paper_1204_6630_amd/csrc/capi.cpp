@@ -200,7 +200,7 @@ struct Request {
     int64_t rb = 0, re = 0;
     int nbins = 0, precision = 0;
     Compiled *cp = nullptr;
-    Plan *plan = nullptr;    // a unit list (batches, jackknife regions), else:
+    std::shared_ptr<Plan> plan;     // a unit list (batches, jackknife regions), else:
     UnitGrid grid{};
     int rows = 4;            // rows per lane
     int32_t n_units = 0;
@@ -237,7 +237,7 @@ struct tpcf_ctx {
     int64_t next_job = 1;
     std::map<int32_t, Catalog> cats;
     std::map<std::string, std::unique_ptr<Compiled>> compiled;
-    std::map<std::string, std::unique_ptr<Plan>> plans;
+    std::map<std::string, std::shared_ptr<Plan>> plans;
     std::map<int64_t, AsyncJob> jobs;
     std::map<std::string, std::unique_ptr<BatchGraph>> graphs;
     std::map<std::string, std::vector<uint64_t>> result_cache;
@@ -864,8 +864,10 @@ Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int rows, int64_
     return p;
 }
 
+// (A batch of more plans than the cache holds drops it on the way: its requests
+// keep their own.)
 int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows, uint64_t load,
-             Plan **out) {
+             std::shared_ptr<Plan> *out) {
     const int64_t max_cols = max_cols_of(ctx->tune);
     char buf[160];
     snprintf(buf, sizeof buf, "%d:%lld:%lld:%lld:%lld:%lld:%lld:%llu", (int)auto_pairs, (long long)na,
@@ -873,7 +875,7 @@ int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb,
              (unsigned long long)load);
     auto it = ctx->plans.find(buf);
     if (it != ctx->plans.end()) {
-        *out = it->second.get();
+        *out = it->second;
         return TPCF_OK;
     }
     if (ctx->plans.size() >= 256) {   // bounded cache: drop all (in-flight work first)
@@ -883,8 +885,8 @@ int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb,
             kv.second->dunits.release(ctx->mem);
         ctx->plans.clear();
     }
-    auto p = std::make_unique<Plan>(make_plan(auto_pairs, na, nb, rb, re, rows, max_cols, load));
-    *out = p.get();
+    auto p = std::make_shared<Plan>(make_plan(auto_pairs, na, nb, rb, re, rows, max_cols, load));
+    *out = p;
     ctx->plans[buf] = std::move(p);
     return TPCF_OK;
 }
@@ -892,7 +894,7 @@ int get_plan(tpcf_ctx *ctx, bool auto_pairs, int64_t na, int64_t nb, int64_t rb,
 // Plan of a whole-catalog request with jackknife regions (cached like get_plan,
 // keyed by the catalog ids, which are never reused).
 int get_plan_regions(tpcf_ctx *ctx, bool auto_pairs, int32_t cat_a, int32_t cat_b, const Catalog &A,
-                     const Catalog &B, int precision, Plan **out) {
+                     const Catalog &B, int precision, std::shared_ptr<Plan> *out) {
     const int rows = rows_per_lane_of(ctx->tune, precision, pairs_of(auto_pairs, A.n, B.n, 0, A.n));
     const int64_t max_cols = max_cols_of(ctx->tune);
     char buf[160];
@@ -900,7 +902,7 @@ int get_plan_regions(tpcf_ctx *ctx, bool auto_pairs, int32_t cat_a, int32_t cat_
              (long long)max_cols);
     auto it = ctx->plans.find(buf);
     if (it != ctx->plans.end()) {
-        *out = it->second.get();
+        *out = it->second;
         return TPCF_OK;
     }
     if (ctx->plans.size() >= 256) {
@@ -910,12 +912,12 @@ int get_plan_regions(tpcf_ctx *ctx, bool auto_pairs, int32_t cat_a, int32_t cat_
             kv.second->dunits.release(ctx->mem);
         ctx->plans.clear();
     }
-    auto p = std::make_unique<Plan>(
+    auto p = std::make_shared<Plan>(
         make_plan_regions(auto_pairs, A.n, B.n, rows, max_cols, A.reg_start, B.reg_start));
     if (p->units.size() > (size_t)0x7fffffff / kWaves)
         return fail(TPCF_E_INVALID, "too many work units (region boundaries split the work too finely)");
     TRY(upload_blocking(ctx->mem, p->dunits, p->units));
-    *out = p.get();
+    *out = p;
     ctx->plans[buf] = std::move(p);
     return TPCF_OK;
 }
