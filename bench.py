@@ -22,25 +22,18 @@ import time
 import numpy as np
 
 METRIC = "exact-count Gpairs/s, FP32-chord vs FP64 path; p50/p99 job latency"
-# ALU roofline of the FP32 angular kernel: 256 CUs x 4 SIMDs x 32 FP32 lanes
-# x 2.4 GHz = 78.6e12 FP32 lane operations per second (157.3 TFLOP/s counting
-# an FMA as two).  The kernel decides a pair from the dot product of the FP32
-# copies where that suffices, so a pair needs at least 4 of them: one
-# multiply and two FMAs for p, one to bin it.  Chord-only kernels (pruned
-# launches) and the 3-D squared distance need at least 7: 3 subtractions,
-# one multiply and two FMAs, and the table key.
-FP32_LANE_OPS = 256 * 4 * 32 * 2.4e9
-OPS_PER_PAIR_FP32 = 4
-OPS_PER_PAIR_CHORD = 7
+# Roofline of the FP32 kernels (angles and 3-D): the squared distances of 32 x
+# 32 pairs are one v_mfma_f32_32x32x16_f16, 32 cycles of a matrix core (32768
+# operations at the dense FP16 peak of 2.5 PFLOP/s), on 256 CUs x 4 matrix
+# cores x 2.4 GHz: 78.6e12 pairs per second.  (Reading the sixteen results of
+# every lane costs the vector unit more than that, about 50 cycles a tile.)
+FP32_PAIRS = 256 * 4 * 2.4e9 / 32 * 1024
 # FP64 vector path: 78.6e12 FP64 lane operations per second; a pair needs 6
 # (three products, two sums, 1 - d) plus the key.
 FP64_LANE_OPS = 256 * 4 * 16 * 2.4e9
 OPS_PER_PAIR_FP64 = 7
 PATH_NAMES = {0: "fp32_chord", 1: "fp64"}
-# the FP32 angular kernel decides steps from the dot product first and forms
-# the chord where that does not settle them
-KERNEL_NAMES = {0: "pairs_kernel<6> (FP32, dot product first, chord where needed)",
-                1: "pairs_kernel<1> (FP64 vector)"}
+KERNEL_NAMES = {0: "pairs_kernel<2> (FP32 tiles on the matrix cores)", 1: "pairs_kernel<1> (FP64 vector)"}
 HERE = os.path.dirname(os.path.abspath(__file__))
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "hbm_traffic_octant_1e6x2e6.txt")
 
@@ -51,7 +44,7 @@ def kernel_source_hash() -> str:
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ("kernels.hip", "internal.h"):
+    for f in ("kernels.hip", "internal.h", "units.h"):
         with open(os.path.join(HERE, "paper_1204_6630_amd", "csrc", f), encoding="utf-8") as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
@@ -76,11 +69,8 @@ def measured_traffic(path: str):
 
 def roofline(prec: int, kernel_gpairs: float, ms_per_launch: float, traffic=None, kernel=None,
              ops_per_pair=None) -> dict:
-    if prec == 0:
-        peak = FP32_LANE_OPS / (ops_per_pair or OPS_PER_PAIR_FP32) / 1e9
-    else:
-        peak = FP64_LANE_OPS / (ops_per_pair or OPS_PER_PAIR_FP64) / 1e9
-    roof = {"bound": "alu", "achieved": round(kernel_gpairs, 1), "peak": round(peak, 1),
+    peak = FP32_PAIRS / 1e9 if prec == 0 else FP64_LANE_OPS / (ops_per_pair or OPS_PER_PAIR_FP64) / 1e9
+    roof = {"bound": "mfma" if prec == 0 else "alu", "achieved": round(kernel_gpairs, 1), "peak": round(peak, 1),
             "unit": "Gpairs/s", "frac": round(kernel_gpairs / peak, 4)}
     roof.update({"traffic": traffic, "kernel": kernel or KERNEL_NAMES[prec],
                  "kernel_ms_per_launch": round(ms_per_launch, 3)})
@@ -398,13 +388,13 @@ def main():
         t = ctx.get_tuning()     # 0 = the library's default
         rpl = t["rows_per_lane"] or 4
         tuning = dict(t, rows_per_lane=rpl, autotuned=tuning is not None)
-        rows_per_step = rpl * 64
-        cols_per_step = {tp.FP32_CHORD: 4, tp.FP64: 2}[prec]
+        # a step: a tile of 32 x 32 pairs, or 64 lanes x rows x 2 columns
+        pairs_per_step = {tp.FP32_CHORD: 1024, tp.FP64: rpl * 64 * 2}[prec]
         return {"s": t1 - t0, "kernel_ms": kms, "launches": launches, "hist": h, "w": ws,
                 "totals_ok": ok, "flagged": st.flagged, "exact": st.exact, "pairs": st.pairs,
                 "rare": st.rare_steps, "beyond": st.beyond_steps, "one_slot": st.one_slot_steps,
                 "two_slot": st.two_slot_steps, "chord": st.chord_steps, "per_kind": per_kind,
-                "tuning": tuning, "pairs_per_wave_step": rows_per_step * cols_per_step}
+                "tuning": tuning, "pairs_per_wave_step": pairs_per_step}
 
     print(f"# workload {wl.name}: N_D={nd} N_R={nr} nbins={edges.size - 1} "
           f"pairs/step={pairs_step:.4e}", file=sys.stderr, flush=True)
@@ -468,7 +458,7 @@ def main():
                   # the roofline of the pairs the kernel still evaluated
                   "roofline_evaluated_pairs": roofline(
                       tp.FP32_CHORD, evaluated / (kms / 1e3) / 1e9, kms / (3 * args.steps),
-                      kernel="pairs_kernel<0> with pruning (FP32 chord)", ops_per_pair=OPS_PER_PAIR_CHORD),
+                      kernel="pairs_kernel<2> with pruning (FP32 tiles)"),
                   "note": "exact tile pruning (tuning prune=1): same counts; pairs of pruned "
                           "blocks are not evaluated, so not comparable to value"}
     jack = None
@@ -507,7 +497,7 @@ def main():
                 "ms_per_step": round(ms, 3), "kernel_ms_per_step": round(kms / args.steps, 3),
                 "roofline": roofline(tp.FP32_CHORD, pairs_step * args.steps / (kms / 1e3) / 1e9,
                                      kms / (3 * args.steps),
-                                     kernel="pairs_kernel<6> with region copies (FP32)"),
+                                     kernel="pairs_kernel<2> with region copies (FP32)"),
                 "over_plain_step": round(ms / sums[tp.FP32_CHORD]["ms_per_step"], 3),
                 "note": "DD+DR+RR with per-region counts (FP32 chord) + host jackknife of w; "
                         "same totals as the plain step"}
@@ -556,13 +546,12 @@ def main():
                 "ms_per_step": round((t1 - t0) / args.steps * 1e3, 3),
                 "kernel_ms_per_launch": round(kms / max(1, nl), 3),
                 "exact_rate": st.exact / max(1, st.pairs),
-                # FP32: 3 differences, a square, 2 FMAs and the key (as for
-                # angles); FP64: 3 differences, 3 squares, 2 sums (the key
-                # is the high word of r^2)
+                # FP64: 3 differences, 3 squares, 2 sums (the key is the high
+                # word of r^2)
                 "roofline": roofline(prec, pairs3 * args.steps / (kms / 1e3) / 1e9, kms / max(1, nl),
-                                     kernel={tp.FP32_CHORD: "pairs_kernel<5> (3-D FP32)",
+                                     kernel={tp.FP32_CHORD: "pairs_kernel<3> (3-D FP32 tiles)",
                                              tp.FP64: "pairs_kernel<4> (3-D FP64)"}[prec],
-                                     ops_per_pair=OPS_PER_PAIR_CHORD if prec == tp.FP32_CHORD else 8)}
+                                     ops_per_pair=8)}
         for other in (tp.FP64,):
             if not all(np.array_equal(a, b) for a, b in zip(hist3[tp.FP32_CHORD], hist3[other])):
                 sys.exit("3-D histograms differ between precisions")

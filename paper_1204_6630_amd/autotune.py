@@ -2,8 +2,8 @@
 
 Knobs: rows held per lane, LDS
 histogram copies per wavefront, the largest column range of a work unit, the
-grid size, the cell-table budget and, for FP32 byte tables, the wrapped or the
-clamped table layout.  The search is a coordinate descent from the library's
+grid size, the cell-table budget and the table layout field (which no kernel
+reads any more).  The search is a coordinate descent from the library's
 defaults: each knob in turn is swept over its candidates with the others held
 at the best values so far, on a sample of the caller's workload (a block of
 rows against the full column catalog) timed with the library's HIP-event
