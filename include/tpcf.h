@@ -55,9 +55,10 @@ typedef struct tpcf_ctx tpcf_ctx;   /* opaque; owns device state */
 enum { TPCF_DD = 0, TPCF_DR = 1, TPCF_RR = 2 };
 
 /* Precision modes (identical counts).
- * TPCF_FP32_CHORD: bulk pairs are classified from the FP32 squared chord
- *   |f_i - f_j|^2 of FP32 copies of the unit vectors, against FP32 chord^2
- *   bands proven to contain every edge; a pair inside a band is re-decided in
+ * TPCF_FP32_CHORD: bulk pairs are classified from the squared chord
+ *   |f_i - f_j|^2 of FP32 copies of the unit vectors (formed by the matrix cores
+ *   within a proven error, or in FP32), against FP32 chord^2 bands proven to
+ *   contain every edge; a pair inside a band is re-decided in
  *   FP64 with the exact counting rule.
  * TPCF_FP64: every pair's FP64 dot product d is computed as in the counting
  *   rule and compared with D_k (the plain path). */
@@ -424,16 +425,15 @@ int tpcf_jackknife(const uint64_t *dd, const uint64_t *dd_touch, const uint64_t 
 int tpcf_compile_edges(const double *bin_edges_deg, int32_t nbins, double delta_max,
                        double *out_D, float *out_qlo, float *out_qhi);
 
-/* The FP32 dot-product screen of the angular kernels (host only, for CPU
- * tests): for catalogs whose squared norms deviate from 1 by at most
+/* An FP32 dot-product screen (host only, for CPU tests; no launch uses it): for catalogs whose squared norms deviate from 1 by at most
  * delta_max, a pair whose FP32 copies have p = fl32(f_i . f_j) <= *out_p
  * (with any order of fused or separate roundings) has the rule's d <= D of
  * the last edge, i.e. lies at or beyond it (Section 3, first bullet: the
  * angle from the dot product).  -inf when no pair can pass the last edge. */
 int tpcf_compile_screen(const double *bin_edges_deg, int32_t nbins, double delta_max, float *out_p);
 
-/* Tables of the FP32 angular kernels' dot-product path (host only, for CPU
- * tests of the host logic).  A step first forms p = fl32(f_i . f_j) of the
+/* Tables of an FP32 dot-product path (host only, for CPU tests of the host
+ * logic; no launch uses them).  A step first forms p = fl32(f_i . f_j) of the
  * FP32 copies (Section 3: the angle comes from the dot product); each lane
  * keys its largest and smallest p as q' = fl32(2 - 2p), a negative q' read
  * as +0, into the cell clamp(bits(q') >> shift, lo, hi), whose entry
@@ -441,7 +441,7 @@ int tpcf_compile_screen(const double *bin_edges_deg, int32_t nbins, double delta
  * floats each, any may be NULL): q' >= out_khi[k] proves that the FP64 rule
  * puts the pair at or past edge k and q' < out_klo[k] that it does not;
  * p <= out_plo[k] and p >= out_phi[k] prove the same directly on p.
- * out_cells holds max_cells entries (16..33792; the kernels use 1024 bytes).
+ * out_cells holds max_cells entries (16..33792).
  * Returns TPCF_E_INVALID for invalid edges, delta_max outside [0, 2^-20] or
  * NULL shift/lo/hi/cells. */
 int tpcf_compile_dot(const double *bin_edges_deg, int32_t nbins, double delta_max, int32_t max_cells,
