@@ -1132,7 +1132,8 @@ PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, int rows, u
             a.tile_slots = (const float2 *)((const float *)cp.dqlo.p + cp.tile_slots_at);
         }
     } else {
-        const double t = cp.edges.E[last];
+        a.beyond_dot = !cp.metric && cp.edges.D[last] > 0.0;
+        const double t = a.beyond_dot ? cp.edges.D[last] : cp.edges.E[last];
         uint64_t b;
         memcpy(&b, &t, sizeof b);
         a.beyond_key = (uint32_t)(b >> 32);

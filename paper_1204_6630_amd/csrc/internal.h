@@ -114,8 +114,10 @@ struct PairArgs {
     int32_t lut_lo, lut_hi;      // clamp range of cells
     // Pairs certainly beyond the last edge: FP32 path, bits(q) >= beyond_key
     // (the bits of the last edge's qhi); FP64 path, high word of e = 1 - d
-    // above beyond_key as signed integers (e > E_last).
+    // above beyond_key as signed integers (e > E_last), or with beyond_dot,
+    // that of d below it (d < D_last).
     uint32_t beyond_key;
+    int32_t beyond_dot;
     // FP32 tiles: every squared distance (cell table, bands, beyond_key) is
     // scaled by q_scale^2 = 2^q_exp2, q_scale the power of two that brings the
     // coordinates into f16's range.  q_small: steps with a column below it

@@ -335,6 +335,7 @@ struct Consts {
     uint32_t lanebase;      // LDS address of this lane's copy of slot 0
     uint32_t flag;          // flag bit of the cell entries (VGPR copy)
     uint32_t beyond;        // PairArgs::beyond_key (VGPR copy)
+    bool by_dot;            // PairArgs::beyond_dot
 };
 
 // LDS address of the cell-table entry of an FP64 key (the high word of e;
@@ -620,8 +621,30 @@ __device__ __forceinline__ uint32_t step_fp64(const PairArgs &a, const JobDev &j
             if (M3)
                 e[t][p] = exact_d2(xi[p], yi[p], zi[p], xj[t], yj[t], zj[t]);
             else
-                e[t][p] = 1.0 - exact_dot(xi[p], yi[p], zi[p], xj[t], yj[t], zj[t]);
+                e[t][p] = exact_dot(xi[p], yi[p], zi[p], xj[t], yj[t], zj[t]);
         }
+    }
+    // a last edge below 90 degrees (D_last > 0): the high word of d below that
+    // of D_last implies d < D_last, also for negative d, and steps beyond the
+    // edge (61 % on the octant) need no 1 - d, one of their seven operations
+    // a pair
+    const bool by_dot = !M3 && k.by_dot;
+    if (!MASKED && by_dot) {
+        int32_t m = __double2hiint(e[0][0]);
+#pragma unroll
+        for (int t = 0; t < JN; ++t)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                m = max(m, __double2hiint(e[t][p]));
+        if (wave_all(m < (int32_t)k.beyond))
+            return kBeyond;
+    }
+    if (!M3) {
+#pragma unroll
+        for (int t = 0; t < JN; ++t)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                e[t][p] = 1.0 - e[t][p];
     }
     if (!MASKED) {
         // high word of e above that of E_last implies e > E_last for every pair
@@ -631,7 +654,7 @@ __device__ __forceinline__ uint32_t step_fp64(const PairArgs &a, const JobDev &j
 #pragma unroll
             for (int p = 0; p < P; ++p)
                 m = min(m, __double2hiint(e[t][p]));
-        if (wave_all(m > (int32_t)k.beyond)) {
+        if (!by_dot && wave_all(m > (int32_t)k.beyond)) {
             return kBeyond;
         }
         if constexpr (ONE) {
@@ -652,18 +675,22 @@ __device__ __forceinline__ uint32_t step_fp64(const PairArgs &a, const JobDev &j
                 // and the exact rule decides e == E_base (as in resolve_fp64);
                 // lanes with one slot compare with +inf
                 const double thr = span ? s.E[min(base, (uint32_t)(a.nedges - 1))] : __builtin_huge_val();
-                uint32_t n_up = 0, tie = 0;
+                // x = fl(e - thr) has the sign of the comparison and is +0
+                // only for a tie; a high word of 0 (a tie, or a subnormal x)
+                // goes to the lookup
+                uint32_t n_below = 0, least = ~0u;
 #pragma unroll
                 for (int t = 0; t < JN; ++t)
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        n_up += e[t][p] > thr ? 1u : 0u;
-                        tie |= e[t][p] == thr ? 1u : 0u;
+                        const uint32_t x = (uint32_t)__double2hiint(e[t][p] - thr);
+                        n_below += x >> 31;
+                        least = min(least, x);
                     }
                 // count before the test, so nothing of it stays live past it
-                asm volatile("" : "+v"(n_up), "+v"(tie));
-                if (!__builtin_amdgcn_ballot_w64(tie != 0)) {
-                    two_slot_add(base, JN * P, n_up, k, cnt);
+                asm volatile("" : "+v"(n_below), "+v"(least));
+                if (!__builtin_amdgcn_ballot_w64(least == 0)) {
+                    two_slot_add(base, JN * P, JN * P - n_below, k, cnt);
                     return kTwoSlot;
                 }
             }
@@ -1611,6 +1638,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
     k.rowlog = 31u - (uint32_t)__builtin_clz(k.rowstep);
     k.flag = to_vgpr(Code<LUT8>::flag);
     k.beyond = to_vgpr(a.beyond_key);
+    k.by_dot = a.beyond_dot != 0;
     k.lanebase = s.hist_addr +
                  (uint32_t)((wave * (a.nslots + 1) * a.hist_copies + (lane & (a.hist_copies - 1))) * 4);
     Counters cnt;

@@ -175,3 +175,22 @@ def test_launches_leave_nothing_behind(ctx):
                 assert np.array_equal(ctx.count(tp.DD, a, e, precision=prec), want)
     finally:
         ctx.release_catalog(a)
+
+
+@pytest.mark.parametrize("last", [89.0, 90.0, 91.0, 180.0])
+def test_fp64_steps_beyond_an_edge_near_90_degrees(ctx, last):
+    """FP64 steps beyond a last edge below 90 degrees are told by the dot
+    product itself, others by 1 - d: points all over the sphere, both signs of
+    the dot product, edges on either side of where the test changes."""
+    g = synthcat.rng_for(98, int(last))
+    d = synthcat.uniform_patch(700, (0.0, 360.0, -90.0, 90.0), g)
+    r = synthcat.uniform_patch(1300, (0.0, 360.0, -90.0, 90.0), g)
+    e = np.array([10.0, 45.0, last])
+    xd, xr = oracle.radec_to_xyz(*d), oracle.radec_to_xyz(*r)
+    a, b = ctx.upload_catalog(*d), ctx.upload_catalog(*r)
+    try:
+        assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b, precision=tp.FP64), oracle.count(oracle.DR, xd, e, b_xyz=xr))
+        assert np.array_equal(ctx.count(tp.DD, b, e, precision=tp.FP64), oracle.count(oracle.DD, xr, e))
+    finally:
+        ctx.release_catalog(a)
+        ctx.release_catalog(b)
