@@ -295,8 +295,9 @@ int tpcf_cancel(tpcf_ctx *ctx, int64_t job);
 /* Launch shape of later launches (set by the autotuner; defaults are fine).
  * Every field 0 takes the default.
  * rows_per_lane   2 or 4: a wavefront covers 64 times as many rows (default
- *                 4; FP32 launches of fewer than 2^23 pairs: 2,
- *                 of fewer than 2^20 without pruning: 1);
+ *                 4; FP32 launches of fewer than 2^23 pairs: 2, of fewer
+ *                 than 2^20 without pruning: 1; single FP64 requests of
+ *                 fewer than 2^26 pairs without pruning: 2);
  * hist_copies     LDS histogram copies per wavefront, 4, 8, 16 or 32
  *                 (default 16); a value above what the slot count allows
  *                 (32 up to 46 slots, 16 up to 94, 8 up to 190, else 4) is

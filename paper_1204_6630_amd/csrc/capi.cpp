@@ -73,10 +73,16 @@ struct Tuning {
 // and the launch lasts as long as the slowest (DD of 4000 points: 4 rows 57.7
 // us, 2 rows 46.6; of 1400: 55, 46 and, with 1 row, 37.0; of 2000: 2 rows
 // 45.2.  DD+DR+RR of 1e4 x 1e4 the other way: 4 rows 222 us, 2 rows 317).
-int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs) {
+// FP64 requests of their own (`single`; not the lists of batches and regions,
+// whose tiles are cut anyway) below 2^26 pairs: 2 (DD of 1000 points 45.8 ->
+// 39.6 us, of 6000 53.4 -> 46.6, of 10000 62.9 -> 60.5; of 20000 200.8 against
+// 214.8).
+int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs, bool single = false) {
     if (t.rows_per_lane)
         return t.rows_per_lane;
-    if (precision != TPCF_FP32_CHORD || pairs >= (uint64_t)1 << 23)
+    if (precision != TPCF_FP32_CHORD)
+        return single && !t.prune && pairs < (uint64_t)1 << 26 ? 2 : 4;
+    if (pairs >= (uint64_t)1 << 23)
         return 4;
     return pairs < (uint64_t)1 << 20 && !t.prune ? 1 : 2;
 }
@@ -1050,7 +1056,7 @@ int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Reques
         r->n_units = (int32_t)r->plan->units.size();
     } else {
         r->pairs = pairs_of(r->auto_pairs, r->A->n, r->B->n, rb, re);
-        rows = rows_per_lane_of(ctx->tune, d.precision, r->pairs);
+        rows = rows_per_lane_of(ctx->tune, d.precision, r->pairs, true);
         r->grid = make_grid(r->auto_pairs, r->A->n, r->B->n, rb, re, rows, max_cols_of(ctx->tune), &r->n_units);
     }
     r->rows = rows;
