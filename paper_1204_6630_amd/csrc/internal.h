@@ -2,6 +2,7 @@
 // Not part of the public ABI (see include/tpcf.h).
 #pragma once
 
+#include <math.h>
 #include <stddef.h>
 #include <hip/hip_vector_types.h>
 #include <stdint.h>
@@ -59,6 +60,18 @@ constexpr int kMaxSlots8 = 127;
 // power of two, at least 16), flags below.
 constexpr uint32_t kCellOpen = 1;    // an edge lies in the cell, between the slot and the next
 constexpr uint32_t kCellMulti = 2;   // several edges (kCellOpen is set too)
+
+// FP32 tiles: the edge a tile's pairs are compared with, the one nearest to
+// its column's distance q from the rows' mean: of the column's slot (lower end
+// and width as in PairArgs::tile_slots) the upper edge above the slot's middle
+// and the lower one up to it.  The first slot has no lower edge and the last
+// no upper one, and both may have no width (a first edge whose band reaches 0,
+// with a column at the mean itself; a last edge out of reach), so the number
+// is clamped here, once for all that it is used for.
+TPCF_HD uint32_t nearest_edge(uint32_t slot, float q, float lower, float width, uint32_t nedges) {
+    const int32_t k = (int32_t)slot - (q > fmaf(0.5f, width, lower) ? 0 : 1), last = (int32_t)nedges - 1;
+    return (uint32_t)(k < 0 ? 0 : k > last ? last : k);
+}
 
 // One work unit: the row tile starting at i0 with valid rows [row_lo, i1),
 // against columns j in [j0, j1) of job `job` (col_lo == j0, kept for the

@@ -1467,11 +1467,11 @@ __device__ void rows_tiles(cargs_p args, cjob_p job, const Smem &s, const Consts
                     uint32_t ke;
                     column_state(h, nb, row, valid, nbh, ke);
                     const bool vh = ke != ~0u;
-                    ke >>= k.rowlog;
+                    ke = min(ke >> k.rowlog, (uint32_t)a.nedges);
                     eh = __fmaf_rn(u * kTileErrN, nbh, e_rows);
-                    const float2 sl = s.slots[min(ke, (uint32_t)a.nedges)];
-                    ke = nbh > __fmaf_rn(0.5f, sl.y, sl.x) ? ke : ke - 1u;
-                    const float4 ed = s.edges[min(ke, (uint32_t)(a.nedges - 1))];   // qhi, qhi - qlo, room below, above
+                    const float2 sl = s.slots[ke];
+                    ke = nearest_edge(ke, nbh, sl.x, sl.y, (uint32_t)a.nedges);
+                    const float4 ed = s.edges[ke];      // qhi, qhi - qlo, room below, above
                     eh = __fmaf_rn(8.0f * u, ed.x, eh);
                     const float room = vh ? fminf(ed.z, __fmaf_rn(-2.0f, eh, ed.w)) : __builtin_huge_valf();
                     const int32_t lim = vh ? (int32_t)__float_as_uint(__fmaf_rn(-2.0f, eh, -ed.y)) : INT32_MIN;

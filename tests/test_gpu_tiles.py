@@ -194,3 +194,33 @@ def test_fp64_steps_beyond_an_edge_near_90_degrees(ctx, last):
     finally:
         ctx.release_catalog(a)
         ctx.release_catalog(b)
+
+
+CORNERS = [(x, y, z) for x in (-1.0, 1.0) for y in (-1.0, 1.0) for z in (-1.0, 1.0)]
+
+
+@pytest.mark.parametrize("rows", [0, 2, 4])
+@pytest.mark.parametrize("edges", [(1e-9, 2.0), (0.0, 1e-9, 2.0), (1e-9, 0.5, 1.5), (1e-9, 0.5, 2.0),
+                                   (0.0, 1e-9, 2e-9, 0.5, 1.1)])
+@pytest.mark.parametrize("around", [[(1.0, 0.0, 0.0), (-1.0, 0.0, 0.0)], CORNERS], ids=["pair", "cube"])
+def test_column_at_the_rows_mean(ctx, around, edges, rows):
+    """Rows placed symmetrically about a column, and a first edge below the
+    FP32 band (its band reaches 0): the column's slot has no lower edge and no
+    width.  Rows in upload order and shuffled, in multiples of every
+    wavefront's rows; DD with the mean itself among the points."""
+    e = np.array(edges)
+    g = synthcat.rng_for(96, 31)
+    for n in (64, 128, 256, 512):
+        p = np.tile(np.array(around), (n // len(around), 1))
+        for q in (p, g.permutation(p), np.concatenate([p, np.zeros((64, 3))]), np.concatenate([p[:-1], np.zeros((1, 3))])):
+            x, y = tuple(q.T.copy()), tuple(np.zeros((3, 1)))
+            a, b = ctx.upload_catalog_3d(*x), ctx.upload_catalog_3d(*y)
+            try:
+                ctx.set_tuning(rows_per_lane=rows)
+                assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b), oracle.count3d(oracle.DR, x, e, b_xyz=y))
+                assert np.array_equal(ctx.count(tp.DD, a, e), oracle.count3d(oracle.DD, x, e))
+                assert np.array_equal(ctx.count(tp.DR, b, e, cat_b=a), oracle.count3d(oracle.DR, y, e, b_xyz=x))
+            finally:
+                ctx.set_tuning()
+                ctx.release_catalog(a)
+                ctx.release_catalog(b)
