@@ -654,6 +654,7 @@ CellTable make_cells32_top(const EdgeTables &t, const Band32 &b, uint32_t ktop, 
         int64_t lo = isfinite(tmin) ? (int64_t)(fbits(tmin) >> shift) - 1 : hi - 1;
         if (lo < 0)
             lo = 0;
+        hi = std::max(hi, lo + 1);      // (3-D: the first edge may lie beyond every pair)
         if (hi - lo + 1 <= max_cells || shift == 23) {
             if (hi - lo + 1 > max_cells)
                 lo = hi - max_cells + 1;
@@ -727,6 +728,7 @@ CellTable make_cells64(const EdgeTables &t, int max_cells, double etop) {
         int64_t lo = isfinite(tmin) ? (int64_t)(dhi(tmin) >> shift) - 1 : hi - 1;
         if (lo < 0)
             lo = 0;
+        hi = std::max(hi, lo + 1);      // (as in make_cells32_top)
         if (hi - lo + 1 <= max_cells || shift == 20) {
             if (hi - lo + 1 > max_cells)
                 lo = hi - max_cells + 1;

@@ -45,6 +45,12 @@ static Tables tables(int metric, const std::vector<double> &e, double extent, in
     t.q_exp = tile_scale_exp(metric, extent);
     scale_band32(2 * t.q_exp, &t.band, &top);
     t.cells = make_cells_tiles(et, t.band, top, max_cells);
+    // the FP64 path has a table of the same edges
+    const CellTable c = make_cells64(et, max_cells, metric ? fmax(4.0 * extent * extent * 1.001, 1e-300) : 2.0);
+    if (c.lo > c.hi || (int)c.cells.size() != c.hi - c.lo + 1) {
+        printf("FP64 cells %d to %d: %zu\n", c.lo, c.hi, c.cells.size());
+        exit(1);
+    }
     make_tile_tables(t.band, &t.slots, &t.edges);
     return t;
 }
@@ -205,6 +211,12 @@ int main() {
         {1, 10.0, {1.0, 1e30, 1e140}},
         {1, 1e-30, {1e-33, 1e-31, 5e-31}},
         {1, 1.9e15, {1e8, 1e12, 1e15}},
+        // the first edge beyond every pair, and no extent at all
+        {1, 1.0, {10.0, 20.0}},
+        {1, 1.0, {2.5, 1e30}},
+        {1, 1.0, {0.0, 20.0, 1e140}},
+        {1, 0.0, {0.0, 1.0}},
+        {1, 0.0, {1e-9, 1.0}},
         {0, eps, {0.0, 180.0}},
         {0, eps, {1e-6, 90.0}},
         {0, eps, {1e-9, 1e-7, 1e-6, 1e-5, 120.0}},

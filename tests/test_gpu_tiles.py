@@ -224,3 +224,28 @@ def test_column_at_the_rows_mean(ctx, around, edges, rows):
                 ctx.set_tuning()
                 ctx.release_catalog(a)
                 ctx.release_catalog(b)
+
+
+@pytest.mark.parametrize("prec", [tp.FP32_CHORD, tp.FP64])
+@pytest.mark.parametrize("edges", [(10.0, 20.0), (0.0, 20.0, 1e140), (2.5, 1e30), (1e-9, 1e9)])
+@pytest.mark.parametrize("extent", [0.0, 1.0])
+def test_3d_edges_beyond_every_pair(ctx, extent, edges, prec):
+    """Edges of which the first positive one lies further than any two points
+    of the catalogs, catalogs of one place and empty ones: every entry point
+    that compiles 3-D edges."""
+    g = synthcat.rng_for(96, 47)
+    x, y = tuple(extent * g.uniform(-0.5, 0.5, (3, 300))), tuple(extent * g.uniform(-0.5, 0.5, (3, 77)))
+    e = np.array(edges)
+    a, b = ctx.upload_catalog_3d(*x), ctx.upload_catalog_3d(*y)
+    none = ctx.upload_catalog_3d(*np.zeros((3, 0)))
+    try:
+        dd, dr = oracle.count3d(oracle.DD, x, e), oracle.count3d(oracle.DR, x, e, b_xyz=y)
+        assert np.array_equal(ctx.count(tp.DD, a, e, precision=prec), dd)
+        assert np.array_equal(ctx.count(tp.DR, a, e, cat_b=b, precision=prec), dr)
+        assert not ctx.count(tp.DD, none, e, precision=prec).any()
+        got = ctx.count_batch([(tp.DD, a, -1), (tp.DR, a, b)], e, precision=prec)
+        assert np.array_equal(got[0], dd) and np.array_equal(got[1], dr)
+        assert np.array_equal(ctx.wait(ctx.submit(tp.DR, a, e, cat_b=b, precision=prec), e.size + 1), dr)
+    finally:
+        for c in (a, b, none):
+            ctx.release_catalog(c)
