@@ -1025,9 +1025,9 @@ int validate(tpcf_ctx *ctx, const tpcf_job_desc &d, Request *r) {
 
 // Validate one request and get its tables and plan.  delta_override >= 0
 // compiles the FP32 band for that norm bound (shared by every job of a batch)
-// instead of the request's own; load > 0 makes the request part of a
-// launch over that many pairs with `rows` rows per lane: its units come as a
-// list.
+// instead of the request's own; rows > 0 makes the request part of a launch
+// over `load` pairs (none when every request is empty) with `rows` rows per
+// lane: its units come as a list.
 int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Request *r, bool regions = false,
             int rows = 0, uint64_t load = 0) {
     TRY(validate(ctx, d, r));
@@ -1050,7 +1050,7 @@ int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Reques
         r->n_units = (int32_t)r->plan->units.size();
         return TPCF_OK;
     }
-    if (load) {
+    if (rows) {
         TRY(get_plan(ctx, r->auto_pairs, r->A->n, r->B->n, rb, re, rows, load, &r->plan));
         r->pairs = r->plan->pairs;
         r->n_units = (int32_t)r->plan->units.size();
