@@ -285,8 +285,10 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
  * when the job has finished, and then retires the id; *done = 0 otherwise.
  * tpcf_wait blocks until the job finishes, then acts like tpcf_poll.
  * tpcf_cancel sets a flag in host memory that every wavefront of the kernel
- * reads at its first work unit and every few million pairs from then on; the
- * job's poll/wait then returns TPCF_E_CANCELLED and retires it.  A catalog cannot be released while an unretired job uses it. */
+ * reads after every two million pairs of its own (a job too short for that
+ * runs to its end on the device); the job's poll/wait then returns
+ * TPCF_E_CANCELLED and retires it.  A catalog cannot be released while an
+ * unretired job uses it. */
 int tpcf_submit(tpcf_ctx *ctx, const tpcf_job_desc *job, int64_t *out_job);
 int tpcf_poll(tpcf_ctx *ctx, int64_t job, uint64_t *out_u64, int *done);
 int tpcf_wait(tpcf_ctx *ctx, int64_t job, uint64_t *out_u64);
