@@ -767,7 +767,8 @@ Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, 
     p.rows = rows;
     const uint64_t pairs = pairs_of(auto_pairs, na, nb, rb, re);
     p.pairs = pairs;
-    const int64_t bj = chunk_width(pairs, load ? load : pairs, T, max_cols, 512, max_units);
+    const int64_t bj = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), load ? load : pairs, T,
+                                   max_cols, 512, max_units);
     // Row tiles start at rb (valid rows from row_lo = rb).
     // Column chunks lie on a common grid of multiples of bj, so units of
     // different row tiles cover the same column ranges; the list is ordered
@@ -823,7 +824,7 @@ Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int rows, int64_
     const int64_t T = (int64_t)kWaves * kWaveSize * rows;
     p.rows = rows;
     p.pairs = auto_pairs ? (uint64_t)na * (uint64_t)(na > 0 ? na - 1 : 0) / 2 : (uint64_t)na * (uint64_t)nb;
-    const int64_t bj = chunk_width(p.pairs, p.pairs, T, max_cols, 1024);
+    const int64_t bj = chunk_width((double)p.pairs / (double)T, p.pairs, T, max_cols, 1024);
     const int nra = (int)sa.size() - 1;
     auto region_of = [](const std::vector<int64_t> &st, int64_t j) {
         return (int32_t)(std::upper_bound(st.begin(), st.end(), j) - st.begin() - 1);

@@ -28,21 +28,29 @@ inline uint64_t pairs_of(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, in
     return (uint64_t)cnt * (uint64_t)(na - 1) - (uint64_t)((rb + re - 1) * cnt / 2);
 }
 
-// Column chunk width of a plan for a launch over `load` pairs: 64 columns up
-// to `busy`, as many as still leave 4096 units (16 items a wavefront slot's
-// worth of wavefronts), and from there on as many as leave 65536, at most
-// max_cols (multiples of 256 above 256); but wide enough that the unit list
-// of this plan stays below kMaxUnits (about 0.8 GB of units; catalogs of 1e8
-// points would otherwise need tens of GB of them).  A launch ends when its
-// last item does, so items are kept short against it, but a narrow item
-// prepares its rows for few columns.  Measured, default before (4096 units
-// from the start) against 512 columns: DD+DR+RR of 1e5 x 1e5 3.83 -> 2.83 ms,
-// FP64 of 1.5e5 x 3e5 28.6 -> 25.9, 24 fields in a batch 8.03 -> 7.25; at 256
-// columns the first takes 3.79.  With jackknife regions, whose boundaries cut
-// the chunks again, 1024 columns are better than 512 (7.2 against 7.65 ms).
+// Columns that the row tiles of a request meet, all tiles together: its units
+// at chunks of bj columns are about this over bj, however few rows a tile has.
+inline int64_t tile_columns(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int64_t T) {
+    const int64_t tiles = (re - rb + T - 1) / T;
+    return auto_pairs ? tiles * (na - rb) - T * (tiles * (tiles - 1) / 2) : tiles * nb;
+}
+
+// Column chunk width of a plan for a launch over `load` pairs, whose tiles are
+// taken to hold T rows: 64 columns up to `busy`, as many as still leave 4096
+// units (16 items a wavefront slot's worth of wavefronts), and from there on
+// as many as leave 65536, at most max_cols (multiples of 256 above 256); but
+// wide enough that a list of `columns` columns of tiles stays below max_units
+// (kMaxUnits: about 0.8 GB of units; catalogs of 1e8 points would otherwise
+// need tens of GB of them).  A launch ends when its last item does, so items
+// are kept short against it, but a narrow item prepares its rows for few
+// columns.  Measured, default before (4096 units from the start) against 512
+// columns: DD+DR+RR of 1e5 x 1e5 3.83 -> 2.83 ms, FP64 of 1.5e5 x 3e5 28.6 ->
+// 25.9, 24 fields in a batch 8.03 -> 7.25; at 256 columns the first takes
+// 3.79.  With jackknife regions, whose boundaries cut the chunks again, 1024
+// columns are better than 512 (7.2 against 7.65 ms).
 constexpr double kMaxUnits = 16777216.0;
 
-inline int64_t chunk_width(uint64_t pairs, uint64_t load, int64_t T, int64_t max_cols, int64_t busy,
+inline int64_t chunk_width(double columns, uint64_t load, int64_t T, int64_t max_cols, int64_t busy,
                     double max_units = kMaxUnits) {
     int64_t bj = std::min(busy, (int64_t)((double)load / 4096.0 / (double)T));
     bj = std::max(bj, (int64_t)((double)load / 65536.0 / (double)T));
@@ -51,7 +59,7 @@ inline int64_t chunk_width(uint64_t pairs, uint64_t load, int64_t T, int64_t max
         bj = max_cols;
     if (bj < 64)
         bj = 64;
-    const double need = (double)pairs / (double)T / max_units;   // columns per unit for max_units units
+    const double need = columns / max_units;    // columns per unit for max_units units
     if ((double)bj < need)
         bj = ((int64_t)need + 256) / 256 * 256;
     return bj;
@@ -119,7 +127,8 @@ inline UnitGrid make_grid(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, i
     if (pairs == 0)
         return g;
     const int64_t T = (int64_t)kWaves * kWaveSize * rows;
-    const int64_t want = chunk_width(pairs, pairs, T, max_cols, 512);
+    const int64_t want = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), pairs, T,
+                                     max_cols, 512);
     int64_t bj = 64;
     while (2 * bj <= want && bj < ((int64_t)1 << 22))
         bj *= 2;

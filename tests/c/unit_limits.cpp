@@ -1,0 +1,45 @@
+// How many units a request is cut into, and how large they are, at catalogs
+// of up to 2^31 - 1024 points (nothing is counted).  Prints the number of
+// requests checked.
+#include <stdio.h>
+
+#include "units.h"
+
+using namespace tpcf;
+
+// Units of a list (DR, or one tile's columns of auto-pairs at a time) at chunks of bj columns.
+static double list_units(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int64_t T, int64_t bj) {
+    double n = 0;
+    const int64_t tiles = (re - rb + T - 1) / T;
+    if (!auto_pairs)
+        return (double)tiles * (double)((nb + bj - 1) / bj);
+    for (int64_t t = 0; t < tiles; ++t)
+        n += (double)((na - (rb + t * T) + bj - 1) / bj);
+    return n;
+}
+
+int main() {
+    int done = 0;
+    // a fixed room for the list: whatever the rows are, the chunks are wide enough for it
+    const double room = 170000.0;
+    for (int64_t nb : {(int64_t)1000, (int64_t)1000000, (int64_t)30000000, (int64_t)500000000, (int64_t)2147482623})
+        for (int64_t cnt : {1, 2, 7, 63, 64, 300, 1023, 1024, 1025, 5000, 20000})
+            for (int rows : {1, 2, 4})
+                    for (int aut = 0; aut < 2; ++aut) {
+                        const int64_t T = 256 * rows, rb = nb / 3, re = rb + cnt;
+                        if (re > nb || (aut && nb < 1000000 && cnt > 500))
+                            continue;
+                        const uint64_t pairs = pairs_of(aut, nb, nb, rb, re);
+                        const int64_t bj = chunk_width((double)tile_columns(aut, nb, nb, rb, re, T), pairs,
+                                                       T, 2048, 512, room);
+                        const double n = list_units(aut, nb, nb, rb, re, T, bj);
+                        if (bj < 64 || n > 1.1 * room + (double)((cnt + T - 1) / T)) {
+                            printf("%s %lld rows x %lld, %d rows a lane: %.0f units of %lld columns\n",
+                                   aut ? "auto" : "cross", (long long)cnt, (long long)nb, rows, n, (long long)bj);
+                            return 1;
+                        }
+                        ++done;
+                    }
+    printf("%d\n", done);
+    return 0;
+}
