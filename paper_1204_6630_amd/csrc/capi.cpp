@@ -87,6 +87,14 @@ int rows_per_lane_of(const Tuning &t, int precision, uint64_t pairs, bool single
     return pairs < (uint64_t)1 << 20 && !t.prune ? 1 : 2;
 }
 
+// Are a single request's columns cut as if its row tiles were full?  FP64
+// requests of few rows go by the rows that they have, which leaves units four
+// times as wide (DR of 100 x 1e6 386 -> 263 us, 300 x 1e6 398 -> 311; 365 with
+// the 256 columns at least of earlier kernels).  FP32 items hold their rows
+// longer, and more of them balance better (300 x 1e6 214 us against 251, 600 x
+// 1e6 204 against 234).
+bool cut_full(int precision) { return precision == TPCF_FP32_CHORD; }
+
 // Largest column chunk: 2048, and 4096 with pruning, where one test covers
 // 4096 columns (1e6 x 2e6: 4096 columns 241.0 ms, 2048 242.3, 1024 251.0; a
 // 3-D box of 5e5 x 1e6 56.0, 55.2, 56.6; pruned 5e5 x 1e6: 8192 52.1, 4096
@@ -760,15 +768,15 @@ Unit mk_unit(int64_t i0, int64_t i1, int64_t j0, int64_t j1, int64_t row_lo, int
 }
 
 Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows,
-               int64_t max_cols, uint64_t load = 0, double max_units = kMaxUnits) {
+               int64_t max_cols, uint64_t load = 0, bool full = true, double max_units = kMaxUnits) {
     Plan p;
     // 64 lanes x rows per lane rows per wavefront, four wavefronts per tile
     const int64_t T = (int64_t)kWaves * kWaveSize * rows;
     p.rows = rows;
     const uint64_t pairs = pairs_of(auto_pairs, na, nb, rb, re);
     p.pairs = pairs;
-    const int64_t bj = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), load ? load : pairs, T,
-                                   max_cols, 512, max_units);
+    const int64_t bj = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), load ? load : pairs,
+                                   full ? T : tile_rows(re - rb, T), max_cols, 512, max_units);
     // Row tiles start at rb (valid rows from row_lo = rb).
     // Column chunks lie on a common grid of multiples of bj, so units of
     // different row tiles cover the same column ranges; the list is ordered
@@ -1058,7 +1066,8 @@ int prepare(tpcf_ctx *ctx, const tpcf_job_desc &d, double delta_override, Reques
     } else {
         r->pairs = pairs_of(r->auto_pairs, r->A->n, r->B->n, rb, re);
         rows = rows_per_lane_of(ctx->tune, d.precision, r->pairs, true);
-        r->grid = make_grid(r->auto_pairs, r->A->n, r->B->n, rb, re, rows, max_cols_of(ctx->tune), &r->n_units);
+        r->grid = make_grid(r->auto_pairs, r->A->n, r->B->n, rb, re, rows, max_cols_of(ctx->tune), &r->n_units,
+                            cut_full(d.precision));
     }
     r->rows = rows;
     if (d.kind == TPCF_RR)
@@ -1673,7 +1682,7 @@ int tpcf_count_noalloc(tpcf_ctx *ctx, int kind, int32_t cat_a, int32_t cat_b, co
     // auto-pairs hold a few more units than the estimate), then checked
     Plan plan = make_plan(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re,
                           rows_per_lane_of(ctx->tune, r.precision, pairs_of(r.auto_pairs, r.A->n, r.B->n, r.rb, r.re)),
-                          max_cols_of(ctx->tune), 0, 0.5 * (double)max_units);
+                          max_cols_of(ctx->tune), 0, cut_full(r.precision), 0.5 * (double)max_units);
     if (plan.units.size() > max_units) {
         char buf[200];
         snprintf(buf, sizeof buf, "the request needs %zu work units; the fixed work area (%zu MiB) holds %zu",

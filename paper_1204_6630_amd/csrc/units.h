@@ -28,6 +28,12 @@ inline uint64_t pairs_of(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, in
     return (uint64_t)cnt * (uint64_t)(na - 1) - (uint64_t)((rb + re - 1) * cnt / 2);
 }
 
+// Rows that a tile of at most T holds on average.
+inline int64_t tile_rows(int64_t rows, int64_t T) {
+    const int64_t tiles = (rows + T - 1) / T;
+    return tiles > 0 ? (rows + tiles - 1) / tiles : T;
+}
+
 // Columns that the row tiles of a request meet, all tiles together: its units
 // at chunks of bj columns are about this over bj, however few rows a tile has.
 inline int64_t tile_columns(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int64_t T) {
@@ -119,16 +125,17 @@ TPCF_HD bool grid_unit(const UnitGrid &g, uint32_t u, int32_t *i0, int32_t *i1, 
 
 // Units of a single request (see UnitGrid): tile and chunk are powers of two,
 // the chunk at most chunk_width's.  No list is built, uploaded or kept.
+// `full`: cut as if every tile were full, else by the rows that each has.
 inline UnitGrid make_grid(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows, int64_t max_cols,
-                   int32_t *n_units) {
+                   int32_t *n_units, bool full = true) {
     UnitGrid g{};
     *n_units = 0;
     const uint64_t pairs = pairs_of(auto_pairs, na, nb, rb, re);
     if (pairs == 0)
         return g;
     const int64_t T = (int64_t)kWaves * kWaveSize * rows;
-    const int64_t want = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), pairs, T,
-                                     max_cols, 512);
+    const int64_t want = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), pairs,
+                                     full ? T : tile_rows(re - rb, T), max_cols, 512);
     int64_t bj = 64;
     while (2 * bj <= want && bj < ((int64_t)1 << 22))
         bj *= 2;

@@ -25,13 +25,14 @@ int main() {
     for (int64_t nb : {(int64_t)1000, (int64_t)1000000, (int64_t)30000000, (int64_t)500000000, (int64_t)2147482623})
         for (int64_t cnt : {1, 2, 7, 63, 64, 300, 1023, 1024, 1025, 5000, 20000})
             for (int rows : {1, 2, 4})
+                for (int full = 0; full < 2; ++full)
                     for (int aut = 0; aut < 2; ++aut) {
                         const int64_t T = 256 * rows, rb = nb / 3, re = rb + cnt;
                         if (re > nb || (aut && nb < 1000000 && cnt > 500))
                             continue;
                         const uint64_t pairs = pairs_of(aut, nb, nb, rb, re);
                         const int64_t bj = chunk_width((double)tile_columns(aut, nb, nb, rb, re, T), pairs,
-                                                       T, 2048, 512, room);
+                                                       full ? T : tile_rows(cnt, T), 2048, 512, room);
                         const double n = list_units(aut, nb, nb, rb, re, T, bj);
                         if (bj < 64 || n > 1.1 * room + (double)((cnt + T - 1) / T)) {
                             printf("%s %lld rows x %lld, %d rows a lane: %.0f units of %lld columns\n",
@@ -40,6 +41,17 @@ int main() {
                         }
                         ++done;
                     }
+    // cut by the rows that they have, requests of any few rows have chunks of the same width as a full tile's
+    for (int64_t cnt : {1, 64, 300, 600}) {
+        int32_t few = 0, all = 0;
+        const UnitGrid g = make_grid(false, 2000, 1000000, 0, cnt, 4, 2048, &few, false);
+        const UnitGrid f = make_grid(false, 2000, 1000000, 0, 1024, 4, 2048, &all, false);
+        if (g.bj != f.bj || few != all) {
+            printf("%lld rows: %d units of %d columns, 1024 rows %d of %d\n", (long long)cnt, few, g.bj, all, f.bj);
+            return 1;
+        }
+        ++done;
+    }
     printf("%d\n", done);
     return 0;
 }

@@ -19,4 +19,4 @@ def test_units_of_the_largest_requests(tmp_path):
                            os.path.join(ROOT, "tests", "c", "unit_limits.cpp"), "-o", exe])
     out = subprocess.run([exe], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
-    assert int(out.stdout) > 200
+    assert int(out.stdout) > 400
