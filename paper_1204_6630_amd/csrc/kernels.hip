@@ -1720,8 +1720,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
                 if (un.reg_b >= 0 && un.reg_b != un.reg_a)
                     r1 = jb.touch + (size_t)un.reg_b * per_region;
             }
-            // (the plan keeps a unit below 2^32 pairs; one near that is
-            // flushed on its own)
+            // (an item is at most 2^30 pairs, see make_grid)
             if (held && (to != jb.hist || to_a != r0 || to_b != r1 || held + pairs >= 0x80000000ull))
                 flush();
             to = jb.hist;

@@ -160,7 +160,10 @@ inline UnitGrid make_grid(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, i
             g.kind = auto_pairs ? 3 : 1;
             n = chunks * tiles;
         }
-        // a unit stays below 2^32 pairs, the items below 2^32
+        // chunks widen until the list would be short enough, but no further
+        // than the number of items (kWaves a unit) needs to stay below 2^32;
+        // a wavefront's item is then at most 2^30 pairs, of which its LDS
+        // counts hold four
         if (n <= (int64_t)kMaxUnits || (bj >= ((int64_t)1 << 21) && n < ((int64_t)1 << 30))) {
             *n_units = (int32_t)n;
             return g;

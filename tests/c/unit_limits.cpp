@@ -7,6 +7,8 @@
 
 using namespace tpcf;
 
+static const int64_t kQueueSlack = 8;    // the queues round the items up to their number
+
 // Units of a list (DR, or one tile's columns of auto-pairs at a time) at chunks of bj columns.
 static double list_units(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int64_t T, int64_t bj) {
     double n = 0;
@@ -52,6 +54,31 @@ int main() {
         }
         ++done;
     }
+    // items are numbered with 32 bits, and one's pairs leave room in the counts that a wavefront keeps over several
+    for (int64_t n : {(int64_t)1000000, (int64_t)100000000, (int64_t)1500000000, (int64_t)2147482623})
+        for (int rows : {2, 4})
+            for (int64_t max_cols : {256, 2048, 65536})
+                for (int kind = 1; kind <= 3; ++kind)
+                    for (int full = 0; full < 2; ++full) {
+                        int32_t units = 0;
+                        const UnitGrid g = make_grid(kind != 1, n, n, kind == 3 ? 5 : 0, kind == 3 ? n - 7 : n, rows,
+                                                     max_cols, &units, full);
+                        const int64_t item = (int64_t)(g.T / kWaves) * g.bj;
+                        if (g.kind != kind || units <= 0 || (int64_t)units * kWaves > ((int64_t)1 << 32) - kQueueSlack ||
+                            item > ((int64_t)1 << 30)) {
+                            printf("kind %d of %lld, %d rows a lane: %d units, items of %lld pairs\n", kind,
+                                   (long long)n, rows, units, (long long)item);
+                            return 1;
+                        }
+                        // the last units lie inside
+                        for (uint32_t u = (uint32_t)units - 1; u + 1000 > (uint32_t)units; --u) {
+                            int32_t i0, i1, j0, j1;
+                            if (grid_unit(g, u, &i0, &i1, &j0, &j1) &&
+                                (i0 < g.rb || i0 >= i1 || i1 > g.re || j0 < 0 || j0 >= j1 || j1 > n))
+                                return 1;
+                        }
+                        ++done;
+                    }
     printf("%d\n", done);
     return 0;
 }
