@@ -773,8 +773,8 @@ __device__ void rows_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, co
     if (PRUNE && !MASKED && jb.bcaps) {
         const Cap rc = block_cap<M3, P>(xi, yi, zi);
         for (int jr = j0, je; jr < j1; jr = je) {
-            const int to = kPruneCols - (jr & 63), b0 = jr >> 6;
-            je = j1 - jr > to ? jr + to : j1;
+            const int b0 = jr >> 6;
+            je = part_end(jr, j1, kPruneCols - (jr & 63));
             uint64_t left = prune_blocks<M3>(rc, jb.bcaps, s, a, k, jr, je, jr, P * 64 * 64, lane, cnt);
             while (left) {      // runs of blocks that are left
                 const int f = __builtin_ctzll(left);
@@ -787,9 +787,10 @@ __device__ void rows_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, co
         }
         return;
     }
-    for (int jc = j0; jc < j1; jc += kFoldCols)
-        cols_fp64<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ie, jc,
-                                             j1 - jc > kFoldCols ? jc + kFoldCols : j1, cnt);
+    for (int jc = j0, je; jc < j1; jc = je) {
+        je = part_end(jc, j1, kFoldCols);
+        cols_fp64<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ie, jc, je, cnt);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1740,9 +1741,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
                     // exists and the catalog has caps
                     const bool caps = ie - ib == kRowsPerWave && jb.bcaps;
                     for (int jr = jb0, je; jr < un.j1; jr = je) {
-                        const int to = kPruneCols - (jr & 63);
-                        je = un.j1 - jr > to ? jr + to : un.j1;
-                        uint64_t left = ~0ull;
+                        je = part_end(jr, un.j1, kPruneCols - (jr & 63));
+                        uint64_t left = blocks_met(jr, je);
                         if (caps) {
                             double x[P], y[P], z[P];
 #pragma unroll

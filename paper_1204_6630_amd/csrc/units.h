@@ -90,6 +90,17 @@ struct UnitGrid {
     int32_t S, sub;              // kind 2
 };
 
+// End of the part of columns [j, j1) that a pass of at most `step` columns
+// takes (j + step itself may lie beyond 32 bits).
+TPCF_HD int32_t part_end(int32_t j, int32_t j1, int32_t step) { return j1 - j > step ? j + step : j1; }
+
+// The aligned 64-column blocks that [j, j1) meets, 64 of them at most: bit b is
+// set for block (j >> 6) + b.
+TPCF_HD uint64_t blocks_met(int32_t j, int32_t j1) {
+    const int32_t n = ((j1 - 1) >> 6) - (j >> 6) + 1;
+    return n < 64 ? ((uint64_t)1 << n) - 1 : ~(uint64_t)0;
+}
+
 // Unit u of a grid; false when it is empty.
 TPCF_HD bool grid_unit(const UnitGrid &g, uint32_t u, int32_t *i0, int32_t *i1, int32_t *j0,
                                           int32_t *j1) {
