@@ -787,10 +787,10 @@ __device__ void rows_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, co
         }
         return;
     }
-    for (int jc = j0, je; jc < j1; jc = je) {
-        je = part_end(jc, j1, kFoldCols);
-        cols_fp64<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ie, jc, je, cnt);
-    }
+    // (unsigned: the position after the last part may lie beyond 31 bits)
+    for (uint32_t jc = (uint32_t)j0; jc < (uint32_t)j1; jc += kFoldCols)
+        cols_fp64<LUT8, MASKED, P, M3, true>(a, jb, s, k, xi, yi, zi, ii, ie, (int)jc, part_end((int)jc, j1, kFoldCols),
+                                             cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -1670,7 +1670,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
     // orders units column chunk first) and the column data stays in L2.
     const uint32_t n_items = (uint32_t)a.n_units * kWaves, n_waves = gridDim.x * kWaves;
     uint32_t queue = blockIdx.x & (kQueues - 1);
-    uint32_t unlooked = 0;          // (a cancellable launch holds one job)
+    int32_t unlooked = 1 << 21;     // pairs up to the next look (a cancellable launch holds one job)
     bool gone = false;
     for (uint32_t next = blockIdx.x * kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wave); next < n_items;
          next = claim_item(a.queue, n_waves, n_items, queue, lane)) {
@@ -1702,9 +1702,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
             // at its first item too, a submitted DR of 637 x 55000 took 293
             // us, now 57, one of 1000 x 100000 567, now 116 (as tpcf_count)
             if (jb.cancel) {
-                unlooked += (uint32_t)min(pairs, (uint64_t)1 << 21);
-                if (unlooked >= 1u << 21) {
-                    unlooked = 0;
+                unlooked -= (int32_t)min(pairs, (uint64_t)1 << 21);
+                if (unlooked <= 0) {
+                    unlooked = 1 << 21;
                     gone = __builtin_amdgcn_readfirstlane(
                                __hip_atomic_load(jb.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) != 0;
                 }
