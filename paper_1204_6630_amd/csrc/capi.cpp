@@ -1202,19 +1202,20 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
     }
     // the histogram copies, then the work queues; zeroed once, then by every
     // launch's reduction for the next one (a clearing launch of its own took
-    // 5 us, of 60 for DD of 1e3 points)
+    // 5 us, of 60 for DD of 1e3 points).  A caller's stream may be capturing:
+    // such a launch runs whenever its graph does, so it clears them itself,
+    // and says nothing about what they hold now.
     const size_t words = (size_t)kGlobalCopies * kMaxSlots + kQueueWords;
     TRY(w.copies.ensure(ctx->mem, sizeof(unsigned long long) * words));
     unsigned long long *copies = (unsigned long long *)w.copies.p;
-    bool clear = w.clear;
-    w.clear = false;        // until the reduction is enqueued
-    if (!clear) {
-        HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)words, w.stream));
-        // (a capturing stream has not run it yet)
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (!w.own)
         HIP_TRY(hipStreamIsCapturing(w.stream, &capture));
-        clear = capture == hipStreamCaptureStatusNone;
-    }
+    const bool captured = capture != hipStreamCaptureStatusNone, clear = w.clear;
+    if (!captured)
+        w.clear = false;    // until the reduction is enqueued
+    if (!clear || captured)
+        HIP_TRY((hipError_t)tpcf_launch_zero_u64(copies, (int64_t)words, w.stream));
     PairArgs a = args_of(ctx, *r.cp, r.nbins, r.rows, (unsigned long long *)w.stats.p, std::max(r.A->delta, r.B->delta));
     a.jobs = nullptr;
     a.job0 = job_of(r, copies, cancel);
@@ -1233,7 +1234,8 @@ int launch_one(tpcf_ctx *ctx, Workspace &w, const Request &r, unsigned long long
         return fail(TPCF_E_HIP, std::string("pair kernel launch: ") + hipGetErrorString((hipError_t)lrc));
     TRY(record_stop(ctx, w.stream, e0, e1));
     lrc = tpcf_launch_reduce_clear(copies, nslots, kQueueWords, d_out, w.stream);
-    w.clear = clear && lrc == 0;
+    if (!captured)
+        w.clear = lrc == 0;
     if (lrc == 0 && touch)
         lrc = tpcf_launch_reduce_copies(touch, nslots, nreg, d_touch, w.stream);
     if (lrc)
