@@ -1,13 +1,11 @@
 """Autotuner for the pair kernels' launch shape.
 
-Knobs: rows held per lane, LDS
-histogram copies per wavefront, the largest column range of a work unit, the
-grid size, the cell-table budget and the table layout field (which no kernel
-reads any more).  The search is a coordinate descent from the library's
-defaults: each knob in turn is swept over its candidates with the others held
-at the best values so far, on a sample of the caller's workload (a block of
-rows against the full column catalog) timed with the library's HIP-event
-kernel timer.  The best shape is applied to the context and cached on disk,
+Knobs: rows held per lane, LDS histogram copies per wavefront, the largest
+column range of a work unit, the grid size and the cell-table budget.  The
+search is a coordinate descent from the library's defaults: each knob in turn
+is swept over its candidates with the others held at the best values so far,
+on a sample of the caller's workload (a block of rows against the full column
+catalog) timed with the library's HIP-event kernel timer.  The best shape is applied to the context and cached on disk,
 keyed by device, HIP runtime, precision and bin count.  Counts never depend
 on the choice.
 """
@@ -26,7 +24,6 @@ CANDIDATES = {
     "hist_copies": (0, 32, 8),
     "max_cols": (0, 16384),
     "blocks_per_cu": (0, 12),
-    "lut_direct": (0, 1),
     "lut_bytes": (0, 16896),
 }
 
@@ -44,7 +41,7 @@ def _device_key(precision: int, nbins: int) -> str:
     except Exception:  # pragma: no cover
         name, hip = "unknown", ""
     # the version part changes whenever the kernels' trade-offs do
-    return f"v4|{name}|hip{hip}|prec{precision}|nbins{nbins}"
+    return f"v5|{name}|hip{hip}|prec{precision}|nbins{nbins}"
 
 
 def _load_cache() -> dict:
