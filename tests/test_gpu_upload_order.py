@@ -84,3 +84,19 @@ def test_stored_order_with_regions(ctx, n):
     np.testing.assert_array_equal(counts, np.bincount(reg, minlength=7))
     x, y, z = oracle.radec_to_xyz(ra, dec)
     np.testing.assert_array_equal(got, _expected_order(x, y, z, reg))
+
+
+@pytest.mark.parametrize("n", [2, 3, 100, 511, 512, 513, 4095, 4096, 8193])
+def test_stored_order_of_few_points(ctx, n):
+    """Up to 511 points are sorted by comparison, more by digits, from 8192 on
+    in chunks: the same order, with and without regions."""
+    x, y, z = _coarse_sphere(n, 17 + n)
+    reg = np.random.default_rng(n).integers(0, 3, n).astype(np.int32)
+    e = np.degrees(np.arctan2(y, x)) % 360.0, np.degrees(np.arcsin(np.clip(z, -1.0, 1.0)))
+    a, b = ctx.upload_catalog_xyz(x, y, z), ctx.upload_catalog_regions(*e, reg, 3)
+    try:
+        np.testing.assert_array_equal(ctx.catalog_order(a), _expected_order(x, y, z))
+        np.testing.assert_array_equal(ctx.catalog_order(b), _expected_order(*oracle.radec_to_xyz(*e), reg))
+    finally:
+        ctx.release_catalog(a)
+        ctx.release_catalog(b)
