@@ -428,10 +428,10 @@ int tpcf_jackknife(const uint64_t *dd, const uint64_t *dd_touch, const uint64_t 
 int tpcf_compile_edges(const double *bin_edges_deg, int32_t nbins, double delta_max,
                        double *out_D, float *out_qlo, float *out_qhi);
 
-/* An FP32 dot-product screen (host only, for CPU tests; no launch uses it): for catalogs whose squared norms deviate from 1 by at most
- * delta_max, a pair whose FP32 copies have p = fl32(f_i . f_j) <= *out_p
- * (with any order of fused or separate roundings) has the rule's d <= D of
- * the last edge, i.e. lies at or beyond it (Section 3, first bullet: the
+/* An FP32 dot-product screen (host only, for CPU tests; no launch uses it):
+ * for catalogs whose squared norms deviate from 1 by at most delta_max, a pair
+ * whose FP32 copies have p = fl32(f_i . f_j) <= *out_p (with any order of
+ * fused or separate roundings) has the rule's d <= D of the last edge, i.e. lies at or beyond it (Section 3, first bullet: the
  * angle from the dot product).  -inf when no pair can pass the last edge. */
 int tpcf_compile_screen(const double *bin_edges_deg, int32_t nbins, double delta_max, float *out_p);
 
@@ -451,28 +451,28 @@ int tpcf_compile_dot(const double *bin_edges_deg, int32_t nbins, double delta_ma
                      float *out_klo, float *out_khi, float *out_plo, float *out_phi, int32_t *out_shift,
                      int32_t *out_lo, int32_t *out_hi, uint16_t *out_cells);
 
-/* Cell table of the pair kernels for the given edges (host only, for CPU
- * tests of the host logic).  precision selects the key: TPCF_FP32_CHORD uses
- * the bits of q = fl32 |f_i - f_j|^2, TPCF_FP64 the high 32 bits of e = 1 - d
- * as a signed integer.  A key maps to cell
- * clamp(key >> shift, lo, hi); entry cells[cell - lo] is a slot (< 0x8000),
- * 0x8000 | k when only edge k is undecided in the cell, or 0xFFFF when
- * several edges are.  direct = 1 (TPCF_FP32_CHORD only) asks for the cells
+/* Cell table for the given edges (host only, for CPU tests of the host logic).
+ * precision selects the key: TPCF_FP32_CHORD uses the bits of
+ * q = fl32 |f_i - f_j|^2 (FP32 launches take the same cells from bands that are
+ * scaled and 2^-10 wider), TPCF_FP64 the high 32 bits of e = 1 - d as a signed
+ * integer.  A key maps to cell clamp(key >> shift, lo, hi); entry
+ * cells[cell - lo] is a slot (< 0x8000), 0x8000 | k when only edge k is
+ * undecided in the cell, or 0xFFFF when several edges are.  direct = 1 (TPCF_FP32_CHORD only) asks for the cells
  * of the wrapped layout (tpcf_compile_wrap32 with max_bytes = max_cells and
  * the default launch's histogram and threshold bytes), in cell order lo..hi;
  * its key is that of q summed from the floor, which always lies in
  * [lo, hi].  It fails with TPCF_E_INVALID if that table would not fit.
- * out_cells must hold max_cells entries (16..33792; the kernels use up to
- * 32768 bytes for wrapped tables, 24576 for other byte tables, 12288 beyond
- * 125 bins); out_E (nbins+1 doubles, may be NULL) receives fl(1 - D_k). */
+ * out_cells must hold max_cells entries (16..33792; launches use at most
+ * 24576 bytes, of one each in FP64 up to 125 bins, else of two); out_E
+ * (nbins+1 doubles, may be NULL) receives fl(1 - D_k). */
 int tpcf_compile_cells(const double *bin_edges_deg, int32_t nbins, int precision, double delta_max,
                        int32_t max_cells, int32_t direct, int32_t *out_shift, int32_t *out_lo,
                        int32_t *out_hi, uint16_t *out_cells, double *out_E);
 
-/* Wrapped FP32 byte table (host only, for CPU tests; the layout of
- * lut_direct = 1).  For unit vectors whose squared norms deviate from 1 by at
- * most delta_max, the kernel forms q = fl(dz^2 + fl(dy^2 + fl(dx^2 + q0)))
- * from the FP32 differences, with the floor q0 = *out_q0, a power of two at
+/* Wrapped FP32 byte table (host only, for CPU tests; no launch uses it: the
+ * layout that lut_direct = 1 asked for).  For unit vectors whose squared norms
+ * deviate from 1 by at most delta_max, a kernel forms
+ * q = fl(dz^2 + fl(dy^2 + fl(dx^2 + q0))) from the FP32 differences, with the floor q0 = *out_q0, a power of two at
  * most a quarter of the smallest positive threshold and at least 2^-100.  Then
  * q < out_qlo[k] implies d > D_k and q >= out_qhi[k] implies d <= D_k (nbins+1
  * floats each, may be NULL), the floor included in the bounds.  Every key

@@ -55,9 +55,9 @@ constexpr double kMaxCoord3d = 1125899906842624.0;    // 2^50: largest |coordina
 constexpr int kPoolStreams = 4;
 
 // Launch shape, set by tpcf_set_tuning (the autotuner) or left at defaults.
-// Zero fields take the defaults, which are the shapes the autotuner picked on
-// the large octant workload: 4 rows per lane, 16 histogram copies,
-// 4096-column units, and clamped cell tables of up to 24 KB.
+// Zero fields take the defaults: rows per lane by the launch's pairs
+// (rows_per_lane_of), 16 histogram copies, units of at most 2048 columns (4096
+// with pruning) and cell tables of up to 24 KB.
 struct Tuning {
     int rows_per_lane = 0;   // 2 or 4
     int hist_copies = 0;     // 4..32, at most what the slot count allows
@@ -1142,11 +1142,7 @@ PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, int rows, u
     // component (sqrt(3) 2^-24 R in all); cp.delta holds R for 3-D edges
     a.prune_margin = cp.metric ? ldexp(cp.delta, -22) + 1e-300 : 0.0;
     a.prune_delta = cp.metric ? 0.0 : delta;
-    // key of the last edge's certain side (see PairArgs::beyond_key)
-    const size_t last = cp.edges.D.size() - 1;
     if (cp.precision == TPCF_FP32_CHORD) {
-        float qh = cp.band.qhi[last];
-        memcpy(&a.beyond_key, &qh, sizeof qh);
         a.q_scale = ldexpf(1.0f, cp.q_exp);
         a.q_exp2 = 2 * cp.q_exp;
         // steps with a column within 7.7 deg of the rows' mean count as chord steps
@@ -1156,8 +1152,9 @@ PairArgs args_of(const tpcf_ctx *ctx, const Compiled &cp, int nbins, int rows, u
             a.tile_slots = (const float2 *)((const float *)cp.dqlo.p + cp.tile_slots_at);
         }
     } else {
-        a.beyond_dot = !cp.metric && cp.edges.D[last] > 0.0;
-        const double t = a.beyond_dot ? cp.edges.D[last] : cp.edges.E[last];
+        // high word of the last edge's threshold (see PairArgs::beyond_key)
+        a.beyond_dot = !cp.metric && cp.edges.D.back() > 0.0;
+        const double t = a.beyond_dot ? cp.edges.D.back() : cp.edges.E.back();
         uint64_t b;
         memcpy(&b, &t, sizeof b);
         a.beyond_key = (uint32_t)(b >> 32);

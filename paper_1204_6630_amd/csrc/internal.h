@@ -125,14 +125,12 @@ struct PairArgs {
     int32_t lut_entry_bytes;     // 1 or 2
     int32_t lut_shift;           // cell = key >> shift
     int32_t lut_lo, lut_hi;      // clamp range of cells
-    // Pairs certainly beyond the last edge: FP32 path, bits(q) >= beyond_key
-    // (the bits of the last edge's qhi); FP64 path, high word of e = 1 - d
-    // above beyond_key as signed integers (e > E_last), or with beyond_dot,
-    // that of d below it (d < D_last).
+    // FP64 path, pairs certainly beyond the last edge: the high word of e =
+    // 1 - d above beyond_key as signed integers (e > E_last), or with
+    // beyond_dot, that of d below it (d < D_last).
     uint32_t beyond_key;
     int32_t beyond_dot;
-    // FP32 tiles: every squared distance (cell table, bands, beyond_key) is
-    // scaled by q_scale^2 = 2^q_exp2, q_scale the power of two that brings the
+    // FP32 tiles: every squared distance (cell table, bands) is scaled by q_scale^2 = 2^q_exp2, q_scale the power of two that brings the
     // coordinates into f16's range.  q_small: steps with a column below it
     // from the rows' mean are counted as chord steps (-inf: none).
     // tile_slots (nslots): lower end and width of every slot; tile_edges
@@ -177,9 +175,8 @@ struct PairArgs {
                                  //  angular FP32 steps that formed the chord]
 };
 
-// LDS bytes per edge: D_k, the FP32 chord band (qlo_k, qhi_k), and either
-// fl(1 - D_k) and the edge in radians (pruning) or the tiles' edge entry.
-
+// LDS bytes per edge: for the tiles D_k, the FP32 chord band (qlo_k, qhi_k)
+// and the tiles' edge entry; FP64 launches use 16 of them (D_k, fl(1 - D_k)).
 constexpr int kEdgeLdsBytes = 8 + 8 + 8 + 8;
 
 // LDS bytes of the histograms (with the discard row) and edge thresholds.

@@ -362,10 +362,8 @@ __device__ __forceinline__ void slot_range(uint32_t e_lo, uint32_t e_hi, uint32_
 
 // One slot for all of a lane's pairs (span 0).  When that holds on every lane
 // the step adds its pairs with one LDS atomic per lane instead of a lookup and
-// an atomic per pair.  A lane's rows (and a wavefront's 256) are consecutive
-// in the Morton order, so at angles large against their extent this is
-// common (on the octant workload 49 % of the FP32 steps that are not beyond
-// the last edge pass).
+// an atomic per pair.  A lane's rows (and a wavefront's) are consecutive in
+// the Morton order, so at angles large against their extent this is common.
 __device__ __forceinline__ bool one_slot_step(uint32_t lo, uint32_t span, uint32_t n, const Consts &k,
                                               Counters &cnt) {
     if (!wave_all(span == 0))
@@ -404,7 +402,7 @@ __device__ __forceinline__ void two_slot_add(uint32_t base, uint32_t n, uint32_t
 // d = |v_i| |v_j| cos(phi) + err with |v_i| |v_j| in [1 - delta, 1 + delta]
 // and |err| <= kPruneDotSlack (the rule's rounding).  So every pair's d lies
 // in [lo - delta |lo| - slack, hi + delta |hi| + slack] for any bounds
-// lo <= cos(phi) <= hi over the block (prune_slot forms them without
+// lo <= cos(phi) <= hi over the block (dot_range forms them without
 // trigonometric functions); when no threshold D_k falls inside that interval
 // every pair passes the same edges, and the wavefront adds the block's pairs
 // to that slot without evaluating them.
@@ -826,9 +824,11 @@ __device__ void rows_fp64(const PairArgs &a, const JobDev &jb, const Smem &s, co
 //      within the neighbouring edges, and the few pairs that lie within e of
 //      the band are settled one by one from FP32 differences and, inside the
 //      band, by the FP64 rule (tile_split);
-//   3. the rest look every pair up in the cell table, by q^ where e is below
-//      2^-16 of it (tile_cells), else by FP32 differences (tile_lookup: close
-//      pairs).
+//   3. the rest take the slots between the cells of a lane's smallest and
+//      largest distance: a few edges are compared with every pair
+//      (tile_count), more send every pair to its own cell (tile_cells); by q^
+//      where e is at most 2^-10 of it (kTileFar), else by FP32 differences
+//      (tile_diffs: close pairs).
 // Tiles with masked pairs (the diagonal, the rows' ends) go to 3.
 //
 // What bounds it: vector issue.  An instruction costs about 4 cycles of a
@@ -1016,7 +1016,7 @@ __device__ __forceinline__ uint32_t settle_row(const TileArgs &a, cjob_p job, co
 }
 
 // Bin one tile with a table lookup per pair, by squared distances q that lie
-// within e of those of the FP32 copies (and within 2^-16 of them, for which
+// within e of those of the FP32 copies (and within 2^-10 of them, for which
 // the cells hold); the first w of the lane's rows count.  Pairs of cells that
 // hold an edge compare q -+ e with its band; those inside it go to the
 // discard row and are settled afterwards, from FP32 differences and by the

@@ -249,3 +249,42 @@ def test_3d_edges_beyond_every_pair(ctx, extent, edges, prec):
     finally:
         for c in (a, b, none):
             ctx.release_catalog(c)
+
+
+@pytest.mark.parametrize("spread", [1e-6, 1e-4, 1e-2, 0.3])
+def test_pairs_within_the_error_of_an_edge(ctx, spread):
+    """The matrix cores' squared distance is trusted beyond e = 2^-24 (24 b^2
+    + 640 r^2) of an edge (b: the column's distance from the rows' mean, r the
+    rows' radius; a constant term is below 3e-13).  Every column lies within 3
+    e of an edge from one of 256 rows spread over `spread` rad: an error larger
+    than e moves a count."""
+    g = synthcat.rng_for(96, 71)
+    e = synthcat.log_edges(0.02, 60.0, 12)
+    c = np.array([0.6, 0.64, np.sqrt(1 - 0.36 - 0.4096)])
+    rows = c[None, :] + g.uniform(-spread, spread, size=(256, 3))
+    rows /= np.linalg.norm(rows, axis=1)[:, None]
+    n = 8192
+    a, k, ph = rows[g.integers(0, 256, n)], g.integers(0, e.size, n), g.uniform(0, 2 * np.pi, n)
+    th = np.radians(e[k])
+    q = 4.0 * np.sin(0.5 * th) ** 2
+    r2 = 3.0 * spread ** 2
+    err = 2.0 ** -24 * (24.0 * (np.sqrt(q) + np.sqrt(r2)) ** 2 + 640.0 * r2) + 3e-13
+    q = np.clip(q + err * g.uniform(-3.0, 3.0, n), 1e-14, 3.9)
+    th = 2.0 * np.arcsin(0.5 * np.sqrt(q))
+    t1 = np.cross(a, [0.0, 0.0, 1.0])
+    t1 /= np.linalg.norm(t1, axis=1)[:, None]
+    t2 = np.cross(a, t1)
+    cols = np.cos(th)[:, None] * a + np.sin(th)[:, None] * (np.cos(ph)[:, None] * t1 + np.sin(ph)[:, None] * t2)
+    cols /= np.linalg.norm(cols, axis=1)[:, None]
+    x, y = rows.T.copy(), cols.T.copy()
+    ca, cb = ctx.upload_catalog_xyz(*x), ctx.upload_catalog_xyz(*y)
+    want = oracle.count(oracle.DR, x, e, b_xyz=y)
+    try:
+        for per_lane in (2, 4):
+            ctx.set_tuning(rows_per_lane=per_lane)
+            assert np.array_equal(ctx.count(tp.DR, ca, e, cat_b=cb), want)
+            assert np.array_equal(ctx.count(tp.DR, cb, e, cat_b=ca), want)
+    finally:
+        ctx.set_tuning()
+        ctx.release_catalog(ca)
+        ctx.release_catalog(cb)
