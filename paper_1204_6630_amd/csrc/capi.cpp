@@ -775,6 +775,23 @@ Unit mk_unit(int64_t i0, int64_t i1, int64_t j0, int64_t j1, int64_t row_lo, int
     return u;
 }
 
+// The units taken in this order.
+std::vector<Unit> in_order(const std::vector<Unit> &units, const std::vector<uint32_t> &order) {
+    std::vector<Unit> out(units.size());
+    for (size_t i = 0; i < out.size(); ++i)
+        out[i] = units[order[i]];
+    return out;
+}
+
+// Units of auto-pairs, listed tile by tile, by the end of their columns, then
+// by rows.
+void by_columns(std::vector<Unit> *units) {
+    std::vector<uint64_t> end(units->size());
+    for (size_t i = 0; i < end.size(); ++i)
+        end[i] = (uint64_t)(*units)[i].j1;
+    *units = in_order(*units, order_of(end));
+}
+
 Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, int rows,
                int64_t max_cols, uint64_t load = 0, bool full = true, double max_units = kMaxUnits) {
     Plan p;
@@ -783,8 +800,10 @@ Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, 
     p.rows = rows;
     const uint64_t pairs = pairs_of(auto_pairs, na, nb, rb, re);
     p.pairs = pairs;
-    const int64_t bj = chunk_width((double)tile_columns(auto_pairs, na, nb, rb, re, T), load ? load : pairs,
-                                   full ? T : tile_rows(re - rb, T), max_cols, 512, max_units);
+    const int64_t columns = tile_columns(auto_pairs, na, nb, rb, re, T);
+    const int64_t bj = chunk_width((double)columns, load ? load : pairs, full ? T : tile_rows(re - rb, T), max_cols, 512,
+                                   max_units);
+    p.units.reserve((size_t)(columns / bj + 3 * ((re - rb + T - 1) / T)));   // (whole chunks, two cut ones a tile, and one)
     // Row tiles start at rb (valid rows from row_lo = rb).
     // Column chunks lie on a common grid of multiples of bj, so units of
     // different row tiles cover the same column ranges; the list is ordered
@@ -812,9 +831,7 @@ Plan make_plan(bool auto_pairs, int64_t na, int64_t nb, int64_t rb, int64_t re, 
                 j0 = j1;
             }
         }
-        std::sort(p.units.begin(), p.units.end(), [](const Unit &x, const Unit &y) {
-            return x.j1 != y.j1 ? x.j1 < y.j1 : x.i0 < y.i0;
-        });
+        by_columns(&p.units);
     } else {
         for (int64_t j0 = 0; j0 < nb; j0 += bj) {
             const int64_t j1 = j0 + bj < nb ? j0 + bj : nb;
@@ -872,9 +889,7 @@ Plan make_plan_regions(bool auto_pairs, int64_t na, int64_t nb, int rows, int64_
                 j = c1;
             }
         }
-        std::sort(p.units.begin(), p.units.end(), [](const Unit &x, const Unit &y) {
-            return x.j1 != y.j1 ? x.j1 < y.j1 : x.i0 < y.i0;
-        });
+        by_columns(&p.units);
     } else {
         for (int64_t j = 0; j < nb;) {
             const int64_t c1 = next_cut(sb, j, nb);
@@ -1811,6 +1826,10 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
         }
         std::vector<JobDev> hj((size_t)njobs);
         std::vector<Unit> hu;
+        size_t n_units = 0;
+        for (const Request &r : reqs)
+            n_units += r.plan->units.size();
+        hu.reserve(n_units);
         for (int32_t k = 0; k < njobs; ++k) {
             hj[k] = job_of(reqs[k], (unsigned long long *)g->copies.p + (size_t)k * kGlobalCopies * nslots, nullptr);
             for (Unit u : reqs[k].plan->units) {
@@ -1819,9 +1838,10 @@ int tpcf_count_batch(tpcf_ctx *ctx, const tpcf_job_desc *jobs, int32_t njobs, in
             }
         }
         // units of all jobs interleaved by size: largest units first
-        std::stable_sort(hu.begin(), hu.end(), [](const Unit &x, const Unit &y) {
-            return (int64_t)(x.i1 - x.i0) * (x.j1 - x.j0) > (int64_t)(y.i1 - y.i0) * (y.j1 - y.j0);
-        });
+        std::vector<uint64_t> size(hu.size());
+        for (size_t i = 0; i < hu.size(); ++i)
+            size[i] = ~((uint64_t)(hu[i].i1 - hu[i].i0) * (uint64_t)(hu[i].j1 - hu[i].j0));
+        hu = in_order(hu, order_of(size));
         if ((rc = upload_blocking(ctx->mem, g->jobs, hj)) || (rc = upload_blocking(ctx->mem, g->units, hu))) {
             free_graph(ctx, *g);
             return rc;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <vector>
 
 #ifdef __HIPCC__
 #define TPCF_HD __host__ __device__ inline
@@ -69,6 +70,38 @@ inline int64_t chunk_width(double columns, uint64_t load, int64_t T, int64_t max
     if ((double)bj < need)
         bj = ((int64_t)need + 256) / 256 * 256;
     return bj;
+}
+
+// Places of keys in ascending order, equal ones in the order that they come:
+// 11 bits at a time, those that differ anywhere.  Unit lists of batches and
+// region counts are ordered by it on their first call (30000 units of an RR
+// list 3.1 -> 1.3 ms with their making; sorting the units themselves took 100
+// ns each).
+inline std::vector<uint32_t> order_of(const std::vector<uint64_t> &key) {
+    const size_t n = key.size();
+    std::vector<uint32_t> at(n), to(n);
+    uint64_t differ = 0;
+    for (size_t i = 0; i < n; ++i) {
+        at[i] = (uint32_t)i;
+        differ |= key[i] ^ key[0];
+    }
+    if (n < 512) {
+        std::stable_sort(at.begin(), at.end(), [&key](uint32_t x, uint32_t y) { return key[x] < key[y]; });
+        return at;
+    }
+    for (int shift = 0; shift < 64; shift += 11) {
+        if (!(differ >> shift & 2047))
+            continue;
+        uint32_t count[2049] = {};
+        for (uint32_t i : at)
+            ++count[(key[i] >> shift & 2047) + 1];
+        for (int v = 0; v < 2048; ++v)
+            count[v + 1] += count[v];
+        for (uint32_t i : at)
+            to[count[key[i] >> shift & 2047]++] = i;
+        at.swap(to);
+    }
+    return at;
 }
 
 // Units of a single request that are computed from their number instead of

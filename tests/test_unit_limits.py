@@ -1,6 +1,7 @@
 """Numbers and sizes of work units at the largest catalogs, and the walks over
-their columns (CPU): compiles tests/c/unit_limits.cpp and column_parts.cpp
-against the library's unit header and runs them."""
+their columns, and the order of unit lists (CPU): compiles unit_limits.cpp,
+column_parts.cpp and unit_order.cpp of tests/c against the library's unit
+header and runs them."""
 
 import os
 import shutil
@@ -29,3 +30,7 @@ def test_units_of_the_largest_requests(tmp_path):
 
 def test_columns_up_to_the_last(tmp_path):
     assert _run("column_parts", tmp_path) > 70
+
+
+def test_unit_lists_are_ordered_stably(tmp_path):
+    assert _run("unit_order", tmp_path) == 54
