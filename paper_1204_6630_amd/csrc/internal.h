@@ -69,8 +69,14 @@ constexpr uint32_t kCellMulti = 2;   // several edges (kCellOpen is set too)
 // with a column at the mean itself; a last edge out of reach), so the number
 // is clamped here, once for all that it is used for.
 TPCF_HD uint32_t nearest_edge(uint32_t slot, float q, float lower, float width, uint32_t nedges) {
-    const int32_t k = (int32_t)slot - (q > fmaf(0.5f, width, lower) ? 0 : 1), last = (int32_t)nedges - 1;
-    return (uint32_t)(k < 0 ? 0 : k > last ? last : k);
+    const int32_t k = q > fmaf(0.5f, width, lower) ? (int32_t)slot : (int32_t)slot - 1, last = (int32_t)nedges - 1;
+#ifdef __HIP_DEVICE_COMPILE__
+    int32_t r;      // (one instruction where the compiler takes two or three)
+    asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(k), "v"(last));
+    return (uint32_t)r;
+#else
+    return (uint32_t)std::min(std::max(k, 0), last);
+#endif
 }
 
 // One work unit: the row tile starting at i0 with valid rows [row_lo, i1),
