@@ -1742,7 +1742,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
                     const bool caps = ie - ib == kRowsPerWave && jb.bcaps;
                     for (int jr = jb0, je; jr < un.j1; jr = je) {
                         je = part_end(jr, un.j1, kPruneCols - (jr & 63));
-                        uint64_t left = blocks_met(jr, je);
+                        uint64_t left;
                         if (caps) {
                             double x[P], y[P], z[P];
 #pragma unroll
@@ -1753,6 +1753,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_pe
                             }
                             left = prune_blocks<M3>(block_cap<M3, P>(x, y, z), jb.bcaps, s, a, k, jr, je, jm,
                                                     kRowsPerWave * 64, lane, cnt);
+                        } else {
+                            left = blocks_met(jr, je);
                         }
                         if (left)
                             rows_tiles<2 * P, M3, true>(args, job, s, k, ib, ie, jr, je, left, lane, cnt);
